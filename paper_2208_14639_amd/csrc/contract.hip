@@ -310,47 +310,58 @@ __device__ __forceinline__ void split2(float v0, float v1, uint32_t &hi, uint32_
     lo = __builtin_bit_cast(uint32_t, l);
 }
 
-// A operands of the block whose 4 j points of this lane are b0[jj], b1[jj].
-__device__ __forceinline__ Aops form_A(const float4 a0, const float4 a1, const float4 *b0,
-                                       const float4 *b1) {
-    uint32_t ph[4], pl[4], qh[4], ql[4];
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj) {
-        float kpp, kpq, kqp, kqq;
-        pair_K(a0, a1, b0[jj], b1[jj], kpp, kpq, kqp, kqq);
-        split2(kpp, kpq, ph[jj], pl[jj]);
-        split2(kqp, kqq, qh[jj], ql[jj]);
+// One pair of a block in three steps of about equal VALU work, so that a
+// caller can place each step between MFMAs: (0) the geometry and its
+// reciprocal, (1) the four kernel values of pair_K, (2) their hi/lo split.
+// The arithmetic is that of pair_K and split2, operation for operation.
+struct PairSteps {
+    float R2, gg, gp, s, t, r, kpp, kpq, kqp, kqq;
+    __device__ __forceinline__ void geometry(const float4 a0, const float4 a1, const float4 b0,
+                                             const float2 b1) {
+        const float dx = a0.x - b0.x, dy = a0.y - b0.y, dz = a0.z - b0.z;
+        R2 = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, dz * dz));
+        gg = __builtin_fmaf(a0.w, R2, a1.x);
+        gp = __builtin_fmaf(b0.w, R2, b1.x);
+        s = gg + gp;
+        t = gg * gp;
+        r = rcp32(t * s);
     }
-    Aops A;
-    A.ph = __builtin_bit_cast(bf16x8, (uint4){ph[0], ph[1], ph[2], ph[3]});
-    A.pl = __builtin_bit_cast(bf16x8, (uint4){pl[0], pl[1], pl[2], pl[3]});
-    A.qh = __builtin_bit_cast(bf16x8, (uint4){qh[0], qh[1], qh[2], qh[3]});
-    A.ql = __builtin_bit_cast(bf16x8, (uint4){ql[0], ql[1], ql[2], ql[3]});
-    return A;
-}
+    __device__ __forceinline__ void values(float ci, float cj) {
+        const float sr = s * r, is = t * r;
+        const float A = r * __builtin_fmaf(gp, sr, is);
+        const float Ap = r * __builtin_fmaf(gg, sr, is);
+        const float Q = (r + r) * __builtin_fmaf(is, is, sr);
+        const float t1 = __builtin_fmaf(ci, Q, -Ap);
+        const float t2 = __builtin_fmaf(cj, Q, -A);
+        kpp = __builtin_fmaf(cj, t1, __builtin_fmaf(-ci, A, r));
+        kpq = R2 * t1;
+        kqp = R2 * t2;
+        kqq = (R2 * R2) * Q;
+    }
+};
 
-// Clear K_pp of the self pair in the A operands of the diagonal block (lane
-// (m, g) forms pairs (ibase + m, ibase + 4 g + e), e = 0..3; K_pp is the low
-// half of word e of ph and pl).
-__device__ __forceinline__ void mask_self(Aops &A, int m, int g) {
-    const uint4 k = bf16_clear_mask(g == (m >> 2), m & 3, false);
-    A.ph = bf16_apply_mask(A.ph, k);
-    A.pl = bf16_apply_mask(A.pl, k);
-}
-
-// Software pipeline per wave (four waves and 16-point stages below eight
-// column blocks; eight waves and 32-point stages from eight on):
-//  * the X of a stage (hi and lo, all columns of the group) is
-//    double-buffered in LDS; the next stage's X goes straight from global
-//    memory into the other buffer (global_load_lds) while this stage's MFMAs
-//    run, and one wait plus one barrier per stage publish it;
-//  * the VALU forms the A operands of the next block from point data loaded
-//    one block ahead straight from global memory; the instruction scheduler
-//    interleaves it with the MFMAs of the current block (measured: forcing a
-//    fixed MFMA/VALU interleave, staging point data through LDS or forcing
-//    three waves per SIMD were all slower on the 20-water grid).
+// Software pipeline per wave, in stages of 32 j points (two 16-point
+// blocks) and chunks of one column block (six MFMAs per chunk):
+//  * X of a stage (hi and lo, all columns of the group) and the points whose
+//    pairs are formed during it are double-buffered in LDS and go there
+//    straight from global memory, issued one stage ahead;
+//  * a chunk's B operands are read from LDS kAhead chunks before their MFMAs,
+//    so that no LDS latency is exposed;
+//  * the next block's A operands are formed meanwhile, a twelfth of the
+//    block's pair arithmetic after each twelfth of its chunks: one wave's
+//    VALU work issues under its own and the other waves' MFMAs;
+//  * the barrier that closes a stage stands kAhead chunks before the stage's
+//    last MFMAs: every read of the stage's buffer has then been issued, and
+//    the chunks that follow cover the first reads of the next one.
+// What bounds it (20-water grid, twelve blocks): 72 MFMAs of 16 cycles and 172
+// VALU instructions per wave and 16-point block.  The form with the waits
+// exposed took 107 M cycles per XCD at 2.05 GHz (matrix cores busy 60 %), this
+// one 87 M at 1.88 GHz (73 %): the clock falls as the cycles do, by the card's
+// power limit, so only less work (without the VALU share: 36.9 ms) would gain
+// more.  Contraction about 50.5 -> 46.3 ms; at four blocks (hexamer), bound by
+// VALU issue, 1.45 -> 1.30 ms.
 template <int NCB>
-constexpr int smem_bf16x3() { return 2 * 2 * NCB * 16 * 4 * (int)sizeof(bf16x8); }
+constexpr int smem_bf16x3() { return (4 * NCB + 2) * 64 * (int)sizeof(bf16x8); }
 
 template <int NCB, bool SCR = false, int WAVES = 4>
 __device__ __forceinline__ void tile_bf16x3(int64_t npad, int64_t jlen, int32_t Pp,
@@ -359,18 +370,20 @@ __device__ __forceinline__ void tile_bf16x3(int64_t npad, int64_t jlen, int32_t 
                                             const bf16x8 *__restrict__ Xhi,
                                             const bf16x8 *__restrict__ Xlo,
                                             double *__restrict__ Yout, int64_t itile, int grp,
-                                            int split, char *smem,
-                                            const uint32_t *__restrict__ mask = nullptr,
-                                            char *smem2 = nullptr) {
+                                            int split, char *smem, char *smem2,
+                                            const uint32_t *__restrict__ mask = nullptr) {
     constexpr int NC = NCB * 16;
-    static_assert(kFp32Run % 32 == 0, "FP32 runs end on stage boundaries");
-    constexpr int UNITS = NC * 4;                       // 8-bf16 units per block and array
+    static_assert(kFp32Run % 64 == 0, "FP32 runs end on stage pairs");
+    constexpr int UNITS = NCB * 64;                     // 8-bf16 units per block and array
     constexpr int NT = 64 * WAVES;                      // threads of the workgroup
-    constexpr int PER = (UNITS + NT - 1) / NT;          // units per thread and array
-    typedef bf16x8 Buf[UNITS];
-    Buf *sH = reinterpret_cast<Buf *>(smem);            // [buffer][col][g]
-    Buf *sL = sH + 2;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int PER = (2 * UNITS + NT - 1) / NT;      // units per thread, stage and array
+    constexpr int kAhead = NCB == 1 ? 1 : 2;
+    // a stage buffer: X hi then lo of two blocks, [block][cb][lane], and 32
+    // points (64 units of P0, then 64 of P1); the two buffers are distinct LDS arrays, so that
+    // the compiler sees that a stage's reads and the loads into the other
+    // buffer never alias
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m = lane & 15, g = lane >> 4;
     const int64_t ibase = itile * (16 * WAVES) + wave * 16;
     const int col0 = grp * NC;
@@ -411,126 +424,134 @@ __device__ __forceinline__ void tile_bf16x3(int64_t npad, int64_t jlen, int32_t 
         }
         first = false;
     };
-    // X of one 16-point block straight from global memory into LDS buffer b
-    // (global_load_lds_dwordx4: lane l of a wave writes the 16 bytes at the
-    // wave's LDS base + 16 l, so unit e = tid + NT k lands at unit e; the
-    // source is a uniform block base plus the lane's unit)
-    const int wv = __builtin_amdgcn_readfirstlane(wave);
-    auto dma_x = [&](int64_t blk, int b) {
-        const int64_t base = ((blk / 16) * Pp + col0) * 4;
-        const bf16x8 *bh = Xhi + base, *bl = Xlo + base;
+    // A stage's 32 points go into a buffer straight from global memory
+    // (buffer_load_dwordx4 ... lds: lane l of a wave writes the 16 bytes at
+    // the wave's LDS base + 16 l, so unit e = tid + NT k lands at unit e), in
+    // PER pieces of hi and lo and one of points, issued one piece per chunk
+    // after the barrier that frees the buffer: issued together they kept the
+    // waves from their MFMAs for some 600 cycles a stage.  The source of piece
+    // k is the stage's base (uniform, in the descriptor) plus a 32-bit offset
+    // fixed over the stages, and the LDS base is uniform, so a piece costs no
+    // vector address arithmetic.  The buffer form matters: with a
+    // global_load_lds pending the compiler makes every wait on an LDS read a
+    // full one (it takes the instruction for a flat access).
+    // (first unit of this wave's piece k, uniform; where the waves outnumber
+    // the units left, some bring units that another wave brings too)
+    auto first_unit = [&](int k) { return (wave * 64 + NT * k) % (2 * UNITS); };
+    uint32_t xoff[PER];
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int e0 = wv * 64 + NT * k;            // first unit of this wave (uniform)
-            if (UNITS % NT == 0 || e0 < UNITS) {        // UNITS is a multiple of 64
-                __builtin_amdgcn_global_load_lds(
-                    static_cast<const void *>(bh + e0 + lane),
-                    reinterpret_cast<__attribute__((address_space(3))) void *>(
-                        reinterpret_cast<uintptr_t>(&sH[b][e0])), 16, 0, 0);
-                __builtin_amdgcn_global_load_lds(
-                    static_cast<const void *>(bl + e0 + lane),
-                    reinterpret_cast<__attribute__((address_space(3))) void *>(
-                        reinterpret_cast<uintptr_t>(&sL[b][e0])), 16, 0, 0);
-            }
-        }
+    for (int k = 0; k < PER; ++k) {
+        const int e = first_unit(k) + lane;
+        const int sub = e >= UNITS;
+        xoff[k] = (uint32_t)(sub * Pp * 4 + (e - sub * UNITS)) * (uint32_t)sizeof(bf16x8);
+    }
+    auto to_lds = [](const void *base, uint32_t off, bf16x8 *dst) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, -1, 0x00027000),
+            reinterpret_cast<__attribute__((address_space(3))) void *>(
+                reinterpret_cast<uintptr_t>(dst)), 16, off, 0, 0, 0);
     };
-    // Screened form: X of a block through registers (loaded before the
-    // block's MFMAs, stored to the other buffer after them).  Its pair
-    // arithmetic sits between the column blocks' MFMA groups and waits for
-    // point data there; with X loads straight into LDS pending, the compiler
-    // makes that wait a full one (it treats the load counter as unordered),
-    // which also waited for the next block's X (measured with this form at
-    // twelve column blocks on the 20-water grid: 52.5 ms that way, 44.9 ms
-    // through registers).
-    bf16x8 rh[PER], rl[PER];
-    auto load_x = [&](int64_t blk) {
-        const int64_t base = ((blk / 16) * Pp + col0) * 4;
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int e = tid + NT * k;
-            if (e < UNITS) {
-                rh[k] = Xhi[base + e];
-                rl[k] = Xlo[base + e];
-            }
+    // piece k of the stage at j
+    auto load_piece = [&](int k, int64_t j, bf16x8 *buf) {
+        if (k == PER) {
+            // the points whose pairs are formed during the stage, j + 16 ..
+            // j + 47 (clamped: past the grid they are formed but never used):
+            // even waves bring P0, odd ones P1, the upper lanes the same again
+            const uint32_t left = (uint32_t)min(npad - 1 - j, (int64_t)64);
+            to_lds((wave & 1 ? P1 : P0) + j, min(16u + (lane & 31), left) * (uint32_t)sizeof(float4),
+                   buf + 4 * UNITS + 64 * (wave & 1));
+            return;
         }
+        const int e0 = first_unit(k);
+        const int64_t base = (j / 16) * Pp * 4 + col0 * 4;
+        to_lds(Xhi + base, xoff[k], buf + e0);
+        to_lds(Xlo + base, xoff[k], buf + 2 * UNITS + e0);
     };
-    auto store_x = [&](int b) {
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int e = tid + NT * k;
-            if (e < UNITS) {
-                sH[b][e] = rh[k];
-                sL[b][e] = rl[k];
-            }
-        }
-    };
-    // point data of this lane's 4 j of a block: j = blk + 4 g + jj
-    float4 n0[4], n1[4];
-    auto load_pts = [&](int64_t blk) {
-        const int64_t jq = min(blk, npad - 16) + 4 * g;   // clamped: never read past npad
+    // points of this lane's four pairs of a block: (x, y, z, omega), (kappa, c)
+    float4 n0[4];
+    float2 n1[4];
+    auto read_points = [&](const bf16x8 *buf, int sub) {
+        const float4 *q = reinterpret_cast<const float4 *>(buf + 4 * UNITS) + 16 * sub + 4 * g;
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) {
-            n0[jj] = P0[jq + jj];
-            n1[jj] = P1[jq + jj];
+            n0[jj] = q[jj];
+            n1[jj] = make_float2(q[64 + jj].x, q[64 + jj].z);
         }
     };
-    if constexpr (WAVES == 8) {
-        // Stages of 32 points: the X of two 16-point blocks is staged at
-        // once and the two blocks' MFMAs run between one pair of barriers.
-        // The A operands alternate between two register sets, each formed
-        // while the other's MFMAs run.
-        // The two stage buffers are distinct LDS arrays (smem: buffer 0,
-        // smem2: buffer 1), each hi then lo of two 16-point blocks; with the
-        // stages unrolled in pairs the compiler sees that a stage's LDS reads
-        // and its loads into the other buffer never alias, and waits for
-        // those loads only at the stage's end.
-        typedef bf16x8 Buf2[2 * UNITS];                 // [sub-block][col][g]
-        Buf2 &H0 = *reinterpret_cast<Buf2 *>(smem), &L0 = *(reinterpret_cast<Buf2 *>(smem) + 1);
-        Buf2 &H1 = *reinterpret_cast<Buf2 *>(smem2), &L1 = *(reinterpret_cast<Buf2 *>(smem2) + 1);
-        constexpr int PER2 = (2 * UNITS + NT - 1) / NT;
-        // X of points j .. j + 31 straight from global memory into LDS
-        // (global_load_lds_dwordx4: lane l of a wave writes the 16 bytes at
-        // the wave's LDS base + 16 l, so unit e = tid + NT k lands at unit e).
-        // The source of piece k is a stage base (uniform, in SGPRs) plus a
-        // per-lane 32-bit offset fixed over the stages; the LDS base is
-        // uniform too, so a piece costs no 64-bit address arithmetic.
-        const int wv = __builtin_amdgcn_readfirstlane(wave);
-        uint32_t xoff[PER2];
+    // the diagonal block leaves out the self pair: it is pair m mod 4 of lane
+    // (m, g = m/4), whose K_pp is cleared (K_pq, K_qp, K_qq vanish there, R = 0);
+    // a lane mask selected by a uniform test, as a branch would split the block
+    bool self[4];
 #pragma unroll
-        for (int k = 0; k < PER2; ++k) {
-            const int e = wv * 64 + NT * k + lane;
-            const int sub = e >= UNITS;
-            xoff[k] = (uint32_t)(sub * Pp * 4 + (e - sub * UNITS));
+    for (int jj = 0; jj < 4; ++jj) self[jj] = m == 4 * g + jj;
+    PairSteps ps;
+    uint32_t ph[4], pl[4], qh[4], ql[4];
+    // (the empty asm statements keep each step's instructions in its chunk)
+    auto step = [&](int k, bool diag) {                 // k = 3 pair + step
+        const int jj = k / 3;
+        if (k % 3 == 0) {
+            ps.geometry(a0, a1, n0[jj], n1[jj]);
+            asm volatile("" : "+v"(ps.R2), "+v"(ps.gg), "+v"(ps.gp), "+v"(ps.s), "+v"(ps.t), "+v"(ps.r));
+        } else if (k % 3 == 1) {
+            ps.values(a1.z, n1[jj].y);
+            ps.kpp = diag && self[jj] ? 0.f : ps.kpp;
+            asm volatile("" : "+v"(ps.kpp), "+v"(ps.kpq), "+v"(ps.kqp), "+v"(ps.kqq));
+        } else {
+            split2(ps.kpp, ps.kpq, ph[jj], pl[jj]);
+            split2(ps.kqp, ps.kqq, qh[jj], ql[jj]);
+            asm volatile("" : "+v"(ph[jj]), "+v"(pl[jj]), "+v"(qh[jj]), "+v"(ql[jj]));
         }
-        auto load2 = [&](int64_t j, Buf2 &H, Buf2 &L) {
-            const int64_t base = ((j / 16) * Pp + col0) * 4;
-            const bf16x8 *bh = Xhi + base, *bl = Xlo + base;
-#pragma unroll
-            for (int k = 0; k < PER2; ++k) {
-                const int e0 = wv * 64 + NT * k;        // first unit of this wave (uniform)
-                // 2 UNITS is a multiple of 64; when it is one of NT, every
-                // wave loads PER2 pieces
-                if ((2 * UNITS) % NT == 0 || e0 < 2 * UNITS) {
-                    __builtin_amdgcn_global_load_lds(
-                        static_cast<const void *>(bh + xoff[k]),
-                        reinterpret_cast<__attribute__((address_space(3))) void *>(
-                            reinterpret_cast<uintptr_t>(&H[e0])), 16, 0, 0);
-                    __builtin_amdgcn_global_load_lds(
-                        static_cast<const void *>(bl + xoff[k]),
-                        reinterpret_cast<__attribute__((address_space(3))) void *>(
-                            reinterpret_cast<uintptr_t>(&L[e0])), 16, 0, 0);
-                }
-            }
-        };
+    };
+    auto formed = [&]() {
+        Aops A;
+        A.ph = __builtin_bit_cast(bf16x8, (uint4){ph[0], ph[1], ph[2], ph[3]});
+        A.pl = __builtin_bit_cast(bf16x8, (uint4){pl[0], pl[1], pl[2], pl[3]});
+        A.qh = __builtin_bit_cast(bf16x8, (uint4){qh[0], qh[1], qh[2], qh[3]});
+        A.ql = __builtin_bit_cast(bf16x8, (uint4){ql[0], ql[1], ql[2], ql[3]});
+        return A;
+    };
+    // B operands (hi, lo) of the chunks in flight
+    bf16x8 Bh[kAhead + 1], Bl[kAhead + 1];
+    // one stage: A holds the operands of its first block on entry and those
+    // of the next stage's first block on return
+    auto stage = [&](int64_t j0, bf16x8 *cur, bf16x8 *nxt, Aops &A) {
         // screened: a column block whose mask bit is clear skips its MFMAs
-        // (the mask word of the 16-point block at jb)
-        auto mfmas = [&](const Aops &A, const bf16x8 *hp, const bf16x8 *lp, int64_t jb) {
-            uint32_t mw = ~0u;
-            if constexpr (SCR) mw = mask[(jb >> 4) * ((Pp >> 4) / NCB) + grp];
+        uint32_t mw[2] = {~0u, ~0u};
+        if constexpr (SCR)
 #pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) {
-                if (SCR && !((mw >> cb) & 1u)) continue;
-                const bf16x8 bh = hp[cb * 64], bl = lp[cb * 64];
+            for (int sub = 0; sub < 2; ++sub)
+                mw[sub] = mask[((j0 >> 4) + sub) * ((Pp >> 4) / NCB) + grp];
+#pragma unroll
+        for (int c = 0; c < 2 * NCB; ++c) {
+            const int sub = c / NCB, cb = c - sub * NCB;
+            if (c == 2 * NCB - kAhead) {
+                __builtin_amdgcn_s_waitcnt(0);   // this wave's LDS loads and reads are done
+                __syncthreads();
+            }
+            // pieces of the next stage (past the last one: that one again)
+#pragma unroll
+            for (int k = 0; k <= PER; ++k)
+                if (c == (k < 2 * NCB - kAhead ? k : 2 * NCB - kAhead - 1))
+                    load_piece(k, min(j0 + 32, jend - 32), nxt);
+            // (issue priority falls along the stage, so that of the waves of a
+            // SIMD the one behind goes first and they reach the barrier together)
+            if (WAVES == 8 && (4 * c) % (2 * NCB) < 4) {
+                const int q = 4 * c / (2 * NCB);
+                if (q == 0) __builtin_amdgcn_s_setprio(3);
+                if (q == 1) __builtin_amdgcn_s_setprio(2);
+                if (q == 2) __builtin_amdgcn_s_setprio(1);
+                if (q == 3) __builtin_amdgcn_s_setprio(0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            {
+                const int pc = c + kAhead, q = pc % (2 * NCB);
+                const bf16x8 *b = (pc < 2 * NCB ? cur : nxt) + q * 64 + lane;
+                Bh[kAhead] = b[0];
+                Bl[kAhead] = b[2 * UNITS];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (!SCR || ((mw[sub] >> cb) & 1u)) {
+                const bf16x8 bh = Bh[0], bl = Bl[0];
                 accp[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A.ph, bh, accp[cb], 0, 0, 0);
                 accq[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A.qh, bh, accq[cb], 0, 0, 0);
                 accp[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A.pl, bh, accp[cb], 0, 0, 0);
@@ -538,125 +559,50 @@ __device__ __forceinline__ void tile_bf16x3(int64_t npad, int64_t jlen, int32_t 
                 accp[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A.ph, bl, accp[cb], 0, 0, 0);
                 accq[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A.qh, bl, accq[cb], 0, 0, 0);
             }
-        };
-        load_pts(jbeg);
-        load2(jbeg, H0, L0);
-        Aops cur = form_A(a0, a1, n0, n1);
-        load_pts(jbeg + 16);
-        __builtin_amdgcn_s_waitcnt(0);   // this wave's LDS loads are done
-        __syncthreads();
-        // one 32-point stage on buffer (Hc, Lc), loading the next into (Hn, Ln)
-        auto stage = [&](int64_t j0, Buf2 &Hc, Buf2 &Lc, Buf2 &Hn, Buf2 &Ln) {
-            if (j0 + 32 < jend) load2(j0 + 32, Hn, Ln);   // every wave finished reading it
-            // the diagonal block: the self pair (i, i) of lane (m, g = m/4) is
-            // its pair m mod 4, whose K_pp (the low half of word m mod 4 of ph,
-            // pl) is cleared; K_pq, K_qp, K_qq vanish there (R = 0)
-            if (j0 == ibase) mask_self(cur, m, g);
-            Aops alt = form_A(a0, a1, n0, n1);      // points j0 + 16 ..
-            load_pts(j0 + 32);
-            mfmas(cur, Hc + m * 4 + g, Lc + m * 4 + g, j0);
-            if (j0 + 16 == ibase) mask_self(alt, m, g);
-            cur = form_A(a0, a1, n0, n1);           // points j0 + 32 ..
-            load_pts(j0 + 48);
-            mfmas(alt, Hc + UNITS + m * 4 + g, Lc + UNITS + m * 4 + g, j0 + 16);
-            __builtin_amdgcn_s_waitcnt(0);   // this wave's LDS loads of the next stage
-            __syncthreads();
-        };
-        // a split holds a whole number of 32-point stages (jbeg and jlen are
-        // multiples of 32, npad of 256)
-        static_assert(kFp32Run % 64 == 0, "FP32 runs end on stage pairs");
-        for (int64_t j0 = jbeg; j0 < jend; j0 += 64) {
-            stage(j0, H0, L0, H1, L1);
-            if (j0 + 32 < jend) stage(j0 + 32, H1, L1, H0, L0);
-            if ((j0 + 64 - jbeg) % kFp32Run == 0 && j0 + 64 < jend) flush();
+#pragma unroll
+            for (int k = 0; k < 12; ++k)
+                if (k * NCB / 12 == cb) step(k, j0 + 16 * sub + 16 == ibase);
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) {
+                Bh[k] = Bh[k + 1];
+                Bl[k] = Bl[k + 1];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (cb == NCB - 1) {
+                A = formed();
+                read_points(sub ? nxt : cur, sub ^ 1);
+            }
         }
-    } else {
-    load_pts(jbeg);
-    if constexpr (SCR) {
-        load_x(jbeg);
-        store_x(0);
-    } else {
-        dma_x(jbeg, 0);
+    };
+    bf16x8 *buf0 = reinterpret_cast<bf16x8 *>(smem), *buf1 = reinterpret_cast<bf16x8 *>(smem2);
+    Aops A;
+#pragma unroll
+    for (int k = 0; k <= PER; ++k) load_piece(k, jbeg, buf0);
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+        n0[jj] = P0[jbeg + 4 * g + jj];
+        n1[jj] = make_float2(P1[jbeg + 4 * g + jj].x, P1[jbeg + 4 * g + jj].z);
     }
-    Aops cur = form_A(a0, a1, n0, n1);
-    load_pts(jbeg + 16);
-    __builtin_amdgcn_s_waitcnt(0);   // this wave's LDS loads are done
+#pragma unroll
+    for (int k = 0; k < 12; ++k) step(k, jbeg == ibase);
+    A = formed();
+    __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    int buf = 0;
-    for (int64_t j0 = jbeg; j0 < jend; j0 += 16) {
-        // the diagonal block: the self pair (i, i) of lane (m, g = m/4) is its
-        // pair m mod 4, whose K_pp (the low half of word m mod 4 of ph, pl) is
-        // cleared; K_pq, K_qp, K_qq vanish there (R = 0)
-        if (j0 == ibase) mask_self(cur, m, g);
-        const bool more = j0 + 16 < jend;
-        if (more) {
-            if constexpr (SCR) load_x(j0 + 16);
-            else dma_x(j0 + 16, buf ^ 1);   // every wave finished reading it
-        }
-        const bf16x8 *hp = sH[buf] + m * 4 + g;
-        const bf16x8 *lp = sL[buf] + m * 4 + g;
-        Aops nxt;
-        if constexpr (!SCR) {
-            nxt = form_A(a0, a1, n0, n1);
-            load_pts(j0 + 32);
 #pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) {
-                const bf16x8 bh = hp[cb * 64], bl = lp[cb * 64];
-                accp[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.ph, bh, accp[cb], 0, 0, 0);
-                accq[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.qh, bh, accq[cb], 0, 0, 0);
-                accp[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.pl, bh, accp[cb], 0, 0, 0);
-                accq[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.ql, bh, accq[cb], 0, 0, 0);
-                accp[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.ph, bl, accp[cb], 0, 0, 0);
-                accq[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.qh, bl, accq[cb], 0, 0, 0);
-            }
-        } else {
-            // Screened: the skipped blocks are branches, which the compiler
-            // does not schedule across, so the next block's A operands are
-            // formed one pair at a time between the column blocks' MFMA
-            // groups (the MFMAs in flight overlap the pair arithmetic).
-            const uint32_t mw = mask[(j0 >> 4) * ((Pp >> 4) / NCB) + grp];
-            uint32_t ph[4], pl[4], qh[4], ql[4];
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) {
-                if ((mw >> cb) & 1u) {
-                    const bf16x8 bh = hp[cb * 64], bl = lp[cb * 64];
-                    accp[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.ph, bh, accp[cb], 0, 0, 0);
-                    accq[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.qh, bh, accq[cb], 0, 0, 0);
-                    accp[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.pl, bh, accp[cb], 0, 0, 0);
-                    accq[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.ql, bh, accq[cb], 0, 0, 0);
-                    accp[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.ph, bl, accp[cb], 0, 0, 0);
-                    accq[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.qh, bl, accq[cb], 0, 0, 0);
-                }
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) {
-                    if (jj * NCB / 4 != cb) continue;      // pair jj after column block jj NCB/4
-                    // empty asm statements pin the pair arithmetic to this
-                    // point (after this column block's MFMAs are issued)
-                    asm volatile("" : "+v"(n0[jj].x), "+v"(n0[jj].y), "+v"(n0[jj].z), "+v"(n0[jj].w),
-                                 "+v"(n1[jj].x), "+v"(n1[jj].z));
-                    float kpp, kpq, kqp, kqq;
-                    pair_K(a0, a1, n0[jj], n1[jj], kpp, kpq, kqp, kqq);
-                    split2(kpp, kpq, ph[jj], pl[jj]);
-                    split2(kqp, kqq, qh[jj], ql[jj]);
-                    asm volatile("" ::"v"(ph[jj]), "v"(pl[jj]), "v"(qh[jj]), "v"(ql[jj]));
-                }
-            }
-            nxt.ph = __builtin_bit_cast(bf16x8, (uint4){ph[0], ph[1], ph[2], ph[3]});
-            nxt.pl = __builtin_bit_cast(bf16x8, (uint4){pl[0], pl[1], pl[2], pl[3]});
-            nxt.qh = __builtin_bit_cast(bf16x8, (uint4){qh[0], qh[1], qh[2], qh[3]});
-            nxt.ql = __builtin_bit_cast(bf16x8, (uint4){ql[0], ql[1], ql[2], ql[3]});
-            load_pts(j0 + 32);
-        }
-        cur = nxt;
-        if constexpr (SCR) {
-            if (more) store_x(buf ^ 1);
-        }
-        if ((j0 + 16 - jbeg) % kFp32Run == 0 && more) flush();
-        __builtin_amdgcn_s_waitcnt(0);   // this wave's LDS loads of the next block
-        __syncthreads();
-        buf ^= 1;
+    for (int k = 0; k < kAhead; ++k) {
+        Bh[k] = buf0[k * 64 + lane];
+        Bl[k] = buf0[2 * UNITS + k * 64 + lane];
     }
+    read_points(buf0, 0);
+    // a split holds a whole number of 32-point stages (jbeg and jlen are
+    // multiples of 32, npad of 256)
+    int64_t j0 = jbeg;
+    for (; j0 + 64 <= jend; j0 += 64) {
+        stage(j0, buf0, buf1, A);
+        stage(j0 + 32, buf1, buf0, A);
+        if ((j0 + 64 - jbeg) % kFp32Run == 0 && j0 + 64 < jend) flush();
     }
+    if (j0 < jend) stage(j0, buf0, buf1, A);
     flush();
 }
 
@@ -687,15 +633,11 @@ __global__ __launch_bounds__(256, 2) void k_contract_f32(int64_t npad, int64_t j
                        mask);
 }
 
-// Waves (16 outer points each) of the standalone split-BF16 kernel, by
-// column blocks: with eight or more blocks the MFMA work per pair dominates
-// and eight waves share each staged X block in 32-point stages (one barrier
-// per two MFMA blocks: 56.5 -> 53.0 ms on the 20-water grid); with fewer,
-// four waves in 16-point stages keep three to four waves per SIMD (the
-// 32-point stages' registers would drop it to two).  Screened, the
-// eight-wave form skips a column block's MFMAs behind a branch (its MFMA and
-// VALU work do not overlap anyway: screened 20-water contraction 37.3 ms,
-// against 45.0 in the four-wave screened form and 49-50 unscreened).
+// Waves (16 outer points each) of the split-BF16 kernels, by column blocks:
+// from eight blocks on, eight waves share each staged X (two per SIMD; their
+// accumulators leave room for no more), below four waves, whose workgroups
+// then fill the SIMDs with three or four waves each (eight waves at four
+// column blocks: 1.46 against 1.29-1.30 ms on the hexamer).
 template <int NCB>
 constexpr int bf16_waves() { return NCB >= kWideMinNcb ? 8 : 4; }
 
@@ -708,11 +650,10 @@ __global__ __launch_bounds__(64 * bf16_waves<NCB>(), 8 / bf16_waves<NCB>()) void
                                                             double *__restrict__ Yout,
                                                             const uint32_t *__restrict__ mask) {
     __shared__ __attribute__((aligned(16))) char smem[smem_bf16x3<NCB>()];
-    // the second stage buffer of the eight-wave form (a one-byte dummy otherwise)
-    __shared__ __attribute__((aligned(16))) char smem2[bf16_waves<NCB>() == 8 ? smem_bf16x3<NCB>() : 1];
+    __shared__ __attribute__((aligned(16))) char smem2[smem_bf16x3<NCB>()];   // the other stage
     tile_bf16x3<NCB, SCR, bf16_waves<NCB>()>(npad, jlen, Pp, P0, P1, Xhi, Xlo, Yout,
-                                             blockIdx.x, blockIdx.y, blockIdx.z, smem, mask,
-                                             smem2);
+                                             blockIdx.x, blockIdx.y, blockIdx.z, smem, smem2,
+                                             mask);
 }
 
 template <int NCB, bool SCR>
@@ -747,24 +688,14 @@ hipError_t run(vv10_plan *p, const Workspace &ws, bool screen) {
 }
 
 template <int NCB>
-int occupancy(vv10_precision prec) {
+int occupancy_f64() {
     int nb = 0;
-    hipError_t e;
-    if (prec == VV10_FP64) {
-        if constexpr (NCB <= 8)
-            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_contract_f64<NCB, false>, 256, 0);
-        else
+    if constexpr (NCB <= 8) {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_contract_f64<NCB, false>, 256, 0) !=
+            hipSuccess) {
+            (void)hipGetLastError();
             return 0;
-    } else if (prec == VV10_MIXED_FP32) {
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_contract_f32<NCB, false>, 256, 0);
-    } else {
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_contract_bf16x3<NCB, false>,
-                                                         64 * bf16_waves<NCB>(), 0);
-        nb *= bf16_waves<NCB>() / 4;   // in units of 64-point tiles, as the other modes
-    }
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        return 0;
+        }
     }
     return nb;
 }
@@ -822,8 +753,8 @@ struct PersistentTraits<VV10_MIXED_BF16X3> {
     // counts only, whose smaller register allocation leaves room for more
     // waves per SIMD
     static constexpr int kMaxNcb = kWideMinNcb - 1;
-    static constexpr int kSmem = smem_bf16x3<kWideMinNcb - 1>();
     static constexpr int kWaves = 4;
+    static constexpr int kSmem = smem_bf16x3<kWideMinNcb - 1>();
 };
 
 template <int PREC, int NCB>
@@ -842,7 +773,7 @@ __device__ __forceinline__ void run_item(const BatchMol &d, const BatchItem &it,
         tile_bf16x3<NCB, false, PersistentTraits<PREC>::kWaves>(
             d.npad, d.jlen, d.Pp, static_cast<const float4 *>(d.P0),
             static_cast<const float4 *>(d.P1), xh, xh + d.npad * d.Pp * 2 / 8,
-            static_cast<double *>(d.Ypart), it.itile, it.grp, it.split, smem, nullptr, smem2);
+            static_cast<double *>(d.Ypart), it.itile, it.grp, it.split, smem, smem2);
     }
 }
 
@@ -878,13 +809,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PREC == VV10
 }
 
 template <int PREC>
-__global__ __launch_bounds__(64 * PersistentTraits<PREC>::kWaves, 8 / PersistentTraits<PREC>::kWaves) void k_contract_persistent(
+__global__ __launch_bounds__(64 * PersistentTraits<PREC>::kWaves, 2) void k_contract_persistent(
     const BatchMol *__restrict__ mols, const BatchItem *__restrict__ items, int32_t n_items,
     int32_t *__restrict__ counter) {
-    constexpr int W = PersistentTraits<PREC>::kWaves;
     __shared__ __attribute__((aligned(16))) char smem[PersistentTraits<PREC>::kSmem];
-    // the second stage buffer of the eight-wave form (a one-byte dummy otherwise)
-    __shared__ __attribute__((aligned(16))) char smem2[W == 8 ? PersistentTraits<PREC>::kSmem : 1];
+    // the second stage buffer of the split-BF16 form (a one-byte dummy otherwise)
+    __shared__ __attribute__((aligned(16))) char smem2[PREC == VV10_MIXED_BF16X3 ? PersistentTraits<PREC>::kSmem : 1];
     __shared__ int32_t next;
     for (;;) {
         if (threadIdx.x == 0) next = atomicAdd(counter, 1);
@@ -939,7 +869,7 @@ __global__ __launch_bounds__(512, 1) void k_contract_persistent_wide(
 #define VV10_CASE(c)                                                                         \
     case c:                                                                                  \
         tile_bf16x3<c, false, 8>(d.npad, d.jlen, d.Pp, p0, p1, xh, xl, y, it.itile, it.grp, \
-                                 it.split, smem, nullptr, smem2);                            \
+                                 it.split, smem, smem2);                                     \
         break;
             VV10_CASE(8) VV10_CASE(9) VV10_CASE(10) VV10_CASE(11) VV10_CASE(12)
 #undef VV10_CASE
@@ -1152,7 +1082,7 @@ __global__ __launch_bounds__(256, 2) void k_contract_bf16x3_w(
             wvh = bf16_apply_mask(wvh, kw);
             wvl = bf16_apply_mask(wvl, kw);
         }
-        const bf16x8 *xb = sX + buf * TOT + m * 4 + g;
+        const bf16x8 *xb = sX + buf * TOT + lane;
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) {
 #pragma unroll
@@ -1199,8 +1129,16 @@ hipError_t run_weighted(vv10_plan *p, const Workspace &ws, const WeightWork &ww)
 
 }  // namespace
 
+// The mixed modes' counts are fixed numbers (about what the kernels' registers
+// and LDS allow), not the runtime's: the split count that follows from them
+// decides where the FP32 runs end, so a result would otherwise change in its
+// last FP32 digits whenever a compiler allocates a register more.
 int contract_blocks_per_cu(vv10_precision prec, int ncb) {
-    return dispatch_ncb(ncb, [&](auto c) { return occupancy<decltype(c)::value>(prec); });
+    static constexpr int f32_slots[13] = {0, 8, 8, 8, 6, 5, 5, 4, 4, 3, 3, 3, 3};
+    if (ncb < 1 || ncb > max_ncb(prec)) return 0;
+    if (prec == VV10_MIXED_FP32) return f32_slots[ncb];
+    if (prec == VV10_MIXED_BF16X3) return ncb <= 4 ? 4 : (ncb < kWideMinNcb ? 3 : 2);
+    return dispatch_ncb(ncb, [](auto c) { return occupancy_f64<decltype(c)::value>(); });
 }
 
 hipError_t launch_contract(vv10_plan *p, const Workspace &ws, bool screen) {

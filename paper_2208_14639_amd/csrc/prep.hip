@@ -136,7 +136,10 @@ __global__ __launch_bounds__(256) void k_prep(
 //   L[i][0][x] = rho^x, L[i][1][x] = gamma^x  (FP64, for the assembly).
 // The channels are stored as the contraction of the plan's mode reads them:
 //   FP64 / FP32: X[i][c][x];
-//   BF16X3: hi = bf16(v), lo = bf16(v - hi), each as [i/16][x][2 (i mod 16) + c].
+//   BF16X3: hi = bf16(v), lo = bf16(v - hi), each as
+//     [i/16][x/16][(i mod 16)/4][x mod 16][2 (i mod 4) + c]: the 16 bytes of a
+//     lane's MFMA B operand are one unit, and the 64 lanes' units of a column
+//     block are consecutive, so that a wave's read of them from LDS is too.
 // The mixed modes store -3/2 p and -3/2 q: their contraction forms the pair
 // kernel divided by the -3/2 factor of Phi.
 // A 32 x 32 (point x perturbation) tile is staged through LDS so that the
@@ -197,11 +200,11 @@ __global__ __launch_bounds__(256) void k_pert_prep(
         L[(i * 2 + 1) * Pp + x] = gxv;
     }
     if constexpr (MODE == VV10_MIXED_BF16X3) {
-        // thread -> (16-point block hb, column xo, quarter qq): the four points
+        // thread -> (16-point block hb, quarter qq, column xo): the four points
         // i0 + 16 hb + 4 qq + e; their (p, q) hi and lo words are 16 B each,
-        // and four adjacent threads write one column's 64 B run of a block.
+        // and sixteen adjacent threads write one 256 B run of a block.
         __syncthreads();
-        const int qq = threadIdx.x & 3, xo = (threadIdx.x >> 2) & (TT - 1), hb = threadIdx.x >> 7;
+        const int xo = threadIdx.x & (TT - 1), qq = (threadIdx.x >> 5) & 3, hb = threadIdx.x >> 7;
         const int x = x0 + xo;
         const int io = 16 * hb + 4 * qq;
         if (x < Pp && i0 + io < npad) {
@@ -217,8 +220,8 @@ __global__ __launch_bounds__(256) void k_pert_prep(
                 lw[e] = (uint32_t)__builtin_bit_cast(uint16_t, pl) |
                         ((uint32_t)__builtin_bit_cast(uint16_t, ql) << 16);
             }
-            // element offset ((i / 16) Pp + x) 32 + 2 (i mod 16) of the first point, in 16 B units
-            const int64_t o = ((((i0 + io) / 16) * Pp + x) * 32 + 2 * ((i0 + io) % 16)) / 8;
+            // the 16 B unit of column x and points 4 qq .. 4 qq + 3 of its block
+            const int64_t o = (((i0 + io) / 16) * (Pp >> 4) + (x >> 4)) * 64 + qq * 16 + (x & 15);
             uint4 *Xh = static_cast<uint4 *>(Xv);
             uint4 *Xl = Xh + npad * 2 * Pp / 8;
             Xh[o] = (uint4){hw[0], hw[1], hw[2], hw[3]};

@@ -49,7 +49,7 @@ struct Workspace {
     int32_t gsplit = 1;          // point slices of the assembly GEMM
     int32_t bgroups = 1;         // atom groups of the grid-term kernel
     void *X = nullptr;           // (p, q) channels: FP64 or FP32 [npad][2][Pp];
-                                 // BF16X3: hi then lo, each [npad/16][Pp][32] bf16
+                                 // BF16X3: hi then lo, each [npad/16][Pp/16][4][16][8] bf16
     double *L = nullptr;         // [npad][2][Pp] (rho^x, gamma^x)
     void *Ypart = nullptr;       // [jsplit][npad][2][Pp] contraction partials (FP64; Y itself with one split)
     double *Y = nullptr;         // [npad][2][Pp] summed contraction, then R in place
@@ -80,7 +80,7 @@ struct GradWork {
 struct WeightWork {
     int32_t ncb = 0, groups = 0; // 16-column blocks per weight-contraction group, groups
     double *Wown = nullptr;      // [npad][3] owner-atom slot of w^x
-    void *Xv = nullptr;          // v = w^x rho: FP64/FP32 [npad][Pp]; BF16X3 hi, lo [npad/32][Pp][32]
+    void *Xv = nullptr;          // v = w^x rho: FP64/FP32 [npad][Pp]; BF16X3 hi, lo [npad/32][Pp/16][4][16][8]
     double *Lw = nullptr;        // [npad][Pp] w^x with the owner slot filled
     void *Ypart = nullptr;       // [jsplit][npad][3][Pp] (Y_pv, Y_qv, Y_vv) partials, FP64
     double *Ze = nullptr;        // [npad][Pp] E^{Bgr}_i (grid pass)

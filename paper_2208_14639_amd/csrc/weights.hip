@@ -56,10 +56,12 @@ __global__ __launch_bounds__(256) void k_wown(int64_t n, int32_t n_atom,
 
 // Lw[i][x] = w^x_i (owner slot from Wown, zero for padding) and the packed
 // channel v = sc w^x_i rho_i (sc = 1 in FP64, -3/2 in the mixed modes):
-// FP64/FP32 [npad][Pp]; BF16X3 hi then lo, each [npad/32][Pp][32] with the
-// point o of a 32-point block at K position 8 ((o mod 16)/4) + o mod 4 + 4 (o/16),
-// so that the 8 K values of lane group g are the points 4 g .. 4 g + 3 of
-// both 16-point halves (the pairs the main contraction's lanes form).
+// FP64/FP32 [npad][Pp]; BF16X3 hi then lo, each [npad/32][Pp/16][4][16][8]
+// (block, column block, lane group g, column, element e) with the point o of
+// a 32-point block at g = (o mod 16)/4, e = o mod 4 + 4 (o/16): the 8 K values
+// of lane group g are the points 4 g .. 4 g + 3 of both 16-point halves (the
+// pairs the main contraction's lanes form), and the 64 lanes' 16-byte units
+// of a column block are consecutive.
 constexpr int TT = 32;
 template <int MODE>
 __global__ __launch_bounds__(256) void k_wprep(int64_t n, int64_t npad, int32_t P, int32_t Pp,
@@ -95,7 +97,8 @@ __global__ __launch_bounds__(256) void k_wprep(int64_t n, int64_t npad, int32_t 
             __bf16 *Xh = static_cast<__bf16 *>(Xv);
             __bf16 *Xl = Xh + npad * Pp;
             const int oo = (int)(i % 32);
-            const int64_t o = ((i / 32) * Pp + x) * 32 + 8 * ((oo & 15) >> 2) + (oo & 3) + 4 * (oo >> 4);
+            const int64_t o = (((i / 32) * (Pp >> 4) + (x >> 4)) * 64 + 16 * ((oo & 15) >> 2) + (x & 15)) * 8 +
+                              (oo & 3) + 4 * (oo >> 4);
             const __bf16 h = (__bf16)(float)v;
             Xh[o] = h;
             Xl[o] = (__bf16)(float)(v - (double)(float)h);
@@ -333,7 +336,7 @@ __global__ __launch_bounds__(256, 2) void k_wcontract_bf16x3(int64_t npad, int64
     constexpr int PER = (UNITS + 255) / 256;
     typedef bf16x8 Buf[UNITS];
     __shared__ __attribute__((aligned(16))) char smem[smem_wbf16<NCB>()];
-    Buf *sH = reinterpret_cast<Buf *>(smem);            // [buffer][col][g]
+    Buf *sH = reinterpret_cast<Buf *>(smem);            // [buffer][cb][lane]
     Buf *sL = sH + 2;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int m = lane & 15, g = lane >> 4;
@@ -441,8 +444,8 @@ __global__ __launch_bounds__(256, 2) void k_wcontract_bf16x3(int64_t npad, int64
         if (more) load_x(j0 + 32);
         const WAops nxt = form_wA(a0, a1, n0, nk);
         load_pts(j0 + 64);
-        const bf16x8 *hp = sH[buf] + m * 4 + g;
-        const bf16x8 *lp = sL[buf] + m * 4 + g;
+        const bf16x8 *hp = sH[buf] + lane;
+        const bf16x8 *lp = sL[buf] + lane;
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) {
             const bf16x8 bh = hp[cb * 64], bl = lp[cb * 64];
