@@ -23,7 +23,8 @@
 // column group, with accumulators in registers.  Three arithmetic modes:
 //
 //  FP64:   one pair per lane per 16 x 4 block, four v_mfma_f64_16x16x4 per
-//          16 columns (K_pp X_p, K_pq X_q into Y_p; K_qp X_p, K_qq X_q into Y_q).
+//          16 columns (K_pp X_p, K_pq X_q into Y_p; K_qp X_p, K_qq X_q into Y_q),
+//          or four v_mfma_f64_4x4x4 per 4 columns past the last whole 16.
 //  FP32:   the same scheme with v_mfma_f32_16x16x4 and FP32 pair arithmetic.
 //  BF16X3: four pairs per lane per 16 x 16 block; the MFMA K index runs over
 //          (j, channel), k = 2 (j mod 16) + c, so one v_mfma_f32_16x16x32_bf16
@@ -32,14 +33,14 @@
 //          lo = bf16(v - hi), and three products hi*hi + hi*lo + lo*hi are
 //          accumulated (relative error about 2^-16 per product).
 //
-// The mixed modes carry the factor -3/2 of Phi in X (the perturbation
-// packing scales both channels), so their pair arithmetic forms K / (-3/2)
-// with r = 1 / (g g' s) in place of Phi.  Using 1/(g g') = s r and
+// X carries the factor -3/2 of Phi (the perturbation packing scales both
+// channels), so the pair arithmetic forms K / (-3/2) with r = 1 / (g g' s) in
+// place of Phi.  Using 1/(g g') = s r and
 // 1/s = g g' r, each pair needs one reciprocal and
 //   A = r (1/g + 1/s),  A' = r (1/g' + 1/s),  Q = 2 r (1/s^2 + 1/(g g')),
 //   t1 = c_i Q - A',  t2 = c_j Q - A,
 //   K_pp = r - c_i A + c_j t1,  K_pq = R^2 t1,  K_qp = R^2 t2,  K_qq = R^4 Q.
-// They accumulate at most kFp32Run consecutive j points in FP32 (the MFMA
+// The mixed modes accumulate at most kFp32Run consecutive j points in FP32 (the MFMA
 // accumulators) and then add those sums into the split's FP64 partials; the
 // assembly sums the partials over splits in FP64.  So the sums are FP32
 // within a tile of kFp32Run points and FP64 across tiles and splits.
@@ -58,32 +59,72 @@ constexpr int kJC = 32;   // j points per LDS stage
 template <int NCB>
 constexpr int smem_f64() { return 2 * kJC * (int)sizeof(double4) + kJC * 2 * NCB * 16 * (int)sizeof(double); }
 
-template <int NCB, bool SCR = false>
+// The four kernel-derivative values of pair (i, j), divided by -3/2 (see the
+// file header); a = (x, y, z, omega), (kappa, ., c, .) of each point.
+__device__ __forceinline__ void pair_K64(const double4 a0, const double4 a1, const double4 b0,
+                                         double bk, double cj, double &kpp, double &kpq,
+                                         double &kqp, double &kqq) {
+    const double dx = a0.x - b0.x, dy = a0.y - b0.y, dz = a0.z - b0.z;
+    const double R2 = __builtin_fma(dx, dx, __builtin_fma(dy, dy, dz * dz));
+    const double gg = __builtin_fma(a0.w, R2, a1.x);
+    const double gp = __builtin_fma(b0.w, R2, bk);
+    const double s = gg + gp, t = gg * gp;
+    const double r = rcp64(t * s);
+    const double sr = s * r, is = t * r;                // 1/(g g'), 1/s
+    const double A = r * __builtin_fma(gp, sr, is);     // r (1/g + 1/s)
+    const double Ap = r * __builtin_fma(gg, sr, is);    // r (1/g' + 1/s)
+    const double Q = (r + r) * __builtin_fma(is, is, sr);
+    const double ci = a1.z;
+    const double t1 = __builtin_fma(ci, Q, -Ap);
+    const double t2 = __builtin_fma(cj, Q, -A);
+    kpp = __builtin_fma(cj, t1, __builtin_fma(-ci, A, r));
+    kpq = R2 * t1;
+    kqp = R2 * t2;
+    kqq = (R2 * R2) * Q;
+}
+
+// FP64 MFMA and FP64 VALU share their multipliers: measured, a 16x16x4 MFMA
+// takes 64 cycles of a SIMD, an FMA 4.75, v_rcp_f64 16.5, and none of them
+// overlap, so the kernel's time is the sum of both and each instruction of
+// the pair arithmetic counts (about 165 cycles per wave and 64 pairs).  The
+// columns past a multiple of 16 go by fours on v_mfma_f64_4x4x4 (four blocks:
+// 16 rows, 4 columns, 17.3 cycles; the same A operand, and measured bitwise
+// the same products as 16x16x4): P = 54 takes 227 cycles per A operand
+// instead of 256, P = 18 81 instead of 128 (contraction of the hexamer
+// 6.27 -> 5.89 ms, 14.8 -> 13.1 M cycles per XCD; of the dimer 0.119 -> 0.091
+// ms).  NQ is a template parameter: tested in the loop, it made the compiler
+// copy accumulators behind MFMA waits and cost all of the gain.
+// NQ: quads of columns in the last block, 4 (the 16-column form) or fewer.
+template <int NCB, bool SCR = false, int NQ = 4>
 __device__ __forceinline__ void tile_f64(int64_t npad, int64_t jlen, int32_t Pp,
                                          const double4 *__restrict__ P0,
                                          const double4 *__restrict__ P1,
                                          const double *__restrict__ X, double *__restrict__ Yout,
                                          int64_t itile, int grp, int split, char *smem,
                                          const uint32_t *__restrict__ mask = nullptr) {
-    constexpr int NC = NCB * 16;
+    constexpr int NC = NCB * 16, LB = NCB - 1;
     double4 *sA = reinterpret_cast<double4 *>(smem);
     double4 *sB = sA + kJC;
     double *sX = reinterpret_cast<double *>(sB + kJC);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int m = lane & 15, kq = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m = lane & 15, kq = lane >> 4, mq = lane & 3;
     const int64_t ibase = itile * 64 + wave * 16;
     const int col0 = grp * NC;
     const int64_t jbeg = (int64_t)split * jlen;
     const int64_t jend = min(npad, jbeg + jlen);
     constexpr int kJJUnroll = SCR ? 1 : 2;   // screened: fewer live registers
     const double4 a0 = P0[ibase + m], a1 = P1[ibase + m];
-    const double ci = a1.z;
-    v4d accp[NCB], accq[NCB];
+    constexpr int NB = NQ == 4 ? NCB : LB, NT = NQ == 4 ? 0 : NQ;   // blocks, quads
+    v4d accp[NB > 0 ? NB : 1], accq[NB > 0 ? NB : 1];
+    double tp[NT > 0 ? NT : 1], tq[NT > 0 ? NT : 1];
 #pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) {
+    for (int cb = 0; cb < NB; ++cb) {
         accp[cb] = (v4d){0.0, 0.0, 0.0, 0.0};
         accq[cb] = (v4d){0.0, 0.0, 0.0, 0.0};
     }
+#pragma unroll
+    for (int t = 0; t < NT; ++t) tp[t] = tq[t] = 0.0;
     for (int64_t j0 = jbeg; j0 < jend; j0 += kJC) {
         __syncthreads();
         if (tid < kJC) {
@@ -104,53 +145,56 @@ __device__ __forceinline__ void tile_f64(int64_t npad, int64_t jlen, int32_t Pp,
 #pragma unroll kJJUnroll
         for (int jj = 0; jj < kJC; jj += 4) {
             const int jl = jj + kq;
-            const double4 b0 = sA[jl], b1 = sB[jl];
-            const double dx = a0.x - b0.x, dy = a0.y - b0.y, dz = a0.z - b0.z;
-            const double R2 = __builtin_fma(dx, dx, __builtin_fma(dy, dy, dz * dz));
-            const double g = __builtin_fma(a0.w, R2, a1.x);
-            const double gp = __builtin_fma(b0.w, R2, b1.x);
-            const double s = g + gp, t = g * gp;
-            const double r = rcp64(t * s);
-            const double phi = -1.5 * r;
-            const double ig = gp * s * r, igp = g * s * r, is = t * r;
-            const double Pg = -phi * (ig + is);
-            const double Pgp = -phi * (igp + is);
-            const double Pgg = 2.0 * phi * __builtin_fma(ig, igp, is * is);
-            const double cj = b1.z;
-            const double kpp0 = phi + ci * Pg + cj * __builtin_fma(ci, Pgg, Pgp);
-            const double kpp = jj == dself ? 0.0 : kpp0;
-            const double kpq = R2 * __builtin_fma(ci, Pgg, Pgp);
-            const double kqp = R2 * __builtin_fma(cj, Pgg, Pg);
-            const double kqq = R2 * R2 * Pgg;
-            const double *xr = sX + (jl * 2) * NC + m;
+            double kpp, kpq, kqp, kqq;
+            pair_K64(a0, a1, sA[jl], sB[jl].x, sB[jl].z, kpp, kpq, kqp, kqq);
+            kpp = jj == dself ? 0.0 : kpp;
+            const double *xr = sX + (jl * 2) * NC;
             const uint32_t mw = SCR ? mask[((j0 + jj) >> 4) * ((Pp >> 4) / NCB) + grp] : 0u;
 #pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) {
+            for (int cb = 0; cb < NB; ++cb) {
                 if (SCR && !((mw >> cb) & 1u)) continue;
-                const double xp = xr[cb * 16];
+                const double xp = xr[cb * 16 + m], xq = xr[NC + cb * 16 + m];
                 accp[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(kpp, xp, accp[cb], 0, 0, 0);
                 accq[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(kqp, xp, accq[cb], 0, 0, 0);
-            }
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) {
-                if (SCR && !((mw >> cb) & 1u)) continue;
-                const double xq = xr[NC + cb * 16];
                 accp[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(kpq, xq, accp[cb], 0, 0, 0);
                 accq[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(kqq, xq, accq[cb], 0, 0, 0);
             }
+            if (SCR && NT && !((mw >> LB) & 1u)) continue;
+            double xp[NT > 0 ? NT : 1], xq[NT > 0 ? NT : 1];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                xp[t] = xr[LB * 16 + 4 * t + mq];
+                xq[t] = xr[NC + LB * 16 + 4 * t + mq];
+            }
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                tp[t] = __builtin_amdgcn_mfma_f64_4x4x4f64(kpp, xp[t], tp[t], 0, 0, 0);
+                tq[t] = __builtin_amdgcn_mfma_f64_4x4x4f64(kqp, xp[t], tq[t], 0, 0, 0);
+            }
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                tp[t] = __builtin_amdgcn_mfma_f64_4x4x4f64(kpq, xq[t], tp[t], 0, 0, 0);
+                tq[t] = __builtin_amdgcn_mfma_f64_4x4x4f64(kqq, xq[t], tq[t], 0, 0, 0);
+            }
         }
     }
-    // D layout of v_mfma_f64_16x16x4 (measured on gfx950): item r of lane l
-    // holds row 4 r + l/16, column l%16
+    // D layouts (measured on gfx950): 16x16x4, item r of lane l holds row
+    // 4 r + l/16, column l%16; 4x4x4, lane l holds row 4 ((l/4)%4) + l/16, column l%4
     double *Yb = Yout + (int64_t)split * npad * 2 * Pp;
 #pragma unroll
-    for (int cb = 0; cb < NCB; ++cb)
+    for (int cb = 0; cb < NB; ++cb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int64_t row = ibase + 4 * r + kq;
             Yb[(row * 2 + 0) * Pp + col0 + cb * 16 + m] = accp[cb][r];
             Yb[(row * 2 + 1) * Pp + col0 + cb * 16 + m] = accq[cb][r];
         }
+    const int64_t rowq = ibase + 4 * ((lane >> 2) & 3) + kq;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        Yb[(rowq * 2 + 0) * Pp + col0 + LB * 16 + 4 * t + mq] = tp[t];
+        Yb[(rowq * 2 + 1) * Pp + col0 + LB * 16 + 4 * t + mq] = tq[t];
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -609,7 +653,8 @@ __device__ __forceinline__ void tile_bf16x3(int64_t npad, int64_t jlen, int32_t 
 // One workgroup per (i tile, column group, j split): blockIdx = (tile, group, split).
 // SCR: skip the (16-point, 16-column) blocks that the screening mask marks
 // inactive (the MFMA work only; the kernel tile is still formed).
-template <int NCB, bool SCR>
+// FP64: the last group's last block holds NQ quads of columns (4: all 16).
+template <int NCB, bool SCR, int NQ>
 __global__ __launch_bounds__(256, 2) void k_contract_f64(int64_t npad, int64_t jlen, int32_t Pp,
                                                          const double4 *__restrict__ P0,
                                                          const double4 *__restrict__ P1,
@@ -617,8 +662,12 @@ __global__ __launch_bounds__(256, 2) void k_contract_f64(int64_t npad, int64_t j
                                                          double *__restrict__ Yout,
                                                          const uint32_t *__restrict__ mask) {
     __shared__ __attribute__((aligned(16))) char smem[smem_f64<NCB>()];
-    tile_f64<NCB, SCR>(npad, jlen, Pp, P0, P1, X, Yout, blockIdx.x, blockIdx.y, blockIdx.z, smem,
-                       mask);
+    if (NQ == 4 || blockIdx.y + 1 == gridDim.y)
+        tile_f64<NCB, SCR, NQ>(npad, jlen, Pp, P0, P1, X, Yout, blockIdx.x, blockIdx.y, blockIdx.z,
+                               smem, mask);
+    else
+        tile_f64<NCB, SCR>(npad, jlen, Pp, P0, P1, X, Yout, blockIdx.x, blockIdx.y, blockIdx.z,
+                           smem, mask);
 }
 
 template <int NCB, bool SCR>
@@ -661,12 +710,23 @@ hipError_t run_mode(vv10_plan *p, const Workspace &ws) {
     dim3 grid((unsigned)(p->npad / 64), (unsigned)ws.ngroups, (unsigned)ws.jsplit);
     const uint32_t *mask = SCR ? ws.mask : nullptr;
     if (p->prec == VV10_FP64) {
-        if constexpr (NCB <= 8)
-            k_contract_f64<NCB, SCR><<<grid, 256, 0, p->stream>>>(
-                p->npad, ws.jlen, ws.Pp, p->P0, p->P1, static_cast<const double *>(ws.X),
-                static_cast<double *>(ws.Ypart), mask);
-        else
+        if constexpr (NCB <= 8) {
+            // quads of columns in the last block (a block past the columns,
+            // which uneven groups leave, takes the 16-column form on zeros)
+            const int left = ws.P - (ws.Pp - 16);
+            const int nq = left > 0 ? (left + 3) / 4 : 4;
+            auto go = [&](auto q) {
+                k_contract_f64<NCB, SCR, decltype(q)::value><<<grid, 256, 0, p->stream>>>(
+                    p->npad, ws.jlen, ws.Pp, p->P0, p->P1, static_cast<const double *>(ws.X),
+                    static_cast<double *>(ws.Ypart), mask);
+            };
+            if (nq == 1) go(std::integral_constant<int, 1>{});
+            else if (nq == 2) go(std::integral_constant<int, 2>{});
+            else if (nq == 3) go(std::integral_constant<int, 3>{});
+            else go(std::integral_constant<int, 4>{});
+        } else {
             return hipErrorInvalidValue;
+        }
     } else if (p->prec == VV10_MIXED_FP32) {
         k_contract_f32<NCB, SCR><<<grid, 256, 0, p->stream>>>(
             p->npad, ws.jlen, ws.Pp, p->P0f, p->P1f, static_cast<const float *>(ws.X),
@@ -691,7 +751,7 @@ template <int NCB>
 int occupancy_f64() {
     int nb = 0;
     if constexpr (NCB <= 8) {
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_contract_f64<NCB, false>, 256, 0) !=
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_contract_f64<NCB, false, 4>, 256, 0) !=
             hipSuccess) {
             (void)hipGetLastError();
             return 0;

@@ -8,15 +8,14 @@ namespace vv10 {
 typedef double v4d __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-// 1/x in FP64: hardware estimate refined by two Newton steps
-// (each step squares the relative error).  Used only for x > 0 and finite.
+// 1/x in FP64: the hardware estimate r0 (relative error at most 2^-24.3,
+// measured over 35 decades) refined by one third-order step,
+// r0 (1 + e + e^2) with e = 1 - x r0, whose error e^3 lies far below an ulp
+// (one FMA fewer than two Newton steps).  Used only for x > 0 and finite.
 __device__ __forceinline__ double rcp64(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    double e = __builtin_fma(-x, r, 1.0);
-    r = __builtin_fma(r, e, r);
-    e = __builtin_fma(-x, r, 1.0);
-    r = __builtin_fma(r, e, r);
-    return r;
+    const double r = __builtin_amdgcn_rcp(x);
+    const double e = __builtin_fma(-x, r, 1.0);
+    return __builtin_fma(r, __builtin_fma(e, e, e), r);
 }
 
 // Barrier for the compiler only: the memory accesses before it are issued

@@ -140,8 +140,8 @@ __global__ __launch_bounds__(256) void k_prep(
 //     [i/16][x/16][(i mod 16)/4][x mod 16][2 (i mod 4) + c]: the 16 bytes of a
 //     lane's MFMA B operand are one unit, and the 64 lanes' units of a column
 //     block are consecutive, so that a wave's read of them from LDS is too.
-// The mixed modes store -3/2 p and -3/2 q: their contraction forms the pair
-// kernel divided by the -3/2 factor of Phi.
+// Every mode stores -3/2 p and -3/2 q: the contraction forms the pair kernel
+// divided by the -3/2 factor of Phi.
 // A 32 x 32 (point x perturbation) tile is staged through LDS so that the
 // [P][N] reads are coalesced.  With bmax (screening), also
 //   bmax[i/16][x] = max over the 16-point block of max(|p|, |q|).
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(256) void k_pert_prep(
         if (i >= npad || x >= Pp) continue;
         const double rx = sr[tx][ty + k], gxv = sg[tx][ty + k];
         const double wi = F[F_W * npad + i], r = F[F_RHO * npad + i];
-        const double sc = MODE == VV10_FP64 ? 1.0 : -1.5;
+        const double sc = -1.5;
         const double p = sc * wi * rx;
         const double qv = sc * wi * r * (F[F_OMR * npad + i] * rx + F[F_OMG * npad + i] * gxv);
         mblk[k / 16] = fmaxf(mblk[k / 16], (float)fmax(fabs(p), fabs(qv)));
