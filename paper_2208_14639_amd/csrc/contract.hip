@@ -837,8 +837,8 @@ __device__ __forceinline__ void run_item(const BatchMol &d, const BatchItem &it,
     }
 }
 
-// Grid items of a batch: one wave per workgroup pulls one grid tile of one
-// molecule and atom group at a time (with the pair integrals, as the Hessian
+// Grid items of a batch: a workgroup pulls one grid tile of one molecule and
+// atom group at a time (with the pair integrals, as the Hessian
 // call forms them).  A kernel of its own keeps the grid pass's register
 // allocation (and the standalone grid kernel's waves per SIMD), where the
 // contraction kernels' allocations would hold it to two waves per SIMD.  At
@@ -846,25 +846,26 @@ __device__ __forceinline__ void run_item(const BatchMol &d, const BatchItem &it,
 // spills measured slower on the 64-cluster batch (2625-2628 ms per launch
 // against 2614-2619).
 template <int PREC>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PREC == VV10_FP64 ? 3 : 4))) void k_grid_persistent(
+__global__ __launch_bounds__(64 * kGridWaves) __attribute__((amdgpu_waves_per_eu(PREC == VV10_FP64 ? 3 : 4))) void k_grid_persistent(
     const BatchMol *__restrict__ mols, const BatchItem *__restrict__ items, int32_t n_items,
     int32_t *__restrict__ counter) {
     using T = std::conditional_t<PREC == VV10_FP64, double, float>;
     using T4 = std::conditional_t<PREC == VV10_FP64, double4, float4>;
-    __shared__ T4 sA[kGridTile], sB[kGridTile];
-    const int lane = threadIdx.x;
+    __shared__ GridLds<T4> lds;
+    __shared__ int32_t next;
     for (;;) {
-        int32_t k = 0;
-        if (lane == 0) k = atomicAdd(counter, 1);
-        k = __builtin_amdgcn_readfirstlane(k);   // lane 0's value, uniform
-        if (k >= n_items) break;                  // every wave leaves once the list is drained
+        if (threadIdx.x == 0) next = atomicAdd(counter, 1);
+        __syncthreads();
+        const int32_t k = __builtin_amdgcn_readfirstlane(next);   // uniform: item data in SGPRs
+        __syncthreads();
+        if (k >= n_items) break;          // every workgroup leaves once the list is drained
         const BatchItem it = items[k];
         const BatchMol d = mols[it.mol];
         // grid_unit orders its LDS writes after the previous reads itself
         grid_unit<T, T4, true, false>(d.n_atom, d.Pp, d.bgroups, d.npad, d.seg, d.tile_i0,
                                       d.tile_n, d.tile_atom, static_cast<const T4 *>(d.P0),
                                       static_cast<const T4 *>(d.P1), d.Pd, d.Z, nullptr, d.Dpart,
-                                      d.Igrp, it.itile, it.grp, lane, sA, sB);
+                                      d.Igrp, it.itile, it.grp, lds);
     }
 }
 
@@ -1268,11 +1269,11 @@ int persistent_grid_blocks_per_cu(vv10_precision prec) {
     int nb = 0;
     hipError_t e;
     if (prec == VV10_FP64)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_grid_persistent<VV10_FP64>, 64, 0);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_grid_persistent<VV10_FP64>, 64 * kGridWaves, 0);
     else if (prec == VV10_MIXED_FP32)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_grid_persistent<VV10_MIXED_FP32>, 64, 0);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_grid_persistent<VV10_MIXED_FP32>, 64 * kGridWaves, 0);
     else
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_grid_persistent<VV10_MIXED_BF16X3>, 64, 0);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_grid_persistent<VV10_MIXED_BF16X3>, 64 * kGridWaves, 0);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return 0;
@@ -1284,11 +1285,11 @@ hipError_t launch_grid_persistent(vv10_precision prec, const BatchMol *mols,
                                   int n_blocks, hipStream_t stream) {
     k_zero_counter<<<1, 1, 0, stream>>>(counter);
     if (prec == VV10_FP64)
-        k_grid_persistent<VV10_FP64><<<n_blocks, 64, 0, stream>>>(mols, items, n_items, counter);
+        k_grid_persistent<VV10_FP64><<<n_blocks, 64 * kGridWaves, 0, stream>>>(mols, items, n_items, counter);
     else if (prec == VV10_MIXED_FP32)
-        k_grid_persistent<VV10_MIXED_FP32><<<n_blocks, 64, 0, stream>>>(mols, items, n_items, counter);
+        k_grid_persistent<VV10_MIXED_FP32><<<n_blocks, 64 * kGridWaves, 0, stream>>>(mols, items, n_items, counter);
     else
-        k_grid_persistent<VV10_MIXED_BF16X3><<<n_blocks, 64, 0, stream>>>(mols, items, n_items, counter);
+        k_grid_persistent<VV10_MIXED_BF16X3><<<n_blocks, 64 * kGridWaves, 0, stream>>>(mols, items, n_items, counter);
     return hipGetLastError();
 }
 hipError_t launch_contract_persistent(vv10_precision prec, const BatchMol *mols,

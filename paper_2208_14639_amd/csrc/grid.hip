@@ -6,18 +6,17 @@ namespace vv10 {
 
 namespace {
 
-// The grid pass as one wave per (tile, atom group): blockIdx = (tile, group).
+// The grid pass as one workgroup per (tile, atom group): blockIdx = (tile, group).
 template <typename T, typename T4, bool INTS, bool ZE>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1))) void k_grid(
+__global__ __launch_bounds__(64 * kGridWaves) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1))) void k_grid(
     int32_t n_atom, int32_t Pp, int32_t bgroups, int64_t npad, const int64_t *__restrict__ seg,
     const int32_t *__restrict__ tile_i0, const int32_t *__restrict__ tile_n,
     const int32_t *__restrict__ tile_atom, const T4 *__restrict__ P0,
     const T4 *__restrict__ P1, const double4 *__restrict__ Pd, double *__restrict__ Z,
     double *__restrict__ Ze, double *__restrict__ Dpart, double *__restrict__ Ipart) {
-    __shared__ T4 sA[TG], sB[TG];
+    __shared__ GridLds<T4> lds;
     grid_unit<T, T4, INTS, ZE>(n_atom, Pp, bgroups, npad, seg, tile_i0, tile_n, tile_atom, P0, P1,
-                               Pd, Z, Ze, Dpart, Ipart, blockIdx.x, blockIdx.y, threadIdx.x, sA,
-                               sB);
+                               Pd, Z, Ze, Dpart, Ipart, blockIdx.x, blockIdx.y, lds);
 }
 
 // I[k][i] = sum over atom groups of Ipart[grp][k][i] (group order),
@@ -144,11 +143,11 @@ void grid_terms_launch(vv10_plan *p, double *Ze) {
     const Workspace &ws = p->ws;
     dim3 grid((unsigned)p->ntiles, (unsigned)ws.bgroups);
     if (p->prec == VV10_FP64)
-        k_grid<double, double4, INTS, ZE><<<grid, TG, 0, p->stream>>>(
+        k_grid<double, double4, INTS, ZE><<<grid, 64 * kGridWaves, 0, p->stream>>>(
             p->n_atom, ws.Pp, ws.bgroups, p->npad, p->d_seg, p->d_tile_i0, p->d_tile_n,
             p->d_tile_atom, p->P0, p->P1, p->P1, ws.Z, Ze, ws.Dpart, ws.Igrp);
     else
-        k_grid<float, float4, INTS, ZE><<<grid, TG, 0, p->stream>>>(
+        k_grid<float, float4, INTS, ZE><<<grid, 64 * kGridWaves, 0, p->stream>>>(
             p->n_atom, ws.Pp, ws.bgroups, p->npad, p->d_seg, p->d_tile_i0, p->d_tile_n,
             p->d_tile_atom, p->P0f, p->P1f, p->P1, ws.Z, Ze, ws.Dpart, ws.Igrp);
 }

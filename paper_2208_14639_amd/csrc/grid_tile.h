@@ -30,7 +30,15 @@
 // pair j = i is left out of the loops and added in FP64 (from the FP64
 // point data Pd) by the workgroup whose atom group holds the own atom.
 //
-// One wave per (tile of 64 outer points, group of atoms B); tiles never
+// One workgroup of kGridWaves waves per (tile of 64 outer points, group of
+// atoms B); every wave holds the tile's points, one per lane, and takes every
+// kGridWaves-th 64-point chunk of each atom B; the waves' FP64 sums are added
+// in wave order through LDS at the end of an atom.  (One wave per tile and
+// group left the last round of waves half empty, 7776 waves of 24 chunks each
+// on the hexamer and 396 on the dimer for 1024 SIMDs: grid pass of the hexamer
+// 0.93 -> 0.77 ms in FP32 and 1.59 -> 1.44 in FP64, of the dimer in FP64 0.128
+// -> 0.072, of the 20-mer in FP32, bound by VALU issue, 16.5 -> 16.0.  Eight
+// waves: 0.78, 1.66, 0.065 and 16.4 ms; six: slower everywhere.)  Tiles never
 // straddle atoms, so the D sums are plain wave reductions in a fixed order.
 // FP64 mode evaluates and accumulates in FP64; the mixed modes evaluate each
 // pair in FP32, accumulate one 64-point chunk in FP32 and add the chunk sums
@@ -143,13 +151,31 @@ __device__ __forceinline__ void grid_chunk(const T4 a0, const T4 a1, const T4 *s
 // to the wave): the writes complete before any lane reads, and no lane
 // overwrites a chunk before every lane has read it.
 __device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// One (tile t, atom group grp) unit of the grid pass, run by one wave (lane
-// = its lane) on its own LDS chunk buffers sA, sB of TG points each.
+constexpr int kGridWaves = 4;
+constexpr int kGridRed = 9;   // sums of a wave held in LDS at once
+
+// LDS of one workgroup of the grid pass.
+template <typename T4>
+struct GridLds {
+    T4 a[kGridWaves][TG], b[kGridWaves][TG];   // each wave's chunk
+    double red[kGridWaves][kGridRed][TG];      // the waves' sums
+};
+
+// Sum k of the waves, in wave order.
+__device__ __forceinline__ double waves_sum(const double (*red)[kGridRed][TG], int k, int lane) {
+    double v = red[0][k][lane];
+#pragma unroll
+    for (int w = 1; w < kGridWaves; ++w) v += red[w][k][lane];
+    return v;
+}
+
+// One (tile t, atom group grp) unit of the grid pass, run by a workgroup of
+// kGridWaves waves.
 // Fused with the pair integrals of the Hessian call (INTS): the group of
 // atoms B of a workgroup also covers the outer point's own atom for
 // E, U, W, A, B, C, whose per-group partial sums go to Ipart[group][6][npad].
@@ -173,7 +199,10 @@ __device__ __forceinline__ void grid_unit(
     const int32_t *__restrict__ tile_atom, const T4 *__restrict__ P0,
     const T4 *__restrict__ P1, const double4 *__restrict__ Pd, double *__restrict__ Z,
     double *__restrict__ Ze, double *__restrict__ Dpart, double *__restrict__ Ipart, int t,
-    int grp, int lane, T4 *__restrict__ sA, T4 *__restrict__ sB) {
+    int grp, GridLds<T4> &lds) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    T4 *sA = lds.a[wave], *sB = lds.b[wave];
     const int A = tile_atom[t];
     const int nt = tile_n[t];
     const bool live = lane < nt;
@@ -186,7 +215,7 @@ __device__ __forceinline__ void grid_unit(
         const int64_t jb = seg[B], je = seg[B + 1];
         const bool dsum = B > A;
         double acc[16] = {};
-        for (int64_t j0 = jb; j0 < je; j0 += TG) {
+        for (int64_t j0 = jb + TG * wave; j0 < je; j0 += TG * kGridWaves) {
             wave_lds_sync();
             const int64_t j = j0 + lane;
             sA[lane] = P0[j < je ? j : jb];
@@ -225,54 +254,62 @@ __device__ __forceinline__ void grid_unit(
         if (B == A) continue;
         // B > A: E^{Bgr} = 3 acc[0..2], U^{Bgr} = -3 acc[3..5]; B < A:
         // E^{Bgr} + c_i U^{Bgr} = 3 acc[0..2] (and E^{Bgr} = 3 acc[3..5] with
-        // Ze); W^{Bgr} = -3 acc[6..8]
-        if (live) {
-            double *z0 = Z + (i * 2 + 0) * Pp + 3 * B;
-            double *z1 = Z + (i * 2 + 1) * Pp + 3 * B;
-            z0[0] = 3.0 * (dsum ? acc[0] - ci * acc[3] : acc[0]);
-            z0[1] = 3.0 * (dsum ? acc[1] - ci * acc[4] : acc[1]);
-            z0[2] = 3.0 * (dsum ? acc[2] - ci * acc[5] : acc[2]);
-            z1[0] = -3.0 * acc[6];
-            z1[1] = -3.0 * acc[7];
-            z1[2] = -3.0 * acc[8];
-            if (ZE) {
-                double *ze = Ze + i * Pp + 3 * B;
-                ze[0] = 3.0 * (dsum ? acc[0] : acc[3]);
-                ze[1] = 3.0 * (dsum ? acc[1] : acc[4]);
-                ze[2] = 3.0 * (dsum ? acc[2] : acc[5]);
-            }
-        }
-        const double di = -3.0 * acc[15];
-        const double red[9] = {ai * (6.0 * acc[9] + di), ai * (6.0 * acc[10] + di),
-                               ai * (6.0 * acc[11] + di), ai * 6.0 * acc[12],
-                               ai * 6.0 * acc[13], ai * 6.0 * acc[14],
-                               ai * 3.0 * acc[0], ai * 3.0 * acc[1], ai * 3.0 * acc[2]};
-        double *dp = Dpart + ((int64_t)t * n_atom + B) * 9;
+        // Ze); W^{Bgr} = -3 acc[6..8].  Wave x < 3 takes axis x, and two of
+        // the six D sums.
+        __syncthreads();   // the previous sums have been read
 #pragma unroll
-        for (int k = 0; k < 9; ++k) {
-            if (!dsum) {   // B < A: the assembly reads both parts from the (B, A) sums
-                if (lane == 0) dp[k] = 0.0;
-                continue;
+        for (int k = 0; k < 9; ++k) lds.red[wave][k][lane] = acc[k];
+        __syncthreads();
+        double *dp = Dpart + ((int64_t)t * n_atom + B) * 9;
+        if (wave < 3) {
+            const double s0 = waves_sum(lds.red, wave, lane);
+            const double s3 = waves_sum(lds.red, 3 + wave, lane);
+            const double s6 = waves_sum(lds.red, 6 + wave, lane);
+            if (live) {
+                Z[(i * 2 + 0) * Pp + 3 * B + wave] = 3.0 * (dsum ? s0 - ci * s3 : s0);
+                Z[(i * 2 + 1) * Pp + 3 * B + wave] = -3.0 * s6;
+                if (ZE) Ze[i * Pp + 3 * B + wave] = 3.0 * (dsum ? s0 : s3);
             }
-            const double tot = wave_sum(red[k]);
-            if (lane == 0) dp[k] = tot;
+            // B < A: the assembly reads both parts from the (B, A) sums
+            const double tot = dsum ? wave_sum(ai * 3.0 * s0) : 0.0;
+            if (lane == 0) dp[6 + wave] = tot;
+        }
+        if (!dsum) {
+            if (wave == 3 && lane < 6) dp[lane] = 0.0;
+            continue;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 7; ++k) lds.red[wave][k][lane] = acc[9 + k];
+        __syncthreads();
+        if (wave < 3) {
+            const double di = -3.0 * waves_sum(lds.red, 6, lane);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int k = 2 * wave + q;   // xx, yy, zz, xy, xz, yz
+                const double v = 6.0 * waves_sum(lds.red, k, lane) + (k < 3 ? di : 0.0);
+                const double tot = wave_sum(ai * v);
+                if (lane == 0) dp[k] = tot;
+            }
         }
     }
-    if (INTS && live) {
-        // the group that holds the own atom adds the self pair in FP64:
-        // E += a Phi, U += -a Phi h, A += 2 a Phi m (W, B, C get none)
-        double self[6] = {0, 0, 0, 0, 0, 0};
-        if (A % bgroups == grp) {
-            const double4 pd = Pd[i];
-            const SelfPair q = self_pair(pd.x);
-            self[0] = pd.y * q.phi;
-            self[1] = -pd.y * q.phi * q.h;
-            self[3] = 2.0 * pd.y * q.phi * q.m;
-        }
-        const double sc[6] = {-1.5, 1.5, 1.5, -3.0, -3.0, -3.0};
+    if (INTS) {
+        __syncthreads();
 #pragma unroll
-        for (int k = 0; k < 6; ++k)
-            Ipart[((int64_t)grp * NI + k) * npad + i] = sc[k] * pint[k] + self[k];
+        for (int k = 0; k < 6; ++k) lds.red[wave][k][lane] = pint[k];
+        __syncthreads();
+        if (live)
+            for (int k = wave; k < 6; k += kGridWaves) {
+                double v = (k == 0 ? -1.5 : (k < 3 ? 1.5 : -3.0)) * waves_sum(lds.red, k, lane);
+                // the group that holds the own atom adds the self pair in FP64:
+                // E += a Phi, U += -a Phi h, A += 2 a Phi m (W, B, C get none)
+                if (A % bgroups == grp && (k == 0 || k == 1 || k == 3)) {
+                    const double4 pd = Pd[i];
+                    const SelfPair q = self_pair(pd.x);
+                    v += pd.y * q.phi * (k == 0 ? 1.0 : (k == 1 ? -q.h : 2.0 * q.m));
+                }
+                Ipart[((int64_t)grp * NI + k) * npad + i] = v;
+            }
     }
 }
 

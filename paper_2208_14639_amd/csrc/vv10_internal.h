@@ -191,7 +191,7 @@ hipError_t launch_contract_persistent(vv10_precision prec, const BatchMol *mols,
 // (i tiles of 128 points), the standalone kernel's form for these counts.
 constexpr int kWideMinNcb = 8;
 // The grid items (one grid tile of one molecule and atom group each) run in
-// a persistent kernel of their own, one wave per workgroup.
+// a persistent kernel of their own.
 int persistent_grid_blocks_per_cu(vv10_precision prec);
 hipError_t launch_grid_persistent(vv10_precision prec, const BatchMol *mols,
                                   const BatchItem *items, int32_t n_items, int32_t *counter,
