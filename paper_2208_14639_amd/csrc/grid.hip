@@ -40,17 +40,20 @@ __global__ __launch_bounds__(256) void k_sum_groups(int64_t n, int64_t npad, int
 // from which the grid part of the gradient follows,
 // E_gr = -sum_{B != A} sum_{i in A} a_i E^{Bgr}_i (translational invariance),
 // the B < A terms being minus the (B, A) ones.
-// The layout and the scaled sums are those of k_grid: E^{Bgr}_i = 3 sum_j p T d.
+// The layout (four waves a unit; grid sums of the hexamer 0.27 -> 0.21 ms in
+// FP32) and the scaled sums are those of k_grid: E^{Bgr}_i = 3 sum_j p T d.
 // Without INTS (the plan already holds E, U, W) only the grid sums are formed.
 template <typename T, typename T4, bool INTS>
-__global__ __launch_bounds__(64) void k_grid_grad(
+__global__ __launch_bounds__(64 * kGridWaves) void k_grid_grad(
     int32_t n_atom, int32_t bgroups, int64_t npad, const int64_t *__restrict__ seg,
     const int32_t *__restrict__ tile_i0, const int32_t *__restrict__ tile_n,
     const int32_t *__restrict__ tile_atom, const T4 *__restrict__ P0,
     const T4 *__restrict__ P1, const double4 *__restrict__ Pd, double *__restrict__ Gpart,
     double *__restrict__ Ipart) {
-    __shared__ T4 sA[TG], sB[TG];
-    const int t = blockIdx.x, grp = blockIdx.y, lane = threadIdx.x;
+    __shared__ GridLds<T4> lds;
+    const int t = blockIdx.x, grp = blockIdx.y, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    T4 *sA = lds.a[wave], *sB = lds.b[wave];
     const int A = tile_atom[t];
     const int nt = tile_n[t];
     const bool live = lane < nt;
@@ -66,17 +69,15 @@ __global__ __launch_bounds__(64) void k_grid_grad(
         // d_ij = -d_ji): formed for B > A only, the assembly takes the B < A
         // ones from the (B, A) sums; B <= A still adds to the pair integrals
         const bool gsum = B > A;
-        if (!INTS && !gsum) {
-            if (lane == 0)
-                for (int k = 0; k < 3; ++k) Gpart[((int64_t)t * n_atom + B) * 3 + k] = 0.0;
-            continue;
-        }
-        for (int64_t j0 = jb; j0 < je; j0 += TG) {
-            __syncthreads();
+        double *gp = Gpart + ((int64_t)t * n_atom + B) * 3;
+        if (!gsum && wave == 0 && lane < 3) gp[lane] = 0.0;
+        if (!INTS && !gsum) continue;
+        for (int64_t j0 = jb + TG * wave; j0 < je; j0 += TG * kGridWaves) {
+            wave_lds_sync();
             const int64_t j = j0 + lane;
             sA[lane] = P0[j < je ? j : jb];
             sB[lane] = P1[j < je ? j : jb];
-            __syncthreads();
+            wave_lds_sync();
             const int cnt = (int)min((int64_t)TG, je - j0);
             T pc[3] = {}, c[3] = {};
             if (!gsum) {
@@ -114,25 +115,31 @@ __global__ __launch_bounds__(64) void k_grid_grad(
 #pragma unroll
                 for (int k = 0; k < 3; ++k) pint[k] += (double)pc[k];
         }
-        double *gp = Gpart + ((int64_t)t * n_atom + B) * 3;
+        if (!gsum) continue;
+        __syncthreads();   // the previous sums have been read
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const double tot = gsum ? wave_sum(ai * 3.0 * acc[k]) : 0.0;
-            if (lane == 0) gp[k] = tot;
+        for (int k = 0; k < 3; ++k) lds.red[wave][k][lane] = acc[k];
+        __syncthreads();
+        if (wave < 3) {
+            const double tot = wave_sum(ai * 3.0 * waves_sum(lds.red, wave, lane));
+            if (lane == 0) gp[wave] = tot;
         }
     }
-    if (INTS && live) {
-        // self pair in FP64 (group of the own atom): E += a Phi, U += -a Phi h
-        double self[3] = {0, 0, 0};
-        if (A % bgroups == grp) {
-            const double4 pd = Pd[i];
-            const SelfPair q = self_pair(pd.x);
-            self[0] = pd.y * q.phi;
-            self[1] = -pd.y * q.phi * q.h;
-        }
-        const double sc[3] = {-1.5, 1.5, 1.5};
+    if (INTS) {
+        __syncthreads();
 #pragma unroll
-        for (int k = 0; k < 3; ++k) Ipart[((int64_t)grp * 3 + k) * npad + i] = sc[k] * pint[k] + self[k];
+        for (int k = 0; k < 3; ++k) lds.red[wave][k][lane] = pint[k];
+        __syncthreads();
+        if (live && wave < 3) {
+            double v = (wave == 0 ? -1.5 : 1.5) * waves_sum(lds.red, wave, lane);
+            // self pair in FP64 (group of the own atom): E += a Phi, U += -a Phi h
+            if (A % bgroups == grp && wave < 2) {
+                const double4 pd = Pd[i];
+                const SelfPair q = self_pair(pd.x);
+                v += pd.y * q.phi * (wave == 0 ? 1.0 : -q.h);
+            }
+            Ipart[((int64_t)grp * 3 + wave) * npad + i] = v;
+        }
     }
 }
 
@@ -163,11 +170,11 @@ void grid_grad_mode(vv10_plan *p) {
     const GradWork &gw = p->gw;
     dim3 grid((unsigned)p->ntiles, (unsigned)gw.bgroups);
     if (p->prec == VV10_FP64)
-        k_grid_grad<double, double4, INTS><<<grid, TG, 0, p->stream>>>(
+        k_grid_grad<double, double4, INTS><<<grid, 64 * kGridWaves, 0, p->stream>>>(
             p->n_atom, gw.bgroups, p->npad, p->d_seg, p->d_tile_i0, p->d_tile_n, p->d_tile_atom,
             p->P0, p->P1, p->P1, gw.Gpart, gw.Igrp);
     else
-        k_grid_grad<float, float4, INTS><<<grid, TG, 0, p->stream>>>(
+        k_grid_grad<float, float4, INTS><<<grid, 64 * kGridWaves, 0, p->stream>>>(
             p->n_atom, gw.bgroups, p->npad, p->d_seg, p->d_tile_i0, p->d_tile_n, p->d_tile_atom,
             p->P0f, p->P1f, p->P1, gw.Gpart, gw.Igrp);
 }

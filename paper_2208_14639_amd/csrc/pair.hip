@@ -22,6 +22,12 @@ namespace vv10 {
 namespace {
 
 constexpr int JC = 256;   // j points staged per block step; wave w takes [64 w, 64 w + 64)
+// Workgroups that the j splits aim at.  The pass is bound by VALU issue (91 %
+// busy); with 2048, one round of resident workgroups, the few that are left
+// over ran a second one alone: hexamer 0.360 -> 0.330 ms in FP32 and 0.717 ->
+// 0.662 in FP64, 17 waters (N = 101949) 4.50 -> 4.14 in FP32; 4096: 0.334,
+// 0.683 and 4.27; 16384: 0.330, 0.670 and 4.23.
+constexpr int kPairBlocks = 8192;
 
 // Sums of one wave's 64 j of an LDS chunk.  SELF: the chunk holds the
 // outer points themselves (lane l's own point at jj = jself), whose pair is
@@ -41,8 +47,14 @@ __device__ __forceinline__ void pair_run(const T4 a0, const T4 a1, const T4 *s0,
         if constexpr (sizeof(T) == 8) r = rcp64(t * s); else r = rcp32(t * s);
         T pj = b1.y * r;
         if (SELF) pj = jj == jself ? T(0) : pj;
-        const T ig = gp * (s * r), is = t * r;
-        const T h = ig + is;
+        T ig, is, h;
+        if constexpr (sizeof(T) == 8 && !HESS) {
+            h = (gp * r) * (s + g);   // 1/g + 1/s without forming either
+        } else {
+            ig = gp * (s * r);
+            is = t * r;
+            h = ig + is;
+        }
         const T ph = pj * h;
         c[0] += pj;
         c[1] += ph;
@@ -199,9 +211,14 @@ __global__ __launch_bounds__(256) void k_sum_partials(int64_t nb, const double *
 }  // namespace
 
 int pair_splits(int64_t npad) {
-    // enough workgroups for about eight waves per SIMD on 256 CUs
     const int64_t blocks = npad / 64;
-    int S = (int)std::min<int64_t>(16, std::max<int64_t>(1, (2048 + blocks - 1) / blocks));
+    int S = (int)std::min<int64_t>(16, std::max<int64_t>(1, (kPairBlocks + blocks - 1) / blocks));
+    // a grid that fits vv10_energy_potential_noalloc's scratch without
+    // partials keeps fitting (about 268 bytes a point besides them), and both
+    // paths split alike
+    const int64_t scratch = VV10_NOALLOC_SCRATCH_BYTES;
+    if (268 * npad <= scratch)
+        while (S > 1 && (268 + 8 * NI * S) * npad > scratch - (1 << 20)) --S;
     while (S > 1 && npad / S < JC) --S;
     return S;
 }
