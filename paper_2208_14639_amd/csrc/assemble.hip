@@ -42,6 +42,8 @@
 //    diagonal blocks of E_{gr,gr} from translational invariance, and the
 //    gradient E_G + E_gr, E_gr = sum_{i in A} a_i E^{Agr}_i
 //    = -sum_{B != A} sum_{i in A} a_i E^{Bgr}_i.
+#include <type_traits>
+
 #include "dev_common.h"
 #include "vv10_internal.h"
 
@@ -99,8 +101,9 @@ struct WeightIn {
     double *Rw;            // [npad][Pp] output
 };
 
-// One wave per point; the partials are FP64 ([S][npad][2][Pp]; with one
-// split they alias Y, read before R is written in place).
+// One wave per point; the partials are [S][npad][2][Pp], FP64 or, in the mixed
+// modes with splits of one FP32 run, the FP32 sums themselves (with one split
+// they are FP64 and alias Y, read before R is written in place).
 template <typename T, bool WT>
 __global__ __launch_bounds__(256) void k_resp(
     int64_t n, int64_t npad, int32_t P, int32_t Pp, int32_t S, const int32_t *__restrict__ atom_of,
@@ -534,10 +537,14 @@ hipError_t launch_gradient(vv10_plan *p, const double *rho_x, const double *grad
 hipError_t launch_trial_response(vv10_plan *p, double *f_rho_t, double *f_gamma_t) {
     const Workspace &ws = p->rws;
     dim3 grid((unsigned)((p->n + TRI - 1) / TRI), (unsigned)((ws.P + TRX - 1) / TRX));
-    // the contraction partials are FP64 in every mode
-    k_trial_resp<double><<<grid, 256, 0, p->stream>>>(
-        p->n, p->npad, ws.P, ws.Pp, ws.jsplit, p->P1, p->F, p->Ir, ws.L,
-        static_cast<const double *>(ws.Ypart), f_rho_t, f_gamma_t);
+    auto go = [&](auto *ypart) {
+        using T = std::remove_const_t<std::remove_pointer_t<decltype(ypart)>>;
+        k_trial_resp<T><<<grid, 256, 0, p->stream>>>(
+            p->n, p->npad, ws.P, ws.Pp, ws.jsplit, p->P1, p->F, p->Ir, ws.L, ypart, f_rho_t,
+            f_gamma_t);
+    };
+    if (partial_elem(p->prec, p->npad, ws.jlen) == sizeof(float)) go(static_cast<const float *>(ws.Ypart));
+    else go(static_cast<const double *>(ws.Ypart));
     return hipGetLastError();
 }
 
@@ -548,18 +555,20 @@ hipError_t launch_assemble(vv10_plan *p, const vv10_nuclear_outputs &out, bool w
     double *hess = out.hess, *grad = out.grad;
     {
         const unsigned nb = (unsigned)((n + 3) / 4);
-        // the contraction partials are FP64 in every mode
-        const WeightIn<double> wt = {static_cast<const double *>(ww.Ypart), ww.Lw, ww.Ze, ww.Rw};
-        if (weighted)
-            k_resp<double, true><<<nb, 256, 0, p->stream>>>(
-                n, p->npad, ws.P, ws.Pp, ws.jsplit, p->atom_of, p->P1, p->F, p->I, ws.L,
-                static_cast<const double *>(ws.Ypart), ws.Y, ws.Z, wt, out.resp_rho,
-                out.resp_gamma, out.fock_rho, out.fock_gamma);
-        else
-            k_resp<double, false><<<nb, 256, 0, p->stream>>>(
-                n, p->npad, ws.P, ws.Pp, ws.jsplit, p->atom_of, p->P1, p->F, p->I, ws.L,
-                static_cast<const double *>(ws.Ypart), ws.Y, ws.Z, wt, out.resp_rho,
-                out.resp_gamma, out.fock_rho, out.fock_gamma);
+        auto go = [&](auto *ypart) {
+            using T = std::remove_const_t<std::remove_pointer_t<decltype(ypart)>>;
+            const WeightIn<T> wt = {static_cast<const T *>(ww.Ypart), ww.Lw, ww.Ze, ww.Rw};
+            if (weighted)
+                k_resp<T, true><<<nb, 256, 0, p->stream>>>(
+                    n, p->npad, ws.P, ws.Pp, ws.jsplit, p->atom_of, p->P1, p->F, p->I, ws.L, ypart,
+                    ws.Y, ws.Z, wt, out.resp_rho, out.resp_gamma, out.fock_rho, out.fock_gamma);
+            else
+                k_resp<T, false><<<nb, 256, 0, p->stream>>>(
+                    n, p->npad, ws.P, ws.Pp, ws.jsplit, p->atom_of, p->P1, p->F, p->I, ws.L, ypart,
+                    ws.Y, ws.Z, wt, out.resp_rho, out.resp_gamma, out.fock_rho, out.fock_gamma);
+        };
+        if (partial_elem(p->prec, p->npad, ws.jlen) == sizeof(float)) go(static_cast<const float *>(ws.Ypart));
+        else go(static_cast<const double *>(ws.Ypart));
     }
     if (!hess && !grad) return hipGetLastError();
     const int64_t slice = (n + ws.gsplit - 1) / ws.gsplit;

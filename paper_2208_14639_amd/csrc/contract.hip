@@ -257,14 +257,13 @@ __device__ __forceinline__ void tile_f32(int64_t npad, int64_t jlen, int32_t Pp,
     // D layout of the FP32 MFMAs (measured on gfx950): item r of lane l holds
     // row 4 (l/16) + r, column l%16.  The FP32 sums of each run of kFp32Run
     // points go into this split's FP64 partials.
-    double *Yb = Yout + (int64_t)split * npad * 2 * Pp;
+    const PartialRows Yb(Yout, split, npad * 2 * Pp, partials_f32(npad, jlen));
     bool first = true;
     auto flush = [&]() {
         // one base address formed here (the empty asm keeps it from being
         // hoisted out of the loop)
         int64_t off = (ibase + 4 * kq) * 2 * Pp + col0 + m;
         asm volatile("" : "+v"(off));
-        double *y = Yb + off;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             float vp[NCB], vq[NCB];
@@ -273,8 +272,8 @@ __device__ __forceinline__ void tile_f32(int64_t npad, int64_t jlen, int32_t Pp,
                 vp[cb] = accp[cb][r];
                 vq[cb] = accq[cb][r];
             }
-            add_row<NCB>(y + (2 * r + 0) * (int64_t)Pp, vp, first);
-            add_row<NCB>(y + (2 * r + 1) * (int64_t)Pp, vq, first);
+            add_row<NCB>(Yb, off + (2 * r + 0) * (int64_t)Pp, vp, first);
+            add_row<NCB>(Yb, off + (2 * r + 1) * (int64_t)Pp, vq, first);
         }
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) {
@@ -442,14 +441,13 @@ __device__ __forceinline__ void tile_bf16x3(int64_t npad, int64_t jlen, int32_t 
     }
     // the FP32 sums of each run of kFp32Run points go into this split's FP64
     // partials (D layout: item r of lane (m, g) is row 4 g + r, column m)
-    double *Yb = Yout + (int64_t)split * npad * 2 * Pp;
+    const PartialRows Yb(Yout, split, npad * 2 * Pp, partials_f32(npad, jlen));
     bool first = true;
     auto flush = [&]() {
         // one base address formed here (the empty asm keeps it from being
         // hoisted out of the loop: 2 x 4 x NCB addresses would stay live)
         int64_t off = (ibase + 4 * g) * 2 * Pp + col0 + m;
         asm volatile("" : "+v"(off));
-        double *y = Yb + off;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             float vp[NCB], vq[NCB];
@@ -458,8 +456,8 @@ __device__ __forceinline__ void tile_bf16x3(int64_t npad, int64_t jlen, int32_t 
                 vp[cb] = accp[cb][r];
                 vq[cb] = accq[cb][r];
             }
-            add_row<NCB>(y + (2 * r + 0) * (int64_t)Pp, vp, first);
-            add_row<NCB>(y + (2 * r + 1) * (int64_t)Pp, vq, first);
+            add_row<NCB>(Yb, off + (2 * r + 0) * (int64_t)Pp, vp, first);
+            add_row<NCB>(Yb, off + (2 * r + 1) * (int64_t)Pp, vq, first);
         }
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) {
@@ -1017,15 +1015,14 @@ __global__ __launch_bounds__(256, 2) void k_contract_bf16x3_w(
     }
     // the FP32 sums of each run of kFp32Run points go into this split's FP64
     // partials (D layout: item r of lane l holds row 4 (l/16) + r, column l%16)
-    double *Yb = Yout + (int64_t)blockIdx.z * npad * 2 * Pp;
-    double *Yw = Ywout + (int64_t)blockIdx.z * npad * 3 * Pp;
+    const PartialRows Yb(Yout, blockIdx.z, npad * 2 * Pp, partials_f32(npad, jlen));
+    const PartialRows Yw(Ywout, blockIdx.z, npad * 3 * Pp, partials_f32(npad, jlen));
     bool first = true;
     auto flush = [&]() {
         // base addresses formed here (the empty asm keeps them from being
         // hoisted out of the loop)
         int64_t ob = (ibase + 4 * g) * 2 * Pp + m, ow = (ibase + 4 * g) * 3 * Pp + m;
         asm volatile("" : "+v"(ob), "+v"(ow));
-        double *yb = Yb + ob, *yw = Yw + ow;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             float v[5][NCB];
@@ -1037,11 +1034,11 @@ __global__ __launch_bounds__(256, 2) void k_contract_bf16x3_w(
                 v[3][cb] = awq[cb][r];
                 v[4][cb] = awv[cb][r];
             }
-            add_row<NCB>(yb + (2 * r + 0) * (int64_t)Pp, v[0], first);
-            add_row<NCB>(yb + (2 * r + 1) * (int64_t)Pp, v[1], first);
-            add_row<NCB>(yw + (3 * r + 0) * (int64_t)Pp, v[2], first);
-            add_row<NCB>(yw + (3 * r + 1) * (int64_t)Pp, v[3], first);
-            add_row<NCB>(yw + (3 * r + 2) * (int64_t)Pp, v[4], first);
+            add_row<NCB>(Yb, ob + (2 * r + 0) * (int64_t)Pp, v[0], first);
+            add_row<NCB>(Yb, ob + (2 * r + 1) * (int64_t)Pp, v[1], first);
+            add_row<NCB>(Yw, ow + (3 * r + 0) * (int64_t)Pp, v[2], first);
+            add_row<NCB>(Yw, ow + (3 * r + 1) * (int64_t)Pp, v[3], first);
+            add_row<NCB>(Yw, ow + (3 * r + 2) * (int64_t)Pp, v[4], first);
         }
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) {

@@ -22,16 +22,36 @@ __device__ __forceinline__ double rcp64(double x) {
 // before those after it.
 __device__ __forceinline__ void mem_order() { asm volatile("" ::: "memory"); }
 
-// Adds one tile row's FP32 sums v[0..N) into its FP64 partials y[0], y[16],
-// ..., y[16 (N - 1)] (N column blocks of 16); first: y is written, not read.
+// The partial sums of one j split of a mixed contraction.  A split of at most
+// one FP32 run stores its FP32 sums as they are (f32: half the bytes written
+// here and read by the assembly, no value changed: hexamer, nine splits, step
+// 2.28 -> 2.23 ms, with moving weights 3.36 -> 3.31); a longer one adds its runs
+// into FP64.
+struct PartialRows {
+    double *y;
+    bool f32;
+    // split: rows of width elements each (all splits back to back)
+    __device__ __forceinline__ PartialRows(double *all, int64_t split, int64_t elems, bool single)
+        : y(single ? reinterpret_cast<double *>(reinterpret_cast<float *>(all) + split * elems)
+                   : all + split * elems),
+          f32(single) {}
+};
+
+// Adds one tile row's FP32 sums v[0..N) into its partials at off, off + 16,
+// ..., off + 16 (N - 1) (N column blocks of 16); first: written, not read.
 // Each partial element has a single writer (one lane of one workgroup), so a
 // plain read-add-write suffices and the order of the additions, and the
 // result, are fixed.  The row's loads are issued together before the adds
 // (one wait per row), and rows are added one at a time so that their loads
 // do not all occupy registers at once.
 template <int N>
-__device__ __forceinline__ void add_row(double *y, const float *v, bool first) {
-    if (first) {
+__device__ __forceinline__ void add_row(const PartialRows &p, int64_t off, const float *v, bool first) {
+    double *y = p.y + off;
+    if (p.f32) {
+        float *yf = reinterpret_cast<float *>(p.y) + off;
+#pragma unroll
+        for (int k = 0; k < N; ++k) yf[16 * k] = v[k];
+    } else if (first) {
 #pragma unroll
         for (int k = 0; k < N; ++k) y[16 * k] = (double)v[k];
     } else {

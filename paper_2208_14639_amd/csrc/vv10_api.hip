@@ -66,7 +66,7 @@ size_t workspace_bytes(int64_t npad, int32_t n_atom, int32_t ntiles, vv10_precis
     size_t b = 3 * ch * sizeof(double);                       // L, Y, Z
     b += ch * (prec == VV10_FP64 ? 8 : 4);                    // X (FP64, FP32, or BF16 hi + lo)
     const bool alias = ws.jsplit == 1;   // partials written straight into Y
-    if (!alias) b += (size_t)ws.jsplit * ch * partial_elem(prec);
+    if (!alias) b += (size_t)ws.jsplit * ch * partial_elem(prec, npad, ws.jlen);
     b += (size_t)ntiles * n_atom * 9 * sizeof(double);
     b += (size_t)ws.bgroups * NI * npad * sizeof(double);
     b += (size_t)(ws.gsplit + 1) * (ws.Pp + 1) * ws.Pp * sizeof(double);
@@ -84,7 +84,7 @@ size_t response_bytes(int64_t npad, vv10_precision prec, const Workspace &ws) {
     const size_t ch = (size_t)npad * 2 * ws.Pp;
     size_t b = ch * sizeof(double);                           // L
     b += ch * (prec == VV10_FP64 ? 8 : 4);                    // X
-    b += (size_t)ws.jsplit * ch * partial_elem(prec);         // partials
+    b += (size_t)ws.jsplit * ch * partial_elem(prec, npad, ws.jlen);         // partials
     b += (size_t)NI * npad * sizeof(double);                  // pair integrals
     return b;
 }
@@ -228,7 +228,7 @@ vv10_status vv10::ensure_workspace(vv10_plan *p) {
         if (ws.jsplit == 1) {
             ws.Ypart = ws.Y;
         } else {
-            e = dalloc(&yp, ch * ws.jsplit * vv10::partial_elem(p->prec));
+            e = dalloc(&yp, ch * ws.jsplit * vv10::partial_elem(p->prec, p->npad, ws.jlen));
             ws.Ypart = yp;
         }
     }
@@ -269,7 +269,7 @@ static vv10_status ensure_response_workspace(vv10_plan *p, int32_t n_t) {
     e = dalloc(&xb, ch * (p->prec == VV10_FP64 ? 8 : 4));
     ws.X = xb;
     if (e == hipSuccess) e = dalloc(&ws.L, ch);
-    if (e == hipSuccess) e = dalloc(&yp, ch * ws.jsplit * vv10::partial_elem(p->prec));
+    if (e == hipSuccess) e = dalloc(&yp, ch * ws.jsplit * vv10::partial_elem(p->prec, p->npad, ws.jlen));
     ws.Ypart = yp;
     if (e != hipSuccess) {
         free_workspace(ws);
@@ -340,7 +340,7 @@ static vv10_status ensure_weight_work(vv10_plan *p) {
     if (e == hipSuccess) e = dalloc(&xv, ch * (p->prec == VV10_FP64 ? 8 : 4));
     ww.Xv = xv;
     if (e == hipSuccess) e = dalloc(&ww.Lw, ch);
-    if (e == hipSuccess) e = dalloc(&yp, ch * 3 * ws.jsplit * vv10::partial_elem(p->prec));
+    if (e == hipSuccess) e = dalloc(&yp, ch * 3 * ws.jsplit * vv10::partial_elem(p->prec, p->npad, ws.jlen));
     ww.Ypart = yp;
     if (e == hipSuccess) e = dalloc(&ww.Ze, ch);
     if (e == hipSuccess) e = dalloc(&ww.Rw, ch);
@@ -353,7 +353,7 @@ static vv10_status ensure_weight_work(vv10_plan *p) {
     ww.bytes = (size_t)p->npad * 3 * sizeof(double)                    // Wown
              + ch * (p->prec == VV10_FP64 ? 8 : 4)                      // Xv
              + 3 * ch * sizeof(double)                                  // Lw, Ze, Rw
-             + ch * 3 * ws.jsplit * vv10::partial_elem(p->prec)         // partials
+             + ch * 3 * ws.jsplit * vv10::partial_elem(p->prec, p->npad, ws.jlen)         // partials
              + (size_t)ws.gsplit * (ws.Pp + 1) * ws.Pp * sizeof(double); // GEMM slices
     p->ww = ww;
     return VV10_OK;

@@ -36,7 +36,8 @@ constexpr int kPad = 256;        // npad is a multiple of this
 constexpr int kGridTile = 64;    // i points per grid-term tile (one wave)
 // The mixed contractions sum at most kFp32Run consecutive j points of a tile
 // in FP32 (the MFMA accumulators) and then add those sums into the tile's
-// rows of the split's FP64 partials: FP32 within a tile, FP64 across tiles.
+// rows of the split's FP64 partials: FP32 within a tile, FP64 across tiles
+// (a split of one tile keeps its FP32 sums as its partials).
 // Each addition after the first re-reads the rows (about 32 N^2 P / kFp32Run
 // bytes over a contraction), which sets the length.
 constexpr int kFp32Run = 8192;
@@ -51,7 +52,7 @@ struct Workspace {
     void *X = nullptr;           // (p, q) channels: FP64 or FP32 [npad][2][Pp];
                                  // BF16X3: hi then lo, each [npad/16][Pp/16][4][16][8] bf16
     double *L = nullptr;         // [npad][2][Pp] (rho^x, gamma^x)
-    void *Ypart = nullptr;       // [jsplit][npad][2][Pp] contraction partials (FP64; Y itself with one split)
+    void *Ypart = nullptr;       // [jsplit][npad][2][Pp] contraction partials (partial_elem; Y itself with one split)
     double *Y = nullptr;         // [npad][2][Pp] summed contraction, then R in place
     double *Z = nullptr;         // [npad][2][Pp] grid-position channels
     double *Dpart = nullptr;     // [ntiles][n_atom][9] tile sums of a_i D^B_i (6) and a_i E^{Bgr}_i (3)
@@ -82,7 +83,7 @@ struct WeightWork {
     double *Wown = nullptr;      // [npad][3] owner-atom slot of w^x
     void *Xv = nullptr;          // v = w^x rho: FP64/FP32 [npad][Pp]; BF16X3 hi, lo [npad/32][Pp/16][4][16][8]
     double *Lw = nullptr;        // [npad][Pp] w^x with the owner slot filled
-    void *Ypart = nullptr;       // [jsplit][npad][3][Pp] (Y_pv, Y_qv, Y_vv) partials, FP64
+    void *Ypart = nullptr;       // [jsplit][npad][3][Pp] (Y_pv, Y_qv, Y_vv) partials, as the contraction's
     double *Ze = nullptr;        // [npad][Pp] E^{Bgr}_i (grid pass)
     double *Rw = nullptr;        // [npad][Pp] right factor of the w^x rows of the GEMM
     double *Hpart = nullptr;     // [gsplit][Pp + 1][Pp] GEMM slices of the w^x rows
@@ -267,8 +268,15 @@ int contract_blocks_per_cu(vv10_precision prec, int ncb);
 inline int max_ncb(vv10_precision prec) { return prec == VV10_FP64 ? 8 : 12; }
 // Max 16-column blocks per weight-contraction workgroup (three outputs).
 inline int max_wncb(vv10_precision prec) { return prec == VV10_FP64 ? 4 : 8; }
-// Bytes of one element of the contraction partials: FP64 in every mode (the
-// mixed modes add their FP32 tile sums into them).
-inline size_t partial_elem(vv10_precision) { return sizeof(double); }
+// Whether a mixed contraction's partials are FP32: several splits of at most
+// one FP32 run each, whose sums are FP32 numbers (one split is summed into Y
+// itself, longer ones add their runs in FP64).
+__host__ __device__ inline bool partials_f32(int64_t npad, int64_t jlen) {
+    return jlen <= kFp32Run && jlen < npad;
+}
+// Bytes of one element of the contraction partials.
+inline size_t partial_elem(vv10_precision prec, int64_t npad, int64_t jlen) {
+    return prec != VV10_FP64 && partials_f32(npad, jlen) ? sizeof(float) : sizeof(double);
+}
 
 }  // namespace vv10

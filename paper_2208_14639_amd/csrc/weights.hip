@@ -198,16 +198,17 @@ __global__ __launch_bounds__(256, 2) void k_wcontract(int64_t npad, int64_t jlen
         accq[cb] = (Acc){0, 0, 0, 0};
         accv[cb] = (Acc){0, 0, 0, 0};
     }
-    // the partials are FP64: FP64 sums are stored once at the end; FP32 sums
-    // go in after each run of kFp32Run points
-    double *Yb = Yout + (int64_t)blockIdx.z * npad * 3 * Pp;
+    // FP64 sums are stored once at the end; FP32 sums go into the partials
+    // after each run of kFp32Run points
+    const PartialRows Yb(Yout, blockIdx.z, npad * 3 * Pp, sizeof(T) == 4 && partials_f32(npad, jlen));
     bool first = true;
     auto flush = [&]() {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int64_t row = ibase + WTraits<T>::row(r, kq);
-            double *y = Yb + row * 3 * Pp + col0 + m;
+            const int64_t off = row * 3 * Pp + col0 + m;
             if constexpr (sizeof(T) == 8) {
+                double *y = Yb.y + off;
 #pragma unroll
                 for (int cb = 0; cb < NCB; ++cb) {
                     y[0 * Pp + cb * 16] = accp[cb][r];
@@ -222,9 +223,9 @@ __global__ __launch_bounds__(256, 2) void k_wcontract(int64_t npad, int64_t jlen
                     v[1][cb] = accq[cb][r];
                     v[2][cb] = accv[cb][r];
                 }
-                add_row<NCB>(y + 0 * (int64_t)Pp, v[0], first);
-                add_row<NCB>(y + 1 * (int64_t)Pp, v[1], first);
-                add_row<NCB>(y + 2 * (int64_t)Pp, v[2], first);
+                add_row<NCB>(Yb, off + 0 * (int64_t)Pp, v[0], first);
+                add_row<NCB>(Yb, off + 1 * (int64_t)Pp, v[1], first);
+                add_row<NCB>(Yb, off + 2 * (int64_t)Pp, v[2], first);
             }
         }
 #pragma unroll
@@ -354,14 +355,13 @@ __global__ __launch_bounds__(256, 2) void k_wcontract_bf16x3(int64_t npad, int64
     }
     // the FP32 sums of each run of kFp32Run points go into this split's FP64
     // partials (D layout: item r of lane l holds row 4 (l/16) + r, column l%16)
-    double *Yb = Yout + (int64_t)blockIdx.z * npad * 3 * Pp;
+    const PartialRows Yb(Yout, blockIdx.z, npad * 3 * Pp, partials_f32(npad, jlen));
     bool first = true;
     auto flush = [&]() {
         // one base address formed here (the empty asm keeps it from being
         // hoisted out of the loop)
         int64_t off = (ibase + 4 * g) * 3 * Pp + col0 + m;
         asm volatile("" : "+v"(off));
-        double *y = Yb + off;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             float v[3][NCB];
@@ -371,9 +371,9 @@ __global__ __launch_bounds__(256, 2) void k_wcontract_bf16x3(int64_t npad, int64
                 v[1][cb] = accq[cb][r];
                 v[2][cb] = accv[cb][r];
             }
-            add_row<NCB>(y + (3 * r + 0) * (int64_t)Pp, v[0], first);
-            add_row<NCB>(y + (3 * r + 1) * (int64_t)Pp, v[1], first);
-            add_row<NCB>(y + (3 * r + 2) * (int64_t)Pp, v[2], first);
+            add_row<NCB>(Yb, off + (3 * r + 0) * (int64_t)Pp, v[0], first);
+            add_row<NCB>(Yb, off + (3 * r + 1) * (int64_t)Pp, v[1], first);
+            add_row<NCB>(Yb, off + (3 * r + 2) * (int64_t)Pp, v[2], first);
         }
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) {
