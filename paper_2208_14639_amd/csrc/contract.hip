@@ -951,69 +951,90 @@ __global__ void k_zero_counter(int32_t *c) { *c = 0; }
 // 16 + 4 g + e - 4 (e >= 4) of the block, which is the order in which the
 // weight packing stores v.
 // ---------------------------------------------------------------------------
-// The four main values and the three weight values (r - c_i A, -R^2 A, r)
-// of pair (i, j), all divided by -3/2; the main values are those of pair_K.
-__device__ __forceinline__ void pair_KW(const float4 a0, const float4 a1, const float4 b0,
-                                        const float4 b1, float *k) {
-    const float dx = a0.x - b0.x, dy = a0.y - b0.y, dz = a0.z - b0.z;
-    const float R2 = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, dz * dz));
-    const float gg = __builtin_fmaf(a0.w, R2, a1.x);
-    const float gp = __builtin_fmaf(b0.w, R2, b1.x);
-    const float s = gg + gp, t = gg * gp;
-    const float r = rcp32(t * s);
-    const float sr = s * r;
-    const float is = t * r;
-    const float A = r * __builtin_fmaf(gp, sr, is);
-    const float Ap = r * __builtin_fmaf(gg, sr, is);
-    const float Q = (r + r) * __builtin_fmaf(is, is, sr);
-    const float ci = a1.z, cj = b1.z;
-    const float t1 = __builtin_fmaf(ci, Q, -Ap);
-    const float t2 = __builtin_fmaf(cj, Q, -A);
-    const float base = __builtin_fmaf(-ci, A, r);
-    k[0] = __builtin_fmaf(cj, t1, base);    // kpp
-    k[1] = R2 * t1;                         // kpq
-    k[2] = R2 * t2;                         // kqp
-    k[3] = (R2 * R2) * Q;                   // kqq
-    k[4] = base;                            // kpv
-    k[5] = -R2 * A;                         // kqv
-    k[6] = r;                               // kvv
-}
+// Two pairs of a block in four steps, so that a caller can place each step
+// between MFMAs: (0) the geometries and reciprocals, (1) the four main values
+// and the three weight values (r - c_i A, -R^2 A, r) of each pair, divided by
+// -3/2, (2) the hi/lo split of the main values, (3) that of the weight values
+// (two pairs share a word).  The main values are those of pair_K.
+struct PairStepsW {
+    float R2[2], gg[2], gp[2], s[2], t[2], r[2], k[2][7];
+    __device__ __forceinline__ void geometry(int u, const float4 a0, const float4 a1,
+                                             const float4 b0, const float2 b1) {
+        const float dx = a0.x - b0.x, dy = a0.y - b0.y, dz = a0.z - b0.z;
+        R2[u] = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, dz * dz));
+        gg[u] = __builtin_fmaf(a0.w, R2[u], a1.x);
+        gp[u] = __builtin_fmaf(b0.w, R2[u], b1.x);
+        s[u] = gg[u] + gp[u];
+        t[u] = gg[u] * gp[u];
+        r[u] = rcp32(t[u] * s[u]);
+    }
+    // self: the self pair, whose K_pp and rows r - c_i A and r are left out
+    // (the others vanish there)
+    __device__ __forceinline__ void values(int u, float ci, float cj, bool self) {
+        const float sr = s[u] * r[u];
+        const float is = t[u] * r[u];
+        const float A = r[u] * __builtin_fmaf(gp[u], sr, is);
+        const float Ap = r[u] * __builtin_fmaf(gg[u], sr, is);
+        const float Q = (r[u] + r[u]) * __builtin_fmaf(is, is, sr);
+        const float t1 = __builtin_fmaf(ci, Q, -Ap);
+        const float t2 = __builtin_fmaf(cj, Q, -A);
+        const float base = __builtin_fmaf(-ci, A, r[u]);
+        const float kpp = __builtin_fmaf(cj, t1, base);
+        k[u][0] = self ? 0.f : kpp;
+        k[u][1] = R2[u] * t1;                       // kpq
+        k[u][2] = R2[u] * t2;                       // kqp
+        k[u][3] = (R2[u] * R2[u]) * Q;              // kqq
+        k[u][4] = self ? 0.f : base;                // kpv
+        k[u][5] = -R2[u] * A;                       // kqv
+        k[u][6] = self ? 0.f : r[u];                // kvv
+    }
+};
 
+// LDS units (16 B) of a stage: main hi and lo of two 16-point blocks, weight
+// hi and lo of the 32-point block (NCB x 64 units each), 64 units each of P0, P1.
 template <int NCB>
-constexpr int smem_bf16x3_w() {
-    return 2 * 6 * NCB * 16 * 4 * (int)sizeof(bf16x8) + 2 * 64 * (int)sizeof(float4);
-}
+constexpr int units_bf16x3_w() { return (6 * NCB + 2) * 64; }
 
+// Pipelined as tile_bf16x3, in chunks of one column block: NCB chunks of the
+// first 16-point block (six MFMAs), NCB of the second, NCB of the weight rows
+// (nine).  During the first NCB chunks the pairs of the second block are
+// formed, during the others those of the next stage's first block; the weight
+// rows' operands consist of both halves, so the half formed a stage ahead
+// waits in registers.  With the operands formed at the stage's start, the
+// staged data through registers and the reads next to their MFMAs the weighted
+// hexamer took 2.31 ms at 2.0 GHz, now 2.05 ms at 1.93 GHz.
 template <int NCB>
 __global__ __launch_bounds__(256, 2) void k_contract_bf16x3_w(
     int64_t npad, int64_t jlen, int32_t Pp, const float4 *__restrict__ P0,
     const float4 *__restrict__ P1, const bf16x8 *__restrict__ Xhi, const bf16x8 *__restrict__ Xlo,
     const bf16x8 *__restrict__ Vhi, const bf16x8 *__restrict__ Vlo, double *__restrict__ Yout,
     double *__restrict__ Ywout) {
-    constexpr int NC = NCB * 16;
-    constexpr int UNITS = NC * 4;           // 8-bf16 units of one array and block
-    constexpr int NARR = 6;                 // main hi (2 sub-blocks), main lo (2), weight hi, lo
-    constexpr int TOT = NARR * UNITS;
-    constexpr int PER = (TOT + 255) / 256;
-    __shared__ __attribute__((aligned(16))) char smem[smem_bf16x3_w<NCB>()];
-    bf16x8 *sX = reinterpret_cast<bf16x8 *>(smem);                 // [2][NARR][UNITS]
-    float4 *sP = reinterpret_cast<float4 *>(sX + 2 * TOT);         // [2][P0, P1][32]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    static_assert(kFp32Run % 64 == 0, "FP32 runs end on stage pairs");
+    constexpr int C = 3 * NCB;                  // chunks of a stage
+    constexpr int kAhead = NCB == 1 ? 1 : 2;
+    constexpr int PER = (6 * NCB + 3) / 4;      // 64-unit pieces per wave and stage
+    __shared__ __attribute__((aligned(16))) bf16x8 buf0[units_bf16x3_w<NCB>()];
+    __shared__ __attribute__((aligned(16))) bf16x8 buf1[units_bf16x3_w<NCB>()];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m = lane & 15, g = lane >> 4;
     const int64_t ibase = (int64_t)blockIdx.x * 64 + wave * 16;
     const int64_t jbeg = (int64_t)blockIdx.z * jlen;
     const int64_t jend = min(npad, jbeg + jlen);
     const float4 a0 = P0[ibase + m], a1 = P1[ibase + m];
     v4f accp[NCB], accq[NCB], awp[NCB], awq[NCB], awv[NCB];
+    auto clear = [&]() {
 #pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) {
-        accp[cb] = (v4f){0.f, 0.f, 0.f, 0.f};
-        accq[cb] = (v4f){0.f, 0.f, 0.f, 0.f};
-        awp[cb] = (v4f){0.f, 0.f, 0.f, 0.f};
-        awq[cb] = (v4f){0.f, 0.f, 0.f, 0.f};
-        awv[cb] = (v4f){0.f, 0.f, 0.f, 0.f};
-    }
-    // the FP32 sums of each run of kFp32Run points go into this split's FP64
+        for (int cb = 0; cb < NCB; ++cb) {
+            accp[cb] = (v4f){0.f, 0.f, 0.f, 0.f};
+            accq[cb] = (v4f){0.f, 0.f, 0.f, 0.f};
+            awp[cb] = (v4f){0.f, 0.f, 0.f, 0.f};
+            awq[cb] = (v4f){0.f, 0.f, 0.f, 0.f};
+            awv[cb] = (v4f){0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    clear();
+    // the FP32 sums of each run of kFp32Run points go into this split's
     // partials (D layout: item r of lane l holds row 4 (l/16) + r, column l%16)
     const PartialRows Yb(Yout, blockIdx.z, npad * 2 * Pp, partials_f32(npad, jlen));
     const PartialRows Yw(Ywout, blockIdx.z, npad * 3 * Pp, partials_f32(npad, jlen));
@@ -1040,135 +1061,210 @@ __global__ __launch_bounds__(256, 2) void k_contract_bf16x3_w(
             add_row<NCB>(Yw, ow + (3 * r + 1) * (int64_t)Pp, v[3], first);
             add_row<NCB>(Yw, ow + (3 * r + 2) * (int64_t)Pp, v[4], first);
         }
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) {
-            accp[cb] = (v4f){0.f, 0.f, 0.f, 0.f};
-            accq[cb] = (v4f){0.f, 0.f, 0.f, 0.f};
-            awp[cb] = (v4f){0.f, 0.f, 0.f, 0.f};
-            awq[cb] = (v4f){0.f, 0.f, 0.f, 0.f};
-            awv[cb] = (v4f){0.f, 0.f, 0.f, 0.f};
-        }
+        clear();
         first = false;
     };
-    bf16x8 rx[PER];
-    float4 rp = {0.f, 0.f, 0.f, 0.f};
-    // unit e = a UNITS + u of a block: a = 0, 1 main hi of sub-block 0, 1;
-    // 2, 3 main lo; 4, 5 weight hi, lo
-    auto load = [&](int64_t j0) {
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int e = tid + 256 * k;
-            if (e < TOT) {
-                const int a = e / UNITS, u = e - a * UNITS;
-                const bf16x8 *src = a < 4 ? (a < 2 ? Xhi : Xlo) + ((j0 / 16 + (a & 1)) * Pp) * 4
-                                          : (a == 4 ? Vhi : Vlo) + ((j0 / 32) * Pp) * 4;
-                rx[k] = src[u];
-            }
-        }
-        if (tid < 64) rp = (tid < 32 ? P0 : P1)[j0 + (tid & 31)];
+    auto to_lds = [](const void *base, uint32_t off, bf16x8 *dst) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, -1, 0x00027000),
+            reinterpret_cast<__attribute__((address_space(3))) void *>(
+                reinterpret_cast<uintptr_t>(dst)), 16, off, 0, 0, 0);
     };
-    auto store = [&](int b) {
+    // piece k: 64 units of one array and column block (where the waves
+    // outnumber the pieces left, some bring one that another wave brings too);
+    // its source at j = 0 and the units from one 16-point block to the next,
+    // in SGPRs
+    const bf16x8 *src[PER];
+    int64_t blk[PER];
+    int unit[PER];
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int e = tid + 256 * k;
-            if (e < TOT) sX[b * TOT + e] = rx[k];
-        }
-        if (tid < 64) sP[b * 64 + tid] = rp;
-    };
-    load(jbeg);
-    store(0);
-    __syncthreads();
-    int buf = 0;
-    for (int64_t j0 = jbeg; j0 < jend; j0 += 32) {
-        const bool more = j0 + 32 < jend;
-        if (more) load(j0 + 32);
-        const float4 *q0 = sP + buf * 64, *q1 = q0 + 32;
-        uint32_t mh[2][4], ml[2][4], nh[2][4], nl[2][4];
-        uint32_t vph[4], vpl[4], vqh[4], vql[4], vvh[4], vvl[4];
-#pragma unroll
-        for (int e = 0; e < 8; e += 2) {
-            const int sb = e >> 2, jj = e & 3;
-            const int jl = 16 * sb + 4 * g + jj;
-            float k0[7], k1[7];
-            pair_KW(a0, a1, q0[jl], q1[jl], k0);
-            pair_KW(a0, a1, q0[jl + 1], q1[jl + 1], k1);
-            split2(k0[0], k0[1], mh[sb][jj], ml[sb][jj]);
-            split2(k0[2], k0[3], nh[sb][jj], nl[sb][jj]);
-            split2(k1[0], k1[1], mh[sb][jj + 1], ml[sb][jj + 1]);
-            split2(k1[2], k1[3], nh[sb][jj + 1], nl[sb][jj + 1]);
-            split2(k0[4], k1[4], vph[e >> 1], vpl[e >> 1]);
-            split2(k0[5], k1[5], vqh[e >> 1], vql[e >> 1]);
-            split2(k0[6], k1[6], vvh[e >> 1], vvl[e >> 1]);
-        }
-        Aops A[2];
-#pragma unroll
-        for (int sb = 0; sb < 2; ++sb) {
-            A[sb].ph = __builtin_bit_cast(bf16x8, (uint4){mh[sb][0], mh[sb][1], mh[sb][2], mh[sb][3]});
-            A[sb].pl = __builtin_bit_cast(bf16x8, (uint4){ml[sb][0], ml[sb][1], ml[sb][2], ml[sb][3]});
-            A[sb].qh = __builtin_bit_cast(bf16x8, (uint4){nh[sb][0], nh[sb][1], nh[sb][2], nh[sb][3]});
-            A[sb].ql = __builtin_bit_cast(bf16x8, (uint4){nl[sb][0], nl[sb][1], nl[sb][2], nl[sb][3]});
-        }
-        bf16x8 wph = __builtin_bit_cast(bf16x8, (uint4){vph[0], vph[1], vph[2], vph[3]});
-        bf16x8 wpl = __builtin_bit_cast(bf16x8, (uint4){vpl[0], vpl[1], vpl[2], vpl[3]});
-        const bf16x8 wqh = __builtin_bit_cast(bf16x8, (uint4){vqh[0], vqh[1], vqh[2], vqh[3]});
-        const bf16x8 wql = __builtin_bit_cast(bf16x8, (uint4){vql[0], vql[1], vql[2], vql[3]});
-        bf16x8 wvh = __builtin_bit_cast(bf16x8, (uint4){vvh[0], vvh[1], vvh[2], vvh[3]});
-        bf16x8 wvl = __builtin_bit_cast(bf16x8, (uint4){vvl[0], vvl[1], vvl[2], vvl[3]});
-        {
-            // The stage that holds the outer points: the self pair (i, i) is
-            // point off = ibase - j0 + m of the stage, formed by lane group
-            // (off mod 16)/4 as main pair off mod 4 of sub-block off/16 (K_pp
-            // cleared) and as weight K entry e = 4 (off/16) + off mod 4 (the
-            // rows r - c_i A and r cleared; -R^2 A vanishes there).  The masks
-            // are applied in every stage (all ones off the diagonal): a branch
-            // here would split the stage into a VALU block and an MFMA block
-            // that the compiler then cannot interleave (measured on the
-            // weighted hexamer: 3.44-3.55 ms with the branch, 2.41 ms without).
-            const bool diag = j0 == (ibase & ~(int64_t)31);
-            const int off = (int)(ibase - j0) + m, sb = (off >> 4) & 1, jj = off & 3;
-            const bool mine = diag && g == ((off & 15) >> 2);
-            const uint4 km0 = bf16_clear_mask(mine && sb == 0, jj, false);
-            const uint4 km1 = bf16_clear_mask(mine && sb == 1, jj, false);
-            A[0].ph = bf16_apply_mask(A[0].ph, km0);
-            A[0].pl = bf16_apply_mask(A[0].pl, km0);
-            A[1].ph = bf16_apply_mask(A[1].ph, km1);
-            A[1].pl = bf16_apply_mask(A[1].pl, km1);
-            const int e = 4 * sb + jj;
-            const uint4 kw = bf16_clear_mask(mine, e >> 1, e & 1);
-            wph = bf16_apply_mask(wph, kw);
-            wpl = bf16_apply_mask(wpl, kw);
-            wvh = bf16_apply_mask(wvh, kw);
-            wvl = bf16_apply_mask(wvl, kw);
-        }
-        const bf16x8 *xb = sX + buf * TOT + lane;
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) {
-#pragma unroll
-            for (int sb = 0; sb < 2; ++sb) {
-                const bf16x8 bh = xb[sb * UNITS + cb * 64], bl = xb[(2 + sb) * UNITS + cb * 64];
-                accp[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[sb].ph, bh, accp[cb], 0, 0, 0);
-                accq[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[sb].qh, bh, accq[cb], 0, 0, 0);
-                accp[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[sb].pl, bh, accp[cb], 0, 0, 0);
-                accq[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[sb].ql, bh, accq[cb], 0, 0, 0);
-                accp[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[sb].ph, bl, accp[cb], 0, 0, 0);
-                accq[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[sb].qh, bl, accq[cb], 0, 0, 0);
-            }
-            const bf16x8 vh = xb[4 * UNITS + cb * 64], vl = xb[5 * UNITS + cb * 64];
-            awp[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wph, vh, awp[cb], 0, 0, 0);
-            awq[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wqh, vh, awq[cb], 0, 0, 0);
-            awv[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wvh, vh, awv[cb], 0, 0, 0);
-            awp[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wpl, vh, awp[cb], 0, 0, 0);
-            awq[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wql, vh, awq[cb], 0, 0, 0);
-            awv[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wvl, vh, awv[cb], 0, 0, 0);
-            awp[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wph, vl, awp[cb], 0, 0, 0);
-            awq[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wqh, vl, awq[cb], 0, 0, 0);
-            awv[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wvh, vl, awv[cb], 0, 0, 0);
-        }
-        if (more) store(buf ^ 1);
-        if ((j0 + 32 - jbeg) % kFp32Run == 0 && more) flush();
-        __syncthreads();
-        buf ^= 1;
+    for (int k = 0; k < PER; ++k) {
+        const int q = (wave + 4 * k) % (6 * NCB), arr = q / NCB, cb = q - arr * NCB;
+        const bf16x8 *x = Xhi;
+        if (arr >= 2) x = Xlo;
+        if (arr == 4) x = Vhi;
+        if (arr == 5) x = Vlo;
+        src[k] = x + (arr < 4 ? (arr & 1) * Pp * 4 : 0) + cb * 64;
+        blk[k] = arr < 4 ? 4 * Pp : 2 * Pp;
+        unit[k] = q * 64;
     }
+    const float4 *psrc = P0;
+    if (wave & 1) psrc = P1;
+    const int punit = (6 * NCB + (wave & 1)) * 64;
+    // piece k (the points: k = PER) of the stage at j
+    auto load_piece = [&](int k, int64_t j, bf16x8 *buf) __attribute__((always_inline)) {
+        if (k == PER) {
+            const uint32_t left = (uint32_t)min(npad - 1 - j, (int64_t)64);
+            to_lds(psrc + j, min(16u + (lane & 31), left) * (uint32_t)sizeof(float4), buf + punit);
+        } else {
+            to_lds(src[k] + (j / 16) * blk[k], lane * (uint32_t)sizeof(bf16x8), buf + unit[k]);
+        }
+    };
+    // points of this lane's four pairs of a block: (x, y, z, omega), (kappa, c)
+    float4 n0[4];
+    float2 n1[4];
+    auto read_points = [&](const bf16x8 *buf, int sub) {
+        const float4 *q = reinterpret_cast<const float4 *>(buf + 6 * NCB * 64) + 16 * sub + 4 * g;
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+            n0[jj] = q[jj];
+            n1[jj] = make_float2(q[64 + jj].x, q[64 + jj].z);
+        }
+    };
+    // the diagonal block leaves out the self pair: pair m mod 4 of lane (m, g = m/4)
+    bool self[4];
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) self[jj] = m == 4 * g + jj;
+    PairStepsW ps;
+    uint32_t ph[4], pl[4], qh[4], ql[4];             // main words being formed
+    uint32_t wf[6][2];                               // weight words being formed (ph, pl, qh, ql, vh, vl)
+    // step k of eight: pairs 2 (k / 4) and 2 (k / 4) + 1 (the empty asm
+    // statements keep each step's instructions in its chunk)
+    auto step = [&](int k, bool diag) {
+        const int e = 2 * (k / 4);
+        if (k % 4 == 0) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                ps.geometry(u, a0, a1, n0[e + u], n1[e + u]);
+                asm volatile("" : "+v"(ps.R2[u]), "+v"(ps.gg[u]), "+v"(ps.gp[u]), "+v"(ps.s[u]),
+                             "+v"(ps.t[u]), "+v"(ps.r[u]));
+            }
+        } else if (k % 4 == 1) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                ps.values(u, a1.z, n1[e + u].y, diag && self[e + u]);
+                asm volatile("" : "+v"(ps.k[u][0]), "+v"(ps.k[u][1]), "+v"(ps.k[u][2]),
+                             "+v"(ps.k[u][3]), "+v"(ps.k[u][4]), "+v"(ps.k[u][5]), "+v"(ps.k[u][6]));
+            }
+        } else if (k % 4 == 2) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                split2(ps.k[u][0], ps.k[u][1], ph[e + u], pl[e + u]);
+                split2(ps.k[u][2], ps.k[u][3], qh[e + u], ql[e + u]);
+                asm volatile("" : "+v"(ph[e + u]), "+v"(pl[e + u]), "+v"(qh[e + u]), "+v"(ql[e + u]));
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                split2(ps.k[0][4 + c], ps.k[1][4 + c], wf[2 * c][e / 2], wf[2 * c + 1][e / 2]);
+                asm volatile("" : "+v"(wf[2 * c][e / 2]), "+v"(wf[2 * c + 1][e / 2]));
+            }
+        }
+    };
+    auto formed = [&]() {
+        Aops A;
+        A.ph = __builtin_bit_cast(bf16x8, (uint4){ph[0], ph[1], ph[2], ph[3]});
+        A.pl = __builtin_bit_cast(bf16x8, (uint4){pl[0], pl[1], pl[2], pl[3]});
+        A.qh = __builtin_bit_cast(bf16x8, (uint4){qh[0], qh[1], qh[2], qh[3]});
+        A.ql = __builtin_bit_cast(bf16x8, (uint4){ql[0], ql[1], ql[2], ql[3]});
+        return A;
+    };
+    Aops A;                       // main operands of the block at hand
+    uint32_t wa[6][2];            // weight words of the stage's first half
+    bf16x8 W[6];                  // weight operands of the stage
+    bf16x8 Bh[kAhead + 1], Bl[kAhead + 1];
+    // B operands of chunk c: block 0, block 1, weight rows
+    auto unit_hi = [](int c) { return c < 2 * NCB ? c : c + 2 * NCB; };
+    auto unit_lo = [](int c) { return c < 2 * NCB ? c + 2 * NCB : c + 3 * NCB; };
+    auto stage = [&](int64_t j0, bf16x8 *cur, bf16x8 *nxt) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int part = c / NCB, cb = c - part * NCB;
+            if (c == C - kAhead) {
+                __builtin_amdgcn_s_waitcnt(0);   // this wave's LDS loads and reads are done
+                __syncthreads();
+            }
+            // pieces of the next stage (past the last one: that one again)
+#pragma unroll
+            for (int k = 0; k <= PER; ++k)
+                if (c == (k < C - kAhead ? k : C - kAhead - 1))
+                    load_piece(k, min(j0 + 32, jend - 32), nxt);
+            __builtin_amdgcn_sched_barrier(0);
+            {
+                const int pc = c + kAhead, q = pc % C;
+                const bf16x8 *b = (pc < C ? cur : nxt) + lane;
+                Bh[kAhead] = b[unit_hi(q) * 64];
+                Bl[kAhead] = b[unit_lo(q) * 64];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            const bf16x8 bh = Bh[0], bl = Bl[0];
+            if (part < 2) {
+                accp[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A.ph, bh, accp[cb], 0, 0, 0);
+                accq[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A.qh, bh, accq[cb], 0, 0, 0);
+                accp[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A.pl, bh, accp[cb], 0, 0, 0);
+                accq[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A.ql, bh, accq[cb], 0, 0, 0);
+                accp[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A.ph, bl, accp[cb], 0, 0, 0);
+                accq[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A.qh, bl, accq[cb], 0, 0, 0);
+            } else {
+                awp[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W[0], bh, awp[cb], 0, 0, 0);
+                awq[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W[2], bh, awq[cb], 0, 0, 0);
+                awv[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W[4], bh, awv[cb], 0, 0, 0);
+                awp[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W[1], bh, awp[cb], 0, 0, 0);
+                awq[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W[3], bh, awq[cb], 0, 0, 0);
+                awv[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W[5], bh, awv[cb], 0, 0, 0);
+                awp[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W[0], bl, awp[cb], 0, 0, 0);
+                awq[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W[2], bl, awq[cb], 0, 0, 0);
+                awv[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W[4], bl, awv[cb], 0, 0, 0);
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                if (part == 0 && k * NCB / 8 == cb) step(k, j0 + 16 == ibase);
+                if (part > 0 && k * 2 * NCB / 8 == c - NCB) step(k, j0 + 32 == ibase);
+            }
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) {
+                Bh[k] = Bh[k + 1];
+                Bl[k] = Bl[k + 1];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (c == NCB - 1) {
+                A = formed();
+#pragma unroll
+                for (int k = 0; k < 6; ++k)
+                    W[k] = __builtin_bit_cast(bf16x8, (uint4){wa[k][0], wa[k][1], wf[k][0], wf[k][1]});
+                read_points(cur, 1);
+            }
+            if (c == C - 1) {
+                A = formed();
+#pragma unroll
+                for (int k = 0; k < 6; ++k) {
+                    wa[k][0] = wf[k][0];
+                    wa[k][1] = wf[k][1];
+                }
+                read_points(nxt, 0);
+            }
+        }
+    };
+#pragma unroll
+    for (int k = 0; k <= PER; ++k) load_piece(k, jbeg, buf0);
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+        n0[jj] = P0[jbeg + 4 * g + jj];
+        n1[jj] = make_float2(P1[jbeg + 4 * g + jj].x, P1[jbeg + 4 * g + jj].z);
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) step(k, jbeg == ibase);
+    A = formed();
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        wa[k][0] = wf[k][0];
+        wa[k][1] = wf[k][1];
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) {
+        Bh[k] = buf0[unit_hi(k) * 64 + lane];
+        Bl[k] = buf0[unit_lo(k) * 64 + lane];
+    }
+    read_points(buf0, 0);
+    int64_t j0 = jbeg;
+    for (; j0 + 64 <= jend; j0 += 64) {
+        stage(j0, buf0, buf1);
+        stage(j0 + 32, buf1, buf0);
+        if ((j0 + 64 - jbeg) % kFp32Run == 0 && j0 + 64 < jend) flush();
+    }
+    if (j0 < jend) stage(j0, buf0, buf1);
     flush();
 }
 
