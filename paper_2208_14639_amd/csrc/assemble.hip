@@ -35,10 +35,10 @@
 //    row Pp, E_w = sum_i w^x_i rho_i (beta + E_i); the R terms above add
 //    2 E_{G,w}.  Symmetrised, this is the nine-term split without the
 //    caller's rho^{AB} and w^{AB} sums.
-// 3. k_hsum: Hsum = sum_s Hpart[s] in a fixed order (the w^x slices after
-//    the others).
-// 4. k_dsum: E_{gr,gr} tile sums of a_i D^B_i reduced per atom pair.
-// 5. k_finish: H = sym(Hsum) + sym(E_{gr,gr}), sym(M) = (M + M^T)/2, with the
+// 3. k_sums: Hsum = sum_s Hpart[s] in a fixed order (the w^x slices after
+//    the others), and the E_{gr,gr} tile sums of a_i D^B_i reduced per atom
+//    pair.
+// 4. k_finish: H = sym(Hsum) + sym(E_{gr,gr}), sym(M) = (M + M^T)/2, with the
 //    diagonal blocks of E_{gr,gr} from translational invariance, and the
 //    gradient E_G + E_gr, E_gr = sum_{i in A} a_i E^{Agr}_i
 //    = -sum_{B != A} sum_{i in A} a_i E^{Bgr}_i.
@@ -355,21 +355,42 @@ __global__ __launch_bounds__(256, 2) void k_gemm(int64_t n, int64_t npad, int64_
     if (grad && tid < 64 && l0 + tid < Pp) H[(int64_t)Pp * Pp + l0 + tid] = sT[64 * 64 + tid];
 }
 
-// Hsum[e] = sum_s Hpart[s][e], e < (Pp + 1) Pp, over the S slices of Hpart
-// and then the S2 slices of H2: 64 entries per workgroup, the four waves sum
-// consecutive quarters of the slices, added in wave order.
-// 16 waves per 64 elements, each over a sixteenth of the slices, so that
-// the few workgroups of a small Hessian keep enough loads in flight.
-constexpr int kHsumWaves = 16;
-__global__ __launch_bounds__(64 * kHsumWaves) void k_hsum(int64_t len, int S,
-                                                          const double *__restrict__ Hpart, int S2,
-                                                          const double *__restrict__ H2,
-                                                          double *__restrict__ Hsum) {
-    __shared__ double part[kHsumWaves][64];
+// Workgroups b < nh: Hsum[e] = sum_s Hpart[s][e], e < len = (Pp + 1) Pp, over
+// the S slices of Hpart and then the S2 slices of H2: 64 entries each, 16 waves
+// per 64 entries, each over a sixteenth of the slices, so that the few
+// workgroups of a small Hessian keep enough loads in flight; the waves' sums
+// are added in wave order.
+// Workgroups b >= nh: DS[A][B][c] = sum over the tiles t of atom A of
+// Dpart[t][B][c] (tile order), one thread each.  Two independent reductions of
+// a few us, bound by latency: one launch instead of two.
+constexpr int kSumWaves = 16;
+__global__ __launch_bounds__(64 * kSumWaves) void k_sums(
+    int64_t len, int S, const double *__restrict__ Hpart, int S2, const double *__restrict__ H2,
+    double *__restrict__ Hsum, int nh, int32_t n_atom, const int32_t *__restrict__ tile_first,
+    const double *__restrict__ Dpart, double *__restrict__ DS) {
+    __shared__ double part[kSumWaves][64];
+    if ((int)blockIdx.x >= nh) {
+        const int64_t k = (int64_t)(blockIdx.x - nh) * (64 * kSumWaves) + threadIdx.x;
+        if (k >= (int64_t)n_atom * n_atom * 9) return;
+        const int A = (int)(k / (9LL * n_atom));
+        const int rem = (int)(k - (int64_t)A * 9 * n_atom);   // B * 9 + c
+        // the own-atom slot (B = A) is never formed by the grid pass (its terms
+        // follow from translational invariance in k_finish): zero, not read
+        if (rem / 9 == A) {
+            DS[k] = 0.0;
+            return;
+        }
+        double v = 0.0;
+#pragma unroll 8
+        for (int t = tile_first[A]; t < tile_first[A + 1]; ++t)
+            v += Dpart[(int64_t)t * n_atom * 9 + rem];
+        DS[k] = v;
+        return;
+    }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t e = (int64_t)blockIdx.x * 64 + lane;
     const int St = S + S2;
-    const int q = (St + kHsumWaves - 1) / kHsumWaves;
+    const int q = (St + kSumWaves - 1) / kSumWaves;
     const int sb = min(St, wave * q), se = min(St, sb + q);
     double a = 0.0;
     if (e < len)
@@ -381,29 +402,9 @@ __global__ __launch_bounds__(64 * kHsumWaves) void k_hsum(int64_t len, int S,
     if (wave == 0 && e < len) {
         double t = part[0][lane];
 #pragma unroll
-        for (int w = 1; w < kHsumWaves; ++w) t += part[w][lane];
+        for (int w = 1; w < kSumWaves; ++w) t += part[w][lane];
         Hsum[e] = t;
     }
-}
-
-// DS[A][B][c] = sum over the tiles t of atom A of Dpart[t][B][c] (tile order).
-__global__ __launch_bounds__(256) void k_dsum(int32_t n_atom, const int32_t *__restrict__ tile_first,
-                                              const double *__restrict__ Dpart,
-                                              double *__restrict__ DS) {
-    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (k >= (int64_t)n_atom * n_atom * 9) return;
-    const int A = (int)(k / (9LL * n_atom));
-    const int rem = (int)(k - (int64_t)A * 9 * n_atom);   // B * 9 + c
-    // the own-atom slot (B = A) is never formed by the grid pass (its terms
-    // follow from translational invariance in k_finish): zero, not read
-    if (rem / 9 == A) {
-        DS[k] = 0.0;
-        return;
-    }
-    double v = 0.0;
-#pragma unroll 8
-    for (int t = tile_first[A]; t < tile_first[A + 1]; ++t) v += Dpart[(int64_t)t * n_atom * 9 + rem];
-    DS[k] = v;
 }
 
 __device__ __forceinline__ int sym_index(int a, int b) {
@@ -582,12 +583,12 @@ hipError_t launch_assemble(vv10_plan *p, const vv10_nuclear_outputs &out, bool w
     }
     {
         const int64_t len = (int64_t)(ws.Pp + 1) * ws.Pp;
-        k_hsum<<<(unsigned)((len + 63) / 64), 64 * kHsumWaves, 0, p->stream>>>(
-            len, ws.gsplit, ws.Hpart, weighted ? ws.gsplit : 0, ww.Hpart, ws.Hsum);
+        const int64_t nds = (int64_t)p->n_atom * p->n_atom * 9;
+        const int nh = (int)((len + 63) / 64), nd = (int)((nds + 64 * kSumWaves - 1) / (64 * kSumWaves));
+        k_sums<<<(unsigned)(nh + nd), 64 * kSumWaves, 0, p->stream>>>(
+            len, ws.gsplit, ws.Hpart, weighted ? ws.gsplit : 0, ww.Hpart, ws.Hsum, nh, p->n_atom,
+            p->d_tile_first, ws.Dpart, ws.DS);
     }
-    const int64_t nds = (int64_t)p->n_atom * p->n_atom * 9;
-    k_dsum<<<(unsigned)((nds + 255) / 256), 256, 0, p->stream>>>(p->n_atom, p->d_tile_first,
-                                                                 ws.Dpart, ws.DS);
     const int64_t nt = (int64_t)ws.P * ws.P + ws.P;
     k_finish<<<(unsigned)((nt + 255) / 256), 256, 0, p->stream>>>(p->n_atom, ws.P, ws.Pp, ws.Hsum,
                                                                   ws.DS, hess, grad);

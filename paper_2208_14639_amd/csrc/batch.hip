@@ -100,8 +100,7 @@ hipError_t enqueue_batch(vv10_batch *b, const double *rho_x, const double *grad_
         p->stream = b->side[m % K];
         const vv10_nuclear_outputs out = {hess + b->h_off[m], nullptr, nullptr, nullptr, nullptr,
                                           nullptr, nullptr, nullptr, nullptr, nullptr};
-        e = vv10::launch_sum_groups(p, 0);
-        if (e == hipSuccess) e = vv10::launch_potential(p, energy + m, nullptr, nullptr);
+        e = vv10::launch_potential(p, vv10::group_parts(p), energy + m, nullptr, nullptr);
         if (e == hipSuccess) e = vv10::launch_assemble(p, out, false);
     }
     for (int k = 0; k < K && e == hipSuccess; ++k) {

@@ -19,21 +19,6 @@ __global__ __launch_bounds__(64 * kGridWaves) __attribute__((amdgpu_waves_per_eu
                                Pd, Z, Ze, Dpart, Ipart, blockIdx.x, blockIdx.y, lds);
 }
 
-// I[k][i] = sum over atom groups of Ipart[grp][k][i] (group order),
-// k0 <= k < nrows, i < n.
-__global__ __launch_bounds__(256) void k_sum_groups(int64_t n, int64_t npad, int G, int nrows, int k0,
-                                                    const double *__restrict__ Ipart,
-                                                    double *__restrict__ I) {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x + (int64_t)k0 * n;
-    if (e >= (int64_t)nrows * n) return;
-    const int k = (int)(e / n);
-    const int64_t i = e - (int64_t)k * n;
-    double a = 0.0;
-#pragma unroll 8
-    for (int gidx = 0; gidx < G; ++gidx) a += Ipart[((int64_t)gidx * nrows + k) * npad + i];
-    I[k * npad + i] = a;
-}
-
 // Gradient pass (Section II.A): the pair integrals E, U, W of every outer
 // point (over all j) and, per tile t of outer points (atom A) and atom
 // B > A, Gpart[t][B][a] = sum_{i in t} a_i E^{Bgr}_{i,a} (zero for B <= A),
@@ -180,31 +165,14 @@ void grid_grad_mode(vv10_plan *p) {
 }
 
 hipError_t launch_grid_terms(vv10_plan *p, double *Ze, int ints_from) {
-    if (ints_from >= NI) {
-        grid_terms_mode<false>(p, Ze);
-        return hipGetLastError();
-    }
-    grid_terms_mode<true>(p, Ze);
-    return launch_sum_groups(p, ints_from);
-}
-
-hipError_t launch_sum_groups(vv10_plan *p, int ints_from) {
-    const int64_t tot = (int64_t)(NI - ints_from) * p->n;
-    if (tot <= 0) return hipSuccess;
-    k_sum_groups<<<(unsigned)((tot + 255) / 256), 256, 0, p->stream>>>(
-        p->n, p->npad, p->ws.bgroups, NI, ints_from, p->ws.Igrp, p->I);
+    if (ints_from >= NI) grid_terms_mode<false>(p, Ze);
+    else grid_terms_mode<true>(p, Ze);
     return hipGetLastError();
 }
 
 hipError_t launch_grid_grad(vv10_plan *p, bool ints) {
-    if (!ints) {
-        grid_grad_mode<false>(p);
-        return hipGetLastError();
-    }
-    grid_grad_mode<true>(p);
-    const int64_t tot = (int64_t)3 * p->n;
-    k_sum_groups<<<(unsigned)((tot + 255) / 256), 256, 0, p->stream>>>(p->n, p->npad, p->gw.bgroups,
-                                                                       3, 0, p->gw.Igrp, p->I);
+    if (ints) grid_grad_mode<true>(p);
+    else grid_grad_mode<false>(p);
     return hipGetLastError();
 }
 

@@ -136,12 +136,58 @@ void dev_release_cached() {
     (void)hipSetDevice(cur);
 }
 
+namespace {
+
+struct Pinned {
+    void *ptr;
+    size_t cap;
+};
+std::mutex g_pinned_mu;
+std::vector<Pinned> g_pinned;
+
+}  // namespace
+
+hipError_t pinned_take(void **ptr, size_t *cap) {
+    {
+        std::lock_guard<std::mutex> lk(g_pinned_mu);
+        for (size_t k = 0; k < g_pinned.size(); ++k)
+            if (g_pinned[k].cap >= *cap) {
+                *ptr = g_pinned[k].ptr;
+                *cap = g_pinned[k].cap;
+                g_pinned.erase(g_pinned.begin() + k);
+                return hipSuccess;
+            }
+    }
+    *cap = (*cap + 4095) / 4096 * 4096;
+    return hipHostMalloc(ptr, *cap, hipHostMallocPortable | hipHostMallocCoherent);
+}
+
+void pinned_give(void *ptr, size_t cap) {
+    {
+        std::lock_guard<std::mutex> lk(g_pinned_mu);
+        if (g_pinned.size() < kPinnedKept) {
+            g_pinned.push_back({ptr, cap});
+            return;
+        }
+    }
+    (void)hipHostFree(ptr);
+}
+
+void pinned_release() {
+    std::lock_guard<std::mutex> lk(g_pinned_mu);
+    for (const Pinned &b : g_pinned) (void)hipHostFree(b.ptr);
+    g_pinned.clear();
+}
+
 }  // namespace vv10
 
 extern "C" {
 
 size_t vv10_cached_bytes(void) { return vv10::dev_cached_bytes(); }
 
-void vv10_release_cached(void) { vv10::dev_release_cached(); }
+void vv10_release_cached(void) {
+    vv10::dev_release_cached();
+    vv10::pinned_release();
+}
 
 }  // extern "C"

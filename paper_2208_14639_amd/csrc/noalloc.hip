@@ -136,11 +136,12 @@ extern "C" vv10_status vv10_energy_potential_noalloc(
     p.flag = reinterpret_cast<int32_t *>(base + L.flag);
 
     // every scratch word a kernel reads is written earlier in this call
-    // (k_fill_i32 sets the flag; k_prep every padded point; the pair pass
-    // every partial), so nothing carries over from a previous call
+    // (k_coord_partials sets the flag and the energy counter; k_prep every
+    // padded point; the pair pass every partial), so nothing carries over from a previous call
     e = vv10::launch_prepare(&p, coords, weights, atom_of, rho, grad_rho);
-    if (e == hipSuccess) e = vv10::launch_pair_integrals(&p, false, p.I);
-    if (e == hipSuccess) e = vv10::launch_potential(&p, energy, f_rho, f_gamma, p.flag);
+    vv10::IntegralParts parts;
+    if (e == hipSuccess) e = vv10::launch_pair_integrals(&p, &parts);
+    if (e == hipSuccess) e = vv10::launch_potential(&p, parts, energy, f_rho, f_gamma, p.flag);
     if (e == hipSuccess && status) {
         k_status<<<1, 1, 0, stream>>>(p.flag, status);
         e = hipGetLastError();

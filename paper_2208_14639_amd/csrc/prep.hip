@@ -14,17 +14,19 @@ namespace {
 
 constexpr double kPi = 3.141592653589793238462643383279502884;
 
-// Fill an int32 array with a value (used instead of a memset so that the
-// launch sequence contains kernels only).
-__global__ void k_fill_i32(int32_t *a, int64_t n, int32_t v) {
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i < n) a[i] = v;
-}
+constexpr int kCoordBlocks = 64;
 
-// Partial sums of the coordinates for the centroid shift (fixed order).
+// Partial sums of the coordinates for the centroid shift (fixed order).  Also
+// clears the energy reduction's counter and, with flag, sets the validation
+// words (flag 0, no segment starts): kernels only, no memset, in the sequence.
 __global__ __launch_bounds__(256) void k_coord_partials(int64_t n, const double *coords,
-                                                        double *part) {
+                                                        double *part, uint32_t *counter,
+                                                        int32_t *flag, int32_t n_flag) {
     __shared__ double s[3][256];
+    const int32_t t0 = blockIdx.x * 256 + threadIdx.x;
+    if (t0 == 0) *counter = 0;
+    if (flag)
+        for (int32_t i = t0; i < n_flag; i += kCoordBlocks * 256) flag[i] = i == 0 ? 0 : -1;
     double a[3] = {0, 0, 0};
     for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
         for (int k = 0; k < 3; ++k) a[k] += coords[3 * i + k];
@@ -38,25 +40,34 @@ __global__ __launch_bounds__(256) void k_coord_partials(int64_t n, const double 
     if (threadIdx.x < 3) part[blockIdx.x * 3 + threadIdx.x] = s[threadIdx.x][0];
 }
 
-__global__ void k_coord_centroid(int nblk, int64_t n, double *part) {
-    if (threadIdx.x < 3) {
-        double t = 0.0;
-#pragma unroll 16   // loads in flight together; the sum stays in block order
-        for (int b = 0; b < nblk; ++b) t += part[3 * b + threadIdx.x];
-        part[3 * nblk + threadIdx.x] = t / (double)n;
-    }
-}
-
 // One thread per padded point.  Pad rows get benign values (omega = kappa = 1,
-// zero weight) so that they contribute exact zeros to every sum.
+// zero weight) so that they contribute exact zeros to every sum.  Every
+// workgroup adds up the centroid from the partials (64 LDS reads, in order)
+// rather than a launch of its own: latency is all that either costs.  Two
+// launches before the host's wait in place of five and a copy: the energy call
+// of one water (N 1500, FP64) 80 -> 63 us with k_potential's fused sums.
+// HOST: the validation words are host memory, which takes plain stores only:
+// one word per kind of fault at flag[n_atom + 1], ..., [n_atom + 3] for bits
+// 1, 2, 4; else the bits are combined into flag[0].
+template <bool HOST>
 __global__ __launch_bounds__(256) void k_prep(
     int64_t n, int64_t npad, int32_t n_atom, double b, double C,
     const double *__restrict__ coords, const double *__restrict__ w,
     const int32_t *__restrict__ atom_of, const double *__restrict__ rho,
-    const double *__restrict__ grad, const double *__restrict__ centroid,
+    const double *__restrict__ grad, const double *__restrict__ part,
     double4 *__restrict__ P0, double4 *__restrict__ P1, float4 *__restrict__ P0f,
     float4 *__restrict__ P1f, double *__restrict__ F, int32_t *__restrict__ ao_out,
     int32_t *__restrict__ flag) {
+    __shared__ double sp[3 * kCoordBlocks], centroid[3];
+    if (threadIdx.x < 3 * kCoordBlocks) sp[threadIdx.x] = part[threadIdx.x];
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        double t = 0.0;
+#pragma unroll 16
+        for (int b = 0; b < kCoordBlocks; ++b) t += sp[3 * b + threadIdx.x];
+        centroid[threadIdx.x] = t / (double)n;
+    }
+    __syncthreads();
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= npad) return;
     if (i >= n) {
@@ -81,7 +92,12 @@ __global__ __launch_bounds__(256) void k_prep(
     if (A < 0 || A >= n_atom) bad |= 4;
     else if (i > 0 && atom_of[i - 1] > A) bad |= 2;
     if (bad) {
-        atomicOr(flag, bad);
+        if (!HOST) {
+            atomicOr(flag, bad);
+        } else {
+            for (int k = 0; k < 3; ++k)
+                if (bad >> k & 1) flag[n_atom + 1 + k] = 1;
+        }
         return;
     }
     // first point of atom A records the segment start
@@ -291,15 +307,15 @@ __global__ __launch_bounds__(256) void k_mask(int64_t nblk, int32_t Pp, int32_t 
 
 hipError_t launch_prepare(vv10_plan *p, const double *coords, const double *w,
                           const int32_t *atom_of, const double *rho,
-                          const double *grad_rho) {
-    const int nb_part = 64;
-    k_fill_i32<<<(p->n_atom + 2 + 255) / 256, 256, 0, p->stream>>>(p->flag, p->n_atom + 2, -1);
-    k_fill_i32<<<1, 1, 0, p->stream>>>(p->flag, 1, 0);
-    k_coord_partials<<<nb_part, 256, 0, p->stream>>>(p->n, coords, p->red);
-    k_coord_centroid<<<1, 64, 0, p->stream>>>(nb_part, p->n, p->red);
-    k_prep<<<(unsigned)(p->npad / 256), 256, 0, p->stream>>>(
-        p->n, p->npad, p->n_atom, p->prm.b, p->prm.C, coords, w, atom_of, rho, grad_rho,
-        p->red + 3 * nb_part, p->P0, p->P1, p->P0f, p->P1f, p->F, p->atom_of, p->flag);
+                          const double *grad_rho, int32_t *host_flag) {
+    uint32_t *counter = energy_counter(p);
+    k_coord_partials<<<kCoordBlocks, 256, 0, p->stream>>>(p->n, coords, p->red, counter,
+                                                          host_flag ? nullptr : p->flag,
+                                                          p->n_atom + 2);
+    auto prep = host_flag ? k_prep<true> : k_prep<false>;
+    prep<<<(unsigned)(p->npad / 256), 256, 0, p->stream>>>(
+        p->n, p->npad, p->n_atom, p->prm.b, p->prm.C, coords, w, atom_of, rho, grad_rho, p->red,
+        p->P0, p->P1, p->P0f, p->P1f, p->F, p->atom_of, host_flag ? host_flag : p->flag);
     return hipGetLastError();
 }
 

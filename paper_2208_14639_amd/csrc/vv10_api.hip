@@ -188,7 +188,6 @@ void free_plan(vv10_plan *p) {
     dfree(p->atom_of);
     dfree(p->d_meta);
     dfree(p->red);
-    dfree(p->flag);
     delete p;
 }
 
@@ -444,35 +443,46 @@ vv10_status vv10_prepare(const vv10_params *params, int64_t n_grid, int32_t n_at
         e = dalloc(&p->Ipart, (size_t)vv10::pair_splits(npad) * vv10::NI * npad);
     if (e == hipSuccess) e = dalloc(&p->atom_of, npad);
     if (e == hipSuccess) e = dalloc(&p->red, vv10::reduction_doubles(npad));
-    if (e == hipSuccess) e = dalloc(&p->flag, (size_t)n_atom + 2);
     if (e != hipSuccess) {
         vv10_status st = hip_status(e);
         (void)hipGetLastError();
         free_plan(p);
         return st;
     }
-    e = vv10::launch_prepare(p, coords, weights, atom_of, rho, grad_rho);
-    std::vector<int32_t> flag((size_t)n_atom + 2);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(flag.data(), p->flag, flag.size() * sizeof(int32_t),
-                           hipMemcpyDeviceToHost, stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
+    // the validation words and segment starts come straight into page-locked
+    // host memory: no fill before and no copy after the kernels
+    void *words = nullptr;
+    size_t cap = ((size_t)n_atom + 4) * sizeof(int32_t);
+    e = vv10::pinned_take(&words, &cap);
     if (e != hipSuccess) {
+        vv10_status st = hip_status(e);
         (void)hipGetLastError();
         free_plan(p);
-        return VV10_E_HIP;
+        return st;
     }
-    if (flag[0] != 0) {
+    int32_t *flag = static_cast<int32_t *>(words);
+    std::fill_n(flag, (size_t)n_atom + 4, -1);
+    flag[0] = flag[n_atom + 1] = flag[n_atom + 2] = flag[n_atom + 3] = 0;
+    e = vv10::launch_prepare(p, coords, weights, atom_of, rho, grad_rho, flag);
+    if (e == hipSuccess) e = hipStreamSynchronize(stream);
+    const int32_t *fault = flag + n_atom + 1;   // density, order, atom index
+    vv10_status st = e != hipSuccess ? VV10_E_HIP
+                     : fault[2]      ? VV10_E_ARG
+                     : fault[0]      ? VV10_E_DENSITY
+                     : fault[1]      ? VV10_E_GRID_ORDER
+                                     : VV10_OK;
+    p->seg.assign((size_t)n_atom + 1, 0);
+    if (st == VV10_OK) std::copy_n(flag + 1, n_atom, p->seg.begin());
+    vv10::pinned_give(words, cap);
+    if (st != VV10_OK) {
+        (void)hipGetLastError();
         free_plan(p);
-        if (flag[0] & 4) return VV10_E_ARG;
-        if (flag[0] & 1) return VV10_E_DENSITY;
-        return VV10_E_GRID_ORDER;
+        return st;
     }
     // atom segments (empty atoms get zero-length segments)
-    p->seg.assign((size_t)n_atom + 1, 0);
     p->seg[n_atom] = n_grid;
     for (int32_t A = n_atom - 1; A >= 0; --A)
-        p->seg[A] = flag[1 + A] >= 0 ? flag[1 + A] : p->seg[A + 1];
+        if (p->seg[A] < 0) p->seg[A] = p->seg[A + 1];
     // grid-term tiles: kGridTile consecutive points of one atom
     p->tile_first.assign((size_t)n_atom + 1, 0);
     for (int32_t A = 0; A < n_atom; ++A) {
@@ -527,12 +537,13 @@ vv10_status vv10_energy_potential(vv10_plan *p, double *energy, double *f_rho, d
     // nuclear-terms call adds A, B, C in its grid pass, which shares the pair
     // arithmetic)
     hipError_t e = hipSuccess;
+    vv10::IntegralParts parts;
     if (p->ints_level < 3) {
-        e = stage(p, VV10_STAGE_PAIR, [&] { return vv10::launch_pair_integrals(p, false, p->I); });
+        e = stage(p, VV10_STAGE_PAIR, [&] { return vv10::launch_pair_integrals(p, &parts); });
         if (e == hipSuccess) p->ints_level = 3;
     }
     if (e == hipSuccess)
-        e = stage(p, VV10_STAGE_POTENTIAL, [&] { return vv10::launch_potential(p, energy, f_rho, f_gamma); });
+        e = stage(p, VV10_STAGE_POTENTIAL, [&] { return vv10::launch_potential(p, parts, energy, f_rho, f_gamma); });
     if (e != hipSuccess) {
         p->failed = true;
         (void)hipGetLastError();
@@ -572,7 +583,8 @@ vv10_status vv10_nuclear_terms(vv10_plan *p, int32_t n_pert, const double *rho_x
     if (e == hipSuccess) p->ints_level = 6;
     if (e == hipSuccess)
         e = stage(p, VV10_STAGE_POTENTIAL, [&] {
-            return vv10::launch_potential(p, out->energy, out->f_rho, out->f_gamma);
+            return vv10::launch_potential(p, vv10::group_parts(p, ints_from), out->energy,
+                                          out->f_rho, out->f_gamma);
         });
     if (e == hipSuccess && out->w_coef)
         e = hipMemcpyAsync(out->w_coef, p->F + (size_t)vv10::F_F0 * p->npad,
@@ -637,7 +649,11 @@ vv10_status vv10_gradient(vv10_plan *p, int32_t n_pert, const double *rho_x,
     hipError_t e = stage(p, VV10_STAGE_GRID, [&] { return vv10::launch_grid_grad(p, ints); });
     if (e == hipSuccess && ints) p->ints_level = 3;
     if (e == hipSuccess)
-        e = stage(p, VV10_STAGE_POTENTIAL, [&] { return vv10::launch_potential(p, nullptr, nullptr, nullptr); });
+        e = stage(p, VV10_STAGE_POTENTIAL, [&] {
+            vv10::IntegralParts parts;
+            if (ints) parts = {p->gw.Igrp, p->gw.bgroups, 3, 0, 3};
+            return vv10::launch_potential(p, parts, nullptr, nullptr, nullptr);
+        });
     if (e == hipSuccess)
         e = stage(p, VV10_STAGE_ASSEMBLE, [&] { return vv10::launch_gradient(p, rho_x, grad_rho_x, w_x, grad); });
     if (e != hipSuccess) {
@@ -664,7 +680,7 @@ vv10_status vv10_trial_response(vv10_plan *p, int32_t n_t, const double *rho_t,
     }
     hipError_t e = hipSuccess;
     if (!p->ir_ready) {
-        e = stage(p, VV10_STAGE_PAIR, [&] { return vv10::launch_pair_integrals(p, true, p->Ir); });
+        e = stage(p, VV10_STAGE_PAIR, [&] { return vv10::launch_pair_integrals6(p, p->Ir); });
         if (e == hipSuccess) p->ir_ready = true;
     }
     if (e == hipSuccess)

@@ -127,7 +127,7 @@ struct vv10_plan {
     int64_t *d_seg = nullptr;     // [n_atom + 1]
     int32_t *d_tile_i0 = nullptr, *d_tile_n = nullptr, *d_tile_atom = nullptr, *d_tile_first = nullptr;
     double *red = nullptr;   // reduction scratch
-    int32_t *flag = nullptr; // [1 + n_atom + 1] validation flag and segment starts
+    int32_t *flag = nullptr; // [1 + n_atom + 1] validation flag and segment starts (noalloc calls)
     size_t base_bytes = 0;
 
     // tile overrides (vv10_set_tiles); 0 = automatic
@@ -208,32 +208,58 @@ void dev_free(void *ptr);
 size_t dev_cached_bytes();
 void dev_release_cached();
 
+// Page-locked host memory that the device writes directly (a process-wide pool
+// of at most kPinnedKept idle buffers; the caller gives one back after the work
+// that uses it has completed).  cap: in, the bytes needed; out, the bytes held.
+constexpr size_t kPinnedKept = 16;
+hipError_t pinned_take(void **ptr, size_t *cap);
+void pinned_give(void *ptr, size_t cap);
+
 // j splits of the pair-integral kernel for a padded grid size.
 int pair_splits(int64_t npad);
-// Doubles of a plan's reduction scratch (centroid partials, energy partials).
+// Doubles of a plan's reduction scratch (centroid partials, energy partials;
+// the last holds the energy reduction's counter, which no partial reaches).
 size_t reduction_doubles(int64_t npad);
+inline uint32_t *energy_counter(const vv10_plan *p) {
+    return reinterpret_cast<uint32_t *>(p->red + reduction_doubles(p->npad) - 1);
+}
+
+// Partial pair integrals still to be added into the plan's I[k0 .. k0 + nk):
+// part[(s rows + k) npad + i], s < S in order.  nk is 0, 3 or 6.
+struct IntegralParts {
+    const double *part = nullptr;
+    int32_t S = 0, rows = 0, k0 = 0, nk = 0;
+};
 
 // Kernel launchers (each enqueues on plan->stream and returns hipGetLastError()).
+// The validation words go to host_flag (n_atom + 4 words of pinned host memory
+// that hold 0, then -1 for each atom, then three zeros) or, if null, to p->flag.
 hipError_t launch_prepare(vv10_plan *p, const double *coords, const double *w,
                           const int32_t *atom_of, const double *rho,
-                          const double *grad_rho);
-hipError_t launch_pair_integrals(vv10_plan *p, bool hessian_mode, double *I_out);
+                          const double *grad_rho, int32_t *host_flag = nullptr);
+// E, U, W of every point: into p->I (one split) or partials that
+// launch_potential adds (*parts).
+hipError_t launch_pair_integrals(vv10_plan *p, IntegralParts *parts);
+// All six pair integrals into I_out.
+hipError_t launch_pair_integrals6(vv10_plan *p, double *I_out);
+// Adds the partial integrals, then forms the potential and the energy.
 // valid (device, or null): when *valid != 0 (a failed input validation)
 // nothing is written to energy, f_rho, f_gamma.
-hipError_t launch_potential(vv10_plan *p, double *energy, double *f_rho, double *f_gamma,
-                            const int32_t *valid = nullptr);
+hipError_t launch_potential(vv10_plan *p, const IntegralParts &parts, double *energy,
+                            double *f_rho, double *f_gamma, const int32_t *valid = nullptr);
 // screen: also the block maxima and the contraction mask (ws.bmax etc. allocated).
 hipError_t launch_pert_prep(vv10_plan *p, const Workspace &ws, const double *rho_x,
                             const double *grad_rho_x, bool screen = false);
 // screen: skip the (16-point, 16-column) blocks that ws.mask marks inactive.
 hipError_t launch_contract(vv10_plan *p, const Workspace &ws, bool screen = false);
-// ints_from: the pair integrals I[k] for ints_from <= k < 6 are formed in the
-// same pass and written to p->I (0: all six; 6: none, the plan holds them).
+// ints_from < 6: the pair integrals are formed in the same pass, as one partial
+// per atom group (group_parts; 6: not formed, the plan holds them).
 hipError_t launch_grid_terms(vv10_plan *p, double *Ze, int ints_from = 0);
-// The second half of launch_grid_terms: I[k] for ints_from <= k < 6 from the
-// per-group partials the grid pass left in ws.Igrp.
-hipError_t launch_sum_groups(vv10_plan *p, int ints_from = 0);
-// ints: also E, U, W into p->I (else the plan holds them).
+// The grid pass's partials of I[k], ints_from <= k < 6 (0, 3 or 6).
+inline IntegralParts group_parts(const vv10_plan *p, int ints_from = 0) {
+    return {p->ws.Igrp, p->ws.bgroups, NI, ints_from, NI - ints_from};
+}
+// ints: also E, U, W as partials per atom group in gw.Igrp (else the plan holds them).
 hipError_t launch_grid_grad(vv10_plan *p, bool ints = true);
 hipError_t launch_gradient(vv10_plan *p, const double *rho_x, const double *grad_rho_x,
                            const double *w_x, double *grad);
