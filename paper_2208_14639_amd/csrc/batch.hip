@@ -32,6 +32,7 @@ struct vv10_batch {
     int64_t n_items = 0;                       // contraction items (four waves)
     int64_t n_wide = 0;                        // wide contraction items (split-BF16)
     int64_t n_grid = 0;                        // grid items
+    int32_t max_ncb = 0;                       // column blocks per group over the first list
     int32_t n_blocks = 0;
     int32_t n_wide_blocks = 0;
     int32_t n_grid_blocks = 0;
@@ -87,8 +88,8 @@ hipError_t enqueue_batch(vv10_batch *b, const double *rho_x, const double *grad_
                                                   (int32_t)b->n_wide, b->d_counter + 1,
                                                   b->n_wide_blocks, b->cap);
     if (e == hipSuccess && b->n_items > 0)
-        e = vv10::launch_contract_persistent(b->prec, b->d_mols, b->d_items, (int32_t)b->n_items,
-                                            b->d_counter, b->n_blocks, b->cap);
+        e = vv10::launch_contract_persistent(b->prec, b->max_ncb, b->d_mols, b->d_items,
+                                             (int32_t)b->n_items, b->d_counter, b->n_blocks, b->cap);
     if (e == hipSuccess && b->n_grid > 0)
         e = vv10::launch_grid_persistent(b->prec, b->d_mols, b->d_items + b->n_items + b->n_wide,
                                          (int32_t)b->n_grid, b->d_counter + 2, b->n_grid_blocks,
@@ -197,6 +198,7 @@ vv10_status vv10_batch_create(const vv10_params *params, int32_t n_mol, const in
             // list, i tiles of 128 points (npad is a multiple of 256)
             const bool wide = prec == VV10_MIXED_BF16X3 && ws.ncb >= vv10::kWideMinNcb;
             const int Wc = wide ? 8 : W;
+            if (!wide) b->max_ncb = std::max(b->max_ncb, ws.ncb);
             for (int32_t s = 0; s < ws.jsplit; ++s) {
                 const int64_t jl = std::min<int64_t>(ws.jlen, p->npad - (int64_t)s * ws.jlen);
                 for (int32_t g = 0; g < ws.ngroups; ++g)
@@ -253,7 +255,7 @@ vv10_status vv10_batch_create(const vv10_params *params, int32_t n_mol, const in
             b->ev.push_back(ev);
         }
         if (e == hipSuccess) {
-            int per_cu = vv10::persistent_blocks_per_cu(prec);
+            int per_cu = vv10::persistent_blocks_per_cu(prec, b->max_ncb);
             if (per_cu <= 0) per_cu = 1;
             b->n_blocks = (int32_t)std::min<int64_t>((int64_t)per_cu * b->plans[0]->num_cu,
                                                      std::max<int64_t>(1, b->n_items));

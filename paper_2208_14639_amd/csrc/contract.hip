@@ -786,19 +786,32 @@ auto dispatch_ncb(int ncb, F &&f) -> decltype(f(std::integral_constant<int, 1>{}
 // item writes its own output slab, so the results do not depend on which
 // workgroup ran which item.
 // ---------------------------------------------------------------------------
+// Two forms each: one for every column count that the list may hold, and one for
+// lists of at most kNarrowNcb column blocks (clusters of up to eight waters),
+// whose smaller register allocation (161, 112 and 162 VGPRs for 252, 208 and
+// 190) leaves room for one or two waves more per SIMD.  Two dozen clusters of
+// 1 to 6 waters with 600 points an atom, per run: FP32 7.70 -> 6.70 ms,
+// split-BF16 4.15 -> 4.08 (the clock falls with the waits); a dozen in FP64 6.66
+// -> 6.13 (5.75 with the column quads).  With a limit of four, 16 clusters of up to eight waters took FP32
+// 6.50 ms against 5.78 and split-BF16 3.27 against 3.22.
+constexpr int kNarrowNcb = 5;
 template <int PREC>
 struct PersistentTraits;
 template <>
 struct PersistentTraits<VV10_FP64> {
     static constexpr int kMaxNcb = 8;
-    static constexpr int kSmem = smem_f64<8>();
+    template <int MAX>
+    static constexpr int smem() { return smem_f64<MAX>(); }
     static constexpr int kWaves = 4;
+    static constexpr int kNarrowPerEu = 3;
 };
 template <>
 struct PersistentTraits<VV10_MIXED_FP32> {
     static constexpr int kMaxNcb = 12;
-    static constexpr int kSmem = smem_f32<12>();
+    template <int MAX>
+    static constexpr int smem() { return smem_f32<MAX>(); }
     static constexpr int kWaves = 4;
+    static constexpr int kNarrowPerEu = 4;
 };
 template <>
 struct PersistentTraits<VV10_MIXED_BF16X3> {
@@ -812,16 +825,30 @@ struct PersistentTraits<VV10_MIXED_BF16X3> {
     // waves per SIMD
     static constexpr int kMaxNcb = kWideMinNcb - 1;
     static constexpr int kWaves = 4;
-    static constexpr int kSmem = smem_bf16x3<kWideMinNcb - 1>();
+    template <int MAX>
+    static constexpr int smem() { return smem_bf16x3<MAX>(); }
+    static constexpr int kNarrowPerEu = 3;
 };
 
 template <int PREC, int NCB>
 __device__ __forceinline__ void run_item(const BatchMol &d, const BatchItem &it, char *smem,
                                          char *smem2) {
     if constexpr (PREC == VV10_FP64) {
-        tile_f64<NCB>(d.npad, d.jlen, d.Pp, static_cast<const double4 *>(d.P0),
-                      static_cast<const double4 *>(d.P1), static_cast<const double *>(d.X),
-                      static_cast<double *>(d.Ypart), it.itile, it.grp, it.split, smem);
+        // quads of columns in the last group's last block, as the standalone
+        // kernel (FP64 batch of a dozen clusters of 1 to 6 waters 6.15 -> 5.75 ms)
+        const int left = 3 * d.n_atom - (d.Pp - 16);
+        const bool last = (it.grp + 1) * 16 * NCB == d.Pp && left > 0;
+        const int nq = last ? (left + 3) / 4 : 4;
+        auto go = [&](auto q) __attribute__((always_inline)) {
+            tile_f64<NCB, false, decltype(q)::value>(
+                d.npad, d.jlen, d.Pp, static_cast<const double4 *>(d.P0),
+                static_cast<const double4 *>(d.P1), static_cast<const double *>(d.X),
+                static_cast<double *>(d.Ypart), it.itile, it.grp, it.split, smem);
+        };
+        if (nq == 1) go(std::integral_constant<int, 1>{});
+        else if (nq == 2) go(std::integral_constant<int, 2>{});
+        else if (nq == 3) go(std::integral_constant<int, 3>{});
+        else go(std::integral_constant<int, 4>{});
     } else if constexpr (PREC == VV10_MIXED_FP32) {
         tile_f32<NCB>(d.npad, d.jlen, d.Pp, static_cast<const float4 *>(d.P0),
                       static_cast<const float4 *>(d.P1), static_cast<const float *>(d.X),
@@ -867,13 +894,15 @@ __global__ __launch_bounds__(64 * kGridWaves) __attribute__((amdgpu_waves_per_eu
     }
 }
 
-template <int PREC>
-__global__ __launch_bounds__(64 * PersistentTraits<PREC>::kWaves, 2) void k_contract_persistent(
+template <int PREC, int MAX>
+__global__ __launch_bounds__(64 * PersistentTraits<PREC>::kWaves,
+                             MAX <= kNarrowNcb ? PersistentTraits<PREC>::kNarrowPerEu : 2) void k_contract_persistent(
     const BatchMol *__restrict__ mols, const BatchItem *__restrict__ items, int32_t n_items,
     int32_t *__restrict__ counter) {
-    __shared__ __attribute__((aligned(16))) char smem[PersistentTraits<PREC>::kSmem];
+    constexpr int kSmem = PersistentTraits<PREC>::template smem<MAX>();
+    __shared__ __attribute__((aligned(16))) char smem[kSmem];
     // the second stage buffer of the split-BF16 form (a one-byte dummy otherwise)
-    __shared__ __attribute__((aligned(16))) char smem2[PREC == VV10_MIXED_BF16X3 ? PersistentTraits<PREC>::kSmem : 1];
+    __shared__ __attribute__((aligned(16))) char smem2[PREC == VV10_MIXED_BF16X3 ? kSmem : 1];
     __shared__ int32_t next;
     for (;;) {
         if (threadIdx.x == 0) next = atomicAdd(counter, 1);
@@ -886,7 +915,7 @@ __global__ __launch_bounds__(64 * PersistentTraits<PREC>::kWaves, 2) void k_cont
         switch (d.ncb) {
 #define VV10_CASE(c) \
     case c:          \
-        if constexpr (c <= PersistentTraits<PREC>::kMaxNcb) run_item<PREC, c>(d, it, smem, smem2); \
+        if constexpr (c <= MAX) run_item<PREC, c>(d, it, smem, smem2); \
         break;
             VV10_CASE(1) VV10_CASE(2) VV10_CASE(3) VV10_CASE(4) VV10_CASE(5) VV10_CASE(6)
             VV10_CASE(7) VV10_CASE(8) VV10_CASE(9) VV10_CASE(10) VV10_CASE(11) VV10_CASE(12)
@@ -1325,17 +1354,29 @@ int persistent_waves(vv10_precision prec) {
     return PersistentTraits<VV10_MIXED_BF16X3>::kWaves;
 }
 
-int persistent_blocks_per_cu(vv10_precision prec) {
+namespace {
+
+using PersistentKernel = void (*)(const BatchMol *, const BatchItem *, int32_t, int32_t *);
+
+template <int PREC>
+PersistentKernel persistent_form(int max_ncb) {
+    if (max_ncb <= kNarrowNcb) return k_contract_persistent<PREC, kNarrowNcb>;
+    return k_contract_persistent<PREC, PersistentTraits<PREC>::kMaxNcb>;
+}
+
+PersistentKernel persistent_kernel(vv10_precision prec, int max_ncb) {
+    if (prec == VV10_FP64) return persistent_form<VV10_FP64>(max_ncb);
+    if (prec == VV10_MIXED_FP32) return persistent_form<VV10_MIXED_FP32>(max_ncb);
+    return persistent_form<VV10_MIXED_BF16X3>(max_ncb);
+}
+
+}  // namespace
+
+int persistent_blocks_per_cu(vv10_precision prec, int max_ncb) {
     int nb = 0;
-    hipError_t e;
-    const int nt = 64 * persistent_waves(prec);
-    if (prec == VV10_FP64)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_contract_persistent<VV10_FP64>, nt, 0);
-    else if (prec == VV10_MIXED_FP32)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_contract_persistent<VV10_MIXED_FP32>, nt, 0);
-    else
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_contract_persistent<VV10_MIXED_BF16X3>, nt, 0);
-    if (e != hipSuccess) {
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &nb, reinterpret_cast<const void *>(persistent_kernel(prec, max_ncb)),
+            64 * persistent_waves(prec), 0) != hipSuccess) {
         (void)hipGetLastError();
         return 0;
     }
@@ -1385,17 +1426,12 @@ hipError_t launch_grid_persistent(vv10_precision prec, const BatchMol *mols,
         k_grid_persistent<VV10_MIXED_BF16X3><<<n_blocks, 64 * kGridWaves, 0, stream>>>(mols, items, n_items, counter);
     return hipGetLastError();
 }
-hipError_t launch_contract_persistent(vv10_precision prec, const BatchMol *mols,
+hipError_t launch_contract_persistent(vv10_precision prec, int max_ncb, const BatchMol *mols,
                                       const BatchItem *items, int32_t n_items, int32_t *counter,
                                       int n_blocks, hipStream_t stream) {
     k_zero_counter<<<1, 1, 0, stream>>>(counter);
-    const int nt = 64 * persistent_waves(prec);
-    if (prec == VV10_FP64)
-        k_contract_persistent<VV10_FP64><<<n_blocks, nt, 0, stream>>>(mols, items, n_items, counter);
-    else if (prec == VV10_MIXED_FP32)
-        k_contract_persistent<VV10_MIXED_FP32><<<n_blocks, nt, 0, stream>>>(mols, items, n_items, counter);
-    else
-        k_contract_persistent<VV10_MIXED_BF16X3><<<n_blocks, nt, 0, stream>>>(mols, items, n_items, counter);
+    persistent_kernel(prec, max_ncb)<<<n_blocks, 64 * persistent_waves(prec), 0, stream>>>(
+        mols, items, n_items, counter);
     return hipGetLastError();
 }
 

@@ -183,8 +183,9 @@ struct BatchItem {
     int32_t mol, grp, split, itile;
 };
 int persistent_waves(vv10_precision prec);
-int persistent_blocks_per_cu(vv10_precision prec);
-hipError_t launch_contract_persistent(vv10_precision prec, const BatchMol *mols,
+// max_ncb: the most 16-column blocks per group of any molecule in the list.
+int persistent_blocks_per_cu(vv10_precision prec, int max_ncb);
+hipError_t launch_contract_persistent(vv10_precision prec, int max_ncb, const BatchMol *mols,
                                       const BatchItem *items, int32_t n_items, int32_t *counter,
                                       int n_blocks, hipStream_t stream);
 // Split-BF16 molecules with at least kWideMinNcb column blocks per group run
