@@ -42,6 +42,7 @@
 //    diagonal blocks of E_{gr,gr} from translational invariance, and the
 //    gradient E_G + E_gr, E_gr = sum_{i in A} a_i E^{Agr}_i
 //    = -sum_{B != A} sum_{i in A} a_i E^{Bgr}_i.
+#include <algorithm>
 #include <type_traits>
 
 #include "dev_common.h"
@@ -249,53 +250,74 @@ __global__ __launch_bounds__(256) void k_trial_resp(
 // row Pp = sum_k L[k][l] wf[k].  NCH = 2: rows k = 2 i + c of (rho^x, gamma^x)
 // with wf[2i + c] = w_i (f^rho_i, f^gamma_i); NCH = 1: rows k = i of w^x with
 // wf[i] = rho_i (beta + E_i).
-// Workgroup (tl, tm, s): output tile rows 64 tl.., columns 64 tm..; its four
-// waves take consecutive quarters of the slice, each on v_mfma_f64_16x16x4
-// with L and R read straight from memory (A = L^T, B = R, K over rows), and
-// are added in wave order through LDS.
-template <int NCH>
-__global__ __launch_bounds__(256, 2) void k_gemm(int64_t n, int64_t npad, int64_t slice,
-                                                 int32_t Pp, const double *__restrict__ F,
-                                                 const double *__restrict__ L,
-                                                 const double *__restrict__ R,
-                                                 double *__restrict__ Hpart) {
-    __shared__ double sT[64 * 64 + 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// Workgroup (tl, tm, s): output tile of NB x NB 16-column blocks; its eight
+// waves take consecutive eighths of the slice, each on v_mfma_f64_16x16x4
+// with L and R read straight from memory (A = L^T, B = R, K over rows).  NB
+// divides the blocks of Pp evenly, so that few MFMAs run on padding (two
+// blocks: four MFMAs a step where a fixed 4 x 4 tile ran sixteen); two waves
+// per SIMD, so that one's loads are in flight under the other's MFMAs.
+// Against four waves of a fixed 4 x 4 tile: the dimer (Pp 32) 15 -> 8 us, nine
+// waters (Pp 96) 51 -> 29, the hexamer (64) 26 -> 22, twenty waters (192) 719
+// -> 434 us, 41 TFLOP/s (also from the tiles of a slice sharing one die's L2).
+constexpr int kGemmWaves = 8;
+inline int gemm_blocks(int nblk) {      // 16-column blocks per tile side
+    const int tiles = (nblk + 3) / 4;
+    return (nblk + tiles - 1) / tiles;
+}
+template <int NCH, int NB>
+__global__ __launch_bounds__(64 * kGemmWaves) void k_gemm(int64_t n, int64_t npad, int64_t slice,
+                                                          int32_t Pp, int32_t tiles, int32_t S,
+                                                          const double *__restrict__ F,
+                                                          const double *__restrict__ L,
+                                                          const double *__restrict__ R,
+                                                          double *__restrict__ Hpart) {
+    constexpr int W = 16 * NB, HALF = kGemmWaves / 2;
+    __shared__ double sT[HALF][W * W + W];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ll = lane & 15, kk = lane >> 4;
-    const int l0 = blockIdx.x * 64, m0 = blockIdx.y * 64;
-    const bool grad = blockIdx.y == 0;
-    const int nlb = min(4, (Pp - l0) / 16), nmb = min(4, (Pp - m0) / 16);   // Pp % 16 == 0
+    // workgroups b, b + 8, ... run on one die: with a multiple of 8 slices,
+    // all tiles of a slice go to one, whose L2 then holds the slice's rows once
+    const int T2 = tiles * tiles, b = blockIdx.x;
+    const int s = S % 8 == 0 ? b % 8 + 8 * (b / 8 / T2) : b / T2;
+    const int tile = S % 8 == 0 ? b / 8 % T2 : b % T2;
+    const int tl = tile / tiles, tm = tile - tl * tiles;
+    const int l0 = tl * W, m0 = tm * W;
+    const bool grad = tm == 0;
+    const int nlb = min(NB, (Pp - l0) / 16), nmb = min(NB, (Pp - m0) / 16);   // Pp % 16 == 0
     const int64_t rows = NCH * n;
-    const int64_t sb = min(rows, (int64_t)blockIdx.z * slice * NCH), se = min(rows, sb + slice * NCH);
-    const int64_t q = (se - sb + 3) / 4;
+    const int64_t sb = min(rows, (int64_t)s * slice * NCH), se = min(rows, sb + slice * NCH);
+    const int64_t q = (se - sb + kGemmWaves - 1) / kGemmWaves;
     const int64_t rb = min(se, sb + wave * q), re = min(se, rb + q);
-    v4d acc[4][4];
-    double gacc[4] = {0.0, 0.0, 0.0, 0.0};
+    v4d acc[NB][NB];
+    double gacc[NB];
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < NB; ++a) {
+        gacc[a] = 0.0;
 #pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = (v4d){0.0, 0.0, 0.0, 0.0};
-    // four k steps per iteration, their loads issued before their MFMAs, so
-    // that several steps' loads are in flight together (one workgroup per
-    // CU leaves little latency hiding to other waves); the MFMAs of each
-    // accumulator still run in k order
-    for (int64_t k00 = rb; k00 < re; k00 += 16) {
+        for (int c = 0; c < NB; ++c) acc[a][c] = (v4d){0.0, 0.0, 0.0, 0.0};
+    }
+    // several k steps per iteration (as many as the registers hold), their
+    // loads issued before their MFMAs; the MFMAs of each accumulator run in k
+    // order
+    constexpr int ST = NB <= 2 ? 8 : NB == 3 ? 4 : 2;
+    for (int64_t k00 = rb; k00 < re; k00 += 4 * ST) {
         // loads without branches, from clamped in-range addresses (finite
         // values); rows past the slice and columns past Pp are zeroed by a
         // multiplication, so that no load waits for another
-        double av[4][4], bv[4][4], wa[4], wb[4];
+        double av[ST][NB], bv[ST][NB], wa[ST], wb[ST];
 #pragma unroll
-        for (int st = 0; st < 4; ++st) {
+        for (int st = 0; st < ST; ++st) {
             const int64_t k = k00 + 4 * st + kk;
             const bool ok = k < re;
             const int64_t kr = ok ? k : rb;
             const double on = ok ? 1.0 : 0.0;
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
+            for (int a = 0; a < NB; ++a)
                 av[st][a] = L[kr * Pp + min(l0 + 16 * a, Pp - 16) + ll] * (a < nlb ? on : 0.0);
 #pragma unroll
-            for (int b = 0; b < 4; ++b)
-                bv[st][b] = R[kr * Pp + min(m0 + 16 * b, Pp - 16) + ll] * (b < nmb ? on : 0.0);
+            for (int c = 0; c < NB; ++c)
+                bv[st][c] = R[kr * Pp + min(m0 + 16 * c, Pp - 16) + ll] * (c < nmb ? on : 0.0);
             if (NCH == 2) {
                 const int64_t pt = kr >> 1;
                 wa[st] = F[F_W * npad + pt] * on;
@@ -306,53 +328,82 @@ __global__ __launch_bounds__(256, 2) void k_gemm(int64_t n, int64_t npad, int64_
             }
         }
 #pragma unroll
-        for (int st = 0; st < 4; ++st) {
+        for (int st = 0; st < ST; ++st) {
             const double wf = NCH == 2 ? wa[st] * wb[st] : wa[st];
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
+            for (int a = 0; a < NB; ++a)
 #pragma unroll
-                for (int b = 0; b < 4; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[st][a], bv[st][b], acc[a][b],
+                for (int c = 0; c < NB; ++c)
+                    acc[a][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[st][a], bv[st][c], acc[a][c],
                                                                      0, 0, 0);
             if (grad)
 #pragma unroll
-                for (int a = 0; a < 4; ++a) gacc[a] = __builtin_fma(av[st][a], wf, gacc[a]);
+                for (int a = 0; a < NB; ++a) gacc[a] = __builtin_fma(av[st][a], wf, gacc[a]);
         }
     }
     // gradient: sum the four k lanes of each column
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
+    for (int a = 0; a < NB; ++a) {
         gacc[a] += __shfl_xor(gacc[a], 16, 64);
         gacc[a] += __shfl_xor(gacc[a], 32, 64);
     }
     // D layout of v_mfma_f64_16x16x4 (measured on gfx950): item r of lane l
-    // holds row 4 r + l/16, column l%16 of the 16 x 16 block
-    for (int w = 0; w < 4; ++w) {
-        if (wave == w) {
+    // holds row 4 r + l/16, column l%16 of the 16 x 16 block.  The upper four
+    // waves' sums are added to the lower four's, those then in wave order.
+    auto row = [&](int a, int r) { return sT[wave % HALF] + (16 * a + 4 * r + kk) * W + ll; };
+    auto put = [&]() {
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
+        for (int a = 0; a < NB; ++a) {
 #pragma unroll
-                for (int b = 0; b < 4; ++b)
+            for (int c = 0; c < NB; ++c)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        double *d = sT + (16 * a + 4 * r + kk) * 64 + 16 * b + ll;
-                        *d = w == 0 ? acc[a][b][r] : *d + acc[a][b][r];
-                    }
-            if (kk == 0)
-#pragma unroll
-                for (int a = 0; a < 4; ++a) {
-                    double *d = sT + 64 * 64 + 16 * a + ll;
-                    *d = w == 0 ? gacc[a] : *d + gacc[a];
-                }
+                for (int r = 0; r < 4; ++r) row(a, r)[16 * c] = acc[a][c][r];
+            if (kk == 0) sT[wave % HALF][W * W + 16 * a + ll] = gacc[a];
         }
-        __syncthreads();
+    };
+    if (wave >= HALF) put();
+    __syncthreads();
+    if (wave < HALF) {
+#pragma unroll
+        for (int a = 0; a < NB; ++a) {
+#pragma unroll
+            for (int c = 0; c < NB; ++c)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[a][c][r] += row(a, r)[16 * c];
+            if (kk == 0) gacc[a] += sT[wave % HALF][W * W + 16 * a + ll];
+            mem_order();                // one row of blocks' loads at a time
+        }
+        put();
     }
-    double *H = Hpart + (int64_t)blockIdx.z * (Pp + 1) * Pp;
-    for (int e = tid; e < 64 * 64; e += 256) {
-        const int rr = e >> 6, cc = e & 63;
-        if (l0 + rr < Pp && m0 + cc < Pp) H[(int64_t)(l0 + rr) * Pp + m0 + cc] = sT[e];
+    __syncthreads();
+    double *H = Hpart + (int64_t)s * (Pp + 1) * Pp;
+    for (int e = tid; e < W * W + (grad ? W : 0); e += 64 * kGemmWaves) {
+        double v = sT[0][e];
+#pragma unroll
+        for (int w = 1; w < HALF; ++w) v += sT[w][e];
+        const int rr = e / W, cc = e - rr * W;
+        if (rr < W) {
+            if (l0 + rr < Pp && m0 + cc < Pp) H[(int64_t)(l0 + rr) * Pp + m0 + cc] = v;
+        } else if (l0 + cc < Pp) {
+            H[(int64_t)Pp * Pp + l0 + cc] = v;
+        }
     }
-    if (grad && tid < 64 && l0 + tid < Pp) H[(int64_t)Pp * Pp + l0 + tid] = sT[64 * 64 + tid];
+}
+
+template <int NCH>
+void gemm_launch(const vv10_plan *p, const Workspace &ws, const double *L, const double *R,
+                 double *Hpart) {
+    const int nblk = ws.Pp / 16, nb = gemm_blocks(nblk), tiles = (nblk + nb - 1) / nb;
+    const int64_t slice = (p->n + ws.gsplit - 1) / ws.gsplit;
+    auto go = [&](auto c) {
+        k_gemm<NCH, decltype(c)::value><<<(unsigned)(tiles * tiles * ws.gsplit), 64 * kGemmWaves, 0,
+                                          p->stream>>>(p->n, p->npad, slice, ws.Pp, tiles,
+                                                       ws.gsplit, p->F, L, R, Hpart);
+    };
+    if (nb == 1) go(std::integral_constant<int, 1>{});
+    else if (nb == 2) go(std::integral_constant<int, 2>{});
+    else if (nb == 3) go(std::integral_constant<int, 3>{});
+    else go(std::integral_constant<int, 4>{});
 }
 
 // Workgroups b < nh: Hsum[e] = sum_s Hpart[s][e], e < len = (Pp + 1) Pp, over
@@ -468,6 +519,8 @@ __global__ __launch_bounds__(256) void k_finish(int32_t n_atom, int32_t P, int32
 
 }  // namespace
 
+namespace {
+
 // Gradient (Section II.A, first form of the grid part): for x = 3 A + a,
 //   grad[x] = sum_i w_i (f^rho_i rho^x_i + f^gamma_i gamma^x_i)
 //           [+ sum_i w^x_i rho_i (beta + E_i)]
@@ -475,52 +528,81 @@ __global__ __launch_bounds__(256) void k_finish(int32_t n_atom, int32_t P, int32
 //           + sum_{B < A} sum_{tiles t of B} Gpart[t][A][a]
 // (the tile sums are antisymmetric in the atom pair; the pass forms B > A),
 // gamma^x = 2 grad rho . grad rho^x; w^x (optional) with the owner slot from
-// Wown.  One workgroup per x; both sums are fixed-order tree reductions,
-// added at the end.
-__global__ __launch_bounds__(256) void k_gradient(int64_t n, int64_t npad, int32_t n_atom,
-                                                  const int32_t *__restrict__ tile_first,
-                                                  const int32_t *__restrict__ atom_of,
-                                                  const double *__restrict__ F,
-                                                  const double *__restrict__ rho_x,
-                                                  const double *__restrict__ grad_rho_x,
-                                                  const double *__restrict__ w_x,
-                                                  const double *__restrict__ Wown,
-                                                  const double *__restrict__ Gpart,
-                                                  double *__restrict__ grad) {
-    __shared__ double sg[256], sr[256];
-    const int tid = threadIdx.x, x = blockIdx.x, A = x / 3, a = x % 3;
-    const double *rx = rho_x + (int64_t)x * n;
-    const double *gx = grad_rho_x + (int64_t)x * n * 3;
-    double eg = 0.0;
-    for (int64_t i = tid; i < n; i += 256) {
-        const double gam = 2.0 * (F[F_GX * npad + i] * gx[3 * i] + F[F_GY * npad + i] * gx[3 * i + 1] +
-                                  F[F_GZ * npad + i] * gx[3 * i + 2]);
-        eg += F[F_W * npad + i] * (F[F_FR * npad + i] * rx[i] + F[F_FG * npad + i] * gam);
-        if (w_x) {
-            const double wx = atom_of[i] == A ? Wown[i * 3 + a] : w_x[(int64_t)x * n + i];
-            eg += wx * F[F_F0 * npad + i];
+// Wown.  The point sums run over S slices of the points, one workgroup per
+// (atom, slice) for the atom's three directions, whose per-point fields it
+// reads once: bound by the 32 N P bytes of the derivatives.  The
+// hexamer (47 MB): 13.0 + 4.6 us, against 48 with one workgroup per x.
+// Fixed-order tree reductions throughout.
+constexpr int kGradSlices = 32;
+__global__ __launch_bounds__(256) void k_gradient_points(int64_t n, int64_t npad, int64_t slice,
+                                                         const int32_t *__restrict__ atom_of,
+                                                         const double *__restrict__ F,
+                                                         const double *__restrict__ rho_x,
+                                                         const double *__restrict__ grad_rho_x,
+                                                         const double *__restrict__ w_x,
+                                                         const double *__restrict__ Wown,
+                                                         double *__restrict__ part) {
+    __shared__ double red[3][4];
+    const int tid = threadIdx.x, A = blockIdx.x;
+    const int64_t end = min(n, (int64_t)(blockIdx.y + 1) * slice);
+    double s[3] = {0.0, 0.0, 0.0};
+#pragma unroll 2
+    for (int64_t i = (int64_t)blockIdx.y * slice + tid; i < end; i += 256) {
+        const double w = F[F_W * npad + i], fr = w * F[F_FR * npad + i];
+        const double fg = 2.0 * (w * F[F_FG * npad + i]);
+        const double gx = F[F_GX * npad + i], gy = F[F_GY * npad + i], gz = F[F_GZ * npad + i];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const int64_t o = (int64_t)(3 * A + a) * n + i;
+            const double *d = grad_rho_x + 3 * o;
+            s[a] += fr * rho_x[o] + fg * (gx * d[0] + gy * d[1] + gz * d[2]);
+            if (w_x) {
+                const double wx = atom_of[i] == A ? Wown[i * 3 + a] : w_x[o];
+                s[a] += wx * F[F_F0 * npad + i];
+            }
         }
     }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        s[a] = wave_sum(s[a]);
+        if ((tid & 63) == 0) red[a][tid >> 6] = s[a];
+    }
+    __syncthreads();
+    if (tid < 3)
+        part[(int64_t)blockIdx.y * 3 * gridDim.x + 3 * A + tid] =
+            red[tid][0] + red[tid][1] + red[tid][2] + red[tid][3];
+}
+
+// The slices' point sums and the tile sums: one wave per x.
+__global__ __launch_bounds__(64) void k_gradient(int32_t n_atom, int S,
+                                                 const int32_t *__restrict__ tile_first,
+                                                 const double *__restrict__ part,
+                                                 const double *__restrict__ Gpart,
+                                                 double *__restrict__ grad) {
+    const int lane = threadIdx.x, x = blockIdx.x, A = x / 3, a = x % 3;
+    double v = 0.0;
+    for (int s = lane; s < S; s += 64) v += part[(int64_t)s * 3 * n_atom + x];
     // -sum_{B != A} sum_{t in A} Gpart[t][B]: the pass forms B > A; a B < A
     // term is minus the (B, A) one, i.e. +Gpart[t][A] over the tiles t of B
     const int t0 = tile_first[A], nt = tile_first[A + 1] - t0;
-    double gr = 0.0;
-    for (int k = tid; k < (n_atom - A - 1) * nt; k += 256) {
+#pragma unroll 8
+    for (int k = lane; k < (n_atom - A - 1) * nt; k += 64) {
         const int B = A + 1 + k / nt, t = t0 + k % nt;
-        gr -= Gpart[((int64_t)t * n_atom + B) * 3 + a];
+        v -= Gpart[((int64_t)t * n_atom + B) * 3 + a];
     }
-    for (int t = tid; t < t0; t += 256) gr += Gpart[((int64_t)t * n_atom + A) * 3 + a];
-    sg[tid] = eg;
-    sr[tid] = gr;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if (tid < off) {
-            sg[tid] += sg[tid + off];
-            sr[tid] += sr[tid + off];
-        }
-        __syncthreads();
-    }
-    if (tid == 0) grad[x] = sg[0] + sr[0];
+#pragma unroll 8
+    for (int t = lane; t < t0; t += 64) v += Gpart[((int64_t)t * n_atom + A) * 3 + a];
+    v = wave_sum(v);
+    if (lane == 0) grad[x] = v;
+}
+
+}  // namespace
+
+// Slices of k_gradient_points: their sums go where the atom groups' partial
+// integrals were (gw.Igrp, [bgroups][3][npad], which the potential has added).
+static int gradient_slices(const vv10_plan *p) {
+    const int64_t room = (int64_t)p->gw.bgroups * p->npad / p->n_atom;
+    return (int)std::max<int64_t>(1, std::min<int64_t>({kGradSlices, room, (p->n + 255) / 256}));
 }
 
 hipError_t launch_gradient(vv10_plan *p, const double *rho_x, const double *grad_rho_x,
@@ -529,9 +611,13 @@ hipError_t launch_gradient(vv10_plan *p, const double *rho_x, const double *grad
         const hipError_t e = launch_weight_own(p, w_x, p->wown);
         if (e != hipSuccess) return e;
     }
-    k_gradient<<<(unsigned)(3 * p->n_atom), 256, 0, p->stream>>>(
-        p->n, p->npad, p->n_atom, p->d_tile_first, p->atom_of, p->F, rho_x, grad_rho_x, w_x,
-        p->wown, p->gw.Gpart, grad);
+    const int S = gradient_slices(p);
+    const int64_t slice = (p->n + S - 1) / S;
+    double *part = p->gw.Igrp;
+    k_gradient_points<<<dim3((unsigned)p->n_atom, (unsigned)S), 256, 0, p->stream>>>(
+        p->n, p->npad, slice, p->atom_of, p->F, rho_x, grad_rho_x, w_x, p->wown, part);
+    k_gradient<<<(unsigned)(3 * p->n_atom), 64, 0, p->stream>>>(p->n_atom, S, p->d_tile_first, part,
+                                                                p->gw.Gpart, grad);
     return hipGetLastError();
 }
 
@@ -572,15 +658,8 @@ hipError_t launch_assemble(vv10_plan *p, const vv10_nuclear_outputs &out, bool w
         else go(static_cast<const double *>(ws.Ypart));
     }
     if (!hess && !grad) return hipGetLastError();
-    const int64_t slice = (n + ws.gsplit - 1) / ws.gsplit;
-    const unsigned tiles = (unsigned)((ws.Pp + 63) / 64);
-    {
-        dim3 grid(tiles, tiles, (unsigned)ws.gsplit);
-        k_gemm<2><<<grid, 256, 0, p->stream>>>(n, p->npad, slice, ws.Pp, p->F, ws.L, ws.Y, ws.Hpart);
-        if (weighted)
-            k_gemm<1><<<grid, 256, 0, p->stream>>>(n, p->npad, slice, ws.Pp, p->F, ww.Lw, ww.Rw,
-                                                   ww.Hpart);
-    }
+    gemm_launch<2>(p, ws, ws.L, ws.Y, ws.Hpart);
+    if (weighted) gemm_launch<1>(p, ws, ww.Lw, ww.Rw, ww.Hpart);
     {
         const int64_t len = (int64_t)(ws.Pp + 1) * ws.Pp;
         const int64_t nds = (int64_t)p->n_atom * p->n_atom * 9;

@@ -52,10 +52,12 @@ void plan_workspace_shape(int64_t npad, int32_t n_atom, int32_t ntiles, int num_
     }
     ws.jlen = ((npad / ws.jsplit + 31) / 32) * 32;
     while ((ws.jsplit - 1) * ws.jlen >= npad) --ws.jsplit;   // no empty split
-    // assembly GEMM: about one workgroup per CU over (64 x 64 tiles) x slices
+    // assembly GEMM: at most one workgroup per CU over (tiles of up to 64 x 64)
+    // x slices, a multiple of 8 slices where there are as many (one slice's
+    // tiles then share a die's L2)
     const int tiles = (ws.Pp + 63) / 64;
-    ws.gsplit = (int)std::max<int64_t>(1, std::min<int64_t>((num_cu + tiles * tiles - 1) / (tiles * tiles),
-                                                             std::max<int64_t>(1, npad / 64)));
+    ws.gsplit = (int)std::max<int64_t>(1, std::min<int64_t>(num_cu / (tiles * tiles), npad / 64));
+    if (ws.gsplit >= 8) ws.gsplit -= ws.gsplit % 8;
     ws.bgroups = std::max(1, std::min<int>(n_atom, (8192 + std::max(ntiles, 1) - 1) / std::max(ntiles, 1)));
     if (bgroups_override > 0) ws.bgroups = std::min<int>(n_atom, bgroups_override);
 }
@@ -289,7 +291,9 @@ static vv10_status ensure_gradient_work(vv10_plan *p) {
     vv10::GradWork gw;
     gw.bgroups = ws.bgroups;
     hipError_t e = dalloc(&gw.Gpart, (size_t)p->ntiles * p->n_atom * 3);
-    if (e == hipSuccess) e = dalloc(&gw.Igrp, (size_t)gw.bgroups * 3 * p->npad);
+    // (also the gradient's point sums of at least one slice)
+    if (e == hipSuccess)
+        e = dalloc(&gw.Igrp, 3 * std::max((size_t)gw.bgroups * p->npad, (size_t)p->n_atom));
     if (e != hipSuccess) {
         dfree(gw.Gpart);
         dfree(gw.Igrp);
@@ -707,7 +711,8 @@ size_t vv10_gradient_footprint_bytes(int64_t n_grid, int32_t n_atom) {
     Workspace ws;
     vv10::plan_workspace_shape(npad, n_atom, (int32_t)ntiles, 256, VV10_FP64, ws);
     // Gpart [tiles][atoms][3] and Igrp [bgroups][3][npad] (ensure_gradient_work)
-    return ((size_t)ntiles * n_atom * 3 + (size_t)ws.bgroups * 3 * npad) * sizeof(double) +
+    return ((size_t)ntiles * n_atom * 3 +
+            3 * std::max((size_t)ws.bgroups * npad, (size_t)n_atom)) * sizeof(double) +
            (size_t)npad * 3 * sizeof(double);   // owner slots of w^x (only with weight derivatives)
 }
 
