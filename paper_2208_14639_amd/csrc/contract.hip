@@ -131,13 +131,7 @@ __device__ __forceinline__ void tile_f64(int64_t npad, int64_t jlen, int32_t Pp,
             sA[tid] = P0[j0 + tid];
             sB[tid] = P1[j0 + tid];
         }
-        // rows (j, c) for j in [j0, j0 + kJC), columns [col0, col0 + NC)
-        constexpr int H2 = NC / 2;
-        for (int e = tid; e < kJC * 2 * H2; e += 256) {
-            const int row = e / H2, cc = e - row * H2;
-            const double2 v = *reinterpret_cast<const double2 *>(X + (j0 * 2 + row) * Pp + col0 + 2 * cc);
-            *reinterpret_cast<double2 *>(sX + row * NC + 2 * cc) = v;
-        }
+        stage_rows<2 * kJC, NC>(X + j0 * 2 * Pp, Pp, col0, sX);
         __syncthreads();
         // the chunk that holds this wave's outer points leaves out the self pair
         const bool diag = ibase < j0 + kJC && ibase + 16 > j0;
@@ -240,7 +234,8 @@ __device__ __forceinline__ void tile_f32(int64_t npad, int64_t jlen, int32_t Pp,
     float4 *sA = reinterpret_cast<float4 *>(smem);
     float4 *sB = sA + kJC;
     float *sX = reinterpret_cast<float *>(sB + kJC);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m = lane & 15, kq = lane >> 4;
     const int64_t ibase = itile * 64 + wave * 16;
     const int col0 = grp * NC;
@@ -288,12 +283,7 @@ __device__ __forceinline__ void tile_f32(int64_t npad, int64_t jlen, int32_t Pp,
             sA[tid] = P0[j0 + tid];
             sB[tid] = P1[j0 + tid];
         }
-        constexpr int H4 = NC / 4;
-        for (int e = tid; e < kJC * 2 * H4; e += 256) {
-            const int row = e / H4, cc = e - row * H4;
-            const float4 v = *reinterpret_cast<const float4 *>(X + (j0 * 2 + row) * Pp + col0 + 4 * cc);
-            *reinterpret_cast<float4 *>(sX + row * NC + 4 * cc) = v;
-        }
+        stage_rows<2 * kJC, NC>(X + j0 * 2 * Pp, Pp, col0, sX);
         __syncthreads();
         // the chunk that holds this wave's outer points leaves out the self pair
         const bool diag = ibase < j0 + kJC && ibase + 16 > j0;
@@ -487,12 +477,7 @@ __device__ __forceinline__ void tile_bf16x3(int64_t npad, int64_t jlen, int32_t 
         const int sub = e >= UNITS;
         xoff[k] = (uint32_t)(sub * Pp * 4 + (e - sub * UNITS)) * (uint32_t)sizeof(bf16x8);
     }
-    auto to_lds = [](const void *base, uint32_t off, bf16x8 *dst) {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, -1, 0x00027000),
-            reinterpret_cast<__attribute__((address_space(3))) void *>(
-                reinterpret_cast<uintptr_t>(dst)), 16, off, 0, 0, 0);
-    };
+    auto to_lds = [](const void *base, uint32_t off, bf16x8 *dst) { load16_lds(base, off, 0, dst); };
     // piece k of the stage at j
     auto load_piece = [&](int k, int64_t j, bf16x8 *buf) {
         if (k == PER) {
@@ -1093,12 +1078,7 @@ __global__ __launch_bounds__(256, 2) void k_contract_bf16x3_w(
         clear();
         first = false;
     };
-    auto to_lds = [](const void *base, uint32_t off, bf16x8 *dst) {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, -1, 0x00027000),
-            reinterpret_cast<__attribute__((address_space(3))) void *>(
-                reinterpret_cast<uintptr_t>(dst)), 16, off, 0, 0, 0);
-    };
+    auto to_lds = [](const void *base, uint32_t off, bf16x8 *dst) { load16_lds(base, off, 0, dst); };
     // piece k: 64 units of one array and column block (where the waves
     // outnumber the pieces left, some bring one that another wave brings too);
     // its source at j = 0 and the units from one 16-point block to the next,

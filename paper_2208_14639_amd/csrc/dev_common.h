@@ -64,6 +64,45 @@ __device__ __forceinline__ void add_row(const PartialRows &p, int64_t off, const
     mem_order();
 }
 
+// 16 bytes a lane from base + off + soff (soff wave-uniform) into LDS at dst
+// (wave-uniform) + 16 lane.  The wait is the caller's.
+__device__ __forceinline__ void load16_lds(const void *base, uint32_t off, uint32_t soff, void *dst) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, -1, 0x00027000),
+        reinterpret_cast<__attribute__((address_space(3))) void *>(reinterpret_cast<uintptr_t>(dst)),
+        16, off, soff, 0, 0);
+}
+
+// ROWS rows of Pp columns from X, columns [col0, col0 + NC), into LDS by a
+// workgroup of four waves; the caller's barrier follows.  With one column group
+// (Pp = NC) they are contiguous and go there straight, 1 KiB per wave and load,
+// for a scalar addition each; otherwise through registers, whose row and column
+// arithmetic takes 13 of 46 VALU instructions per 64 pairs of the FP32
+// contraction, which share the lanes of its matrix instructions (nine waters,
+// six blocks: 2.98 -> 2.81 ms; the FP64 response of the hexamer 5.67 -> 5.53).
+template <int ROWS, int NC, typename T>
+__device__ __forceinline__ void stage_rows(const T *__restrict__ X, int32_t Pp, int col0, T *sX) {
+    constexpr int U = NC * (int)sizeof(T) / 16;       // 16-byte units of a row
+    constexpr int LOADS = ROWS * U / 64;
+    static_assert(ROWS * U % 64 == 0, "whole loads");
+    if (Pp == NC) {
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#pragma unroll
+        for (int k = 0; k < (LOADS + 3) / 4; ++k) {
+            const int off = (wave + 4 * k) * 1024;
+            if (LOADS % 4 == 0 || wave + 4 * k < LOADS)
+                load16_lds(X, (threadIdx.x & 63) * 16, off, reinterpret_cast<char *>(sX) + off);
+        }
+        __builtin_amdgcn_s_waitcnt(0);
+    } else {
+        for (int e = threadIdx.x; e < ROWS * U; e += 256) {
+            const int row = e / U, cc = e - row * U;
+            reinterpret_cast<float4 *>(sX)[e] =
+                reinterpret_cast<const float4 *>(X + (int64_t)row * Pp + col0)[cc];
+        }
+    }
+}
+
 // 1/x in FP32 (hardware estimate, about 1 ulp).
 __device__ __forceinline__ float rcp32(float x) { return __builtin_amdgcn_rcpf(x); }
 

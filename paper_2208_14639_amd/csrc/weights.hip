@@ -242,10 +242,7 @@ __global__ __launch_bounds__(256, 2) void k_wcontract(int64_t npad, int64_t jlen
             sA[tid] = P0[j0 + tid];
             sB[tid] = P1[j0 + tid];
         }
-        for (int e = tid; e < kJC * NC; e += 256) {
-            const int row = e / NC, cc = e - row * NC;
-            sX[e] = X[(j0 + row) * Pp + col0 + cc];
-        }
+        stage_rows<kJC, NC>(X + j0 * Pp, Pp, col0, sX);
         __syncthreads();
         // the chunk that holds this wave's outer points leaves out the self
         // pair (its rows Phi + c_i Phi_g and Phi; R^2 Phi_g vanishes there)
