@@ -47,6 +47,8 @@
 #include <type_traits>
 
 #include "dev_common.h"
+#include <algorithm>
+
 #include "grid_tile.h"
 #include "vv10_internal.h"
 
@@ -954,6 +956,77 @@ __global__ __launch_bounds__(512, 1) void k_contract_persistent_wide(
 
 __global__ void k_zero_counter(int32_t *c) { *c = 0; }
 
+// The grid pass (with the pair integrals) and the contraction of a small call
+// as one launch: workgroups b < ngrid are grid units, the others contraction
+// tiles, which need nothing from each other.  A grid of a few hundred units
+// leaves part of the chip idle by itself; the tiles fill it.  A Hessian call of
+// one water (N 1500, FP64) 153 -> 133 us, of two (N 4200) 267 -> 248 in FP64,
+// 230 -> 214 in FP32, 205 -> 185 in split-BF16; of four (N 12000, 2256 units)
+// 1243 -> 1225 and 573 -> 555; the hexamer (N 27000, 7776 units), whose tiles run
+// with the grid pass's registers here, 7.09 -> 7.18 ms in FP64: the line is at
+// ten units a CU.
+constexpr int kTogetherNcb = 4, kTogetherUnitsPerCu = 10;
+template <int PREC, int NCB, int NQ>
+__global__ __launch_bounds__(256, 3) void k_grid_contract(
+    int32_t ngrid, int32_t ntiles, int32_t bgroups, int32_t n_atom, int64_t npad, int64_t jlen,
+    int32_t Pp, const int64_t *__restrict__ seg, const int32_t *__restrict__ tile_i0,
+    const int32_t *__restrict__ tile_n, const int32_t *__restrict__ tile_atom,
+    const void *__restrict__ P0v, const void *__restrict__ P1v, const double4 *__restrict__ Pd,
+    const void *__restrict__ Xv, double *__restrict__ Z, double *__restrict__ Dpart,
+    double *__restrict__ Igrp, double *__restrict__ Yout) {
+    using T = std::conditional_t<PREC == VV10_FP64, double, float>;
+    using T4 = std::conditional_t<PREC == VV10_FP64, double4, float4>;
+    constexpr int kTile = PREC == VV10_FP64 ? smem_f64<NCB>()
+                          : PREC == VV10_MIXED_FP32 ? smem_f32<NCB>() : smem_bf16x3<NCB>();
+    constexpr int kSmem = std::max<int>(kTile, sizeof(GridLds<T4>));
+    __shared__ __attribute__((aligned(16))) char smem[kSmem];
+    // the second stage buffer of the split-BF16 form (a one-byte dummy otherwise)
+    __shared__ __attribute__((aligned(16))) char smem2[PREC == VV10_MIXED_BF16X3 ? kTile : 1];
+    const T4 *P0 = static_cast<const T4 *>(P0v), *P1 = static_cast<const T4 *>(P1v);
+    const int b = blockIdx.x;
+    if (b < ngrid) {
+        const int grp = b / ntiles;
+        grid_unit<T, T4, true, false>(n_atom, Pp, bgroups, npad, seg, tile_i0, tile_n, tile_atom,
+                                      P0, P1, Pd, Z, nullptr, Dpart, Igrp, b - grp * ntiles, grp,
+                                      *reinterpret_cast<GridLds<T4> *>(smem));
+        return;
+    }
+    const int it = (int)(npad / 64), k = b - ngrid, split = k / it, itile = k - split * it;
+    if constexpr (PREC == VV10_FP64)
+        tile_f64<NCB, false, NQ>(npad, jlen, Pp, P0, P1, static_cast<const double *>(Xv), Yout,
+                                 itile, 0, split, smem);
+    else if constexpr (PREC == VV10_MIXED_FP32)
+        tile_f32<NCB>(npad, jlen, Pp, P0, P1, static_cast<const float *>(Xv), Yout, itile, 0,
+                      split, smem);
+    else
+        tile_bf16x3<NCB, false, 4>(npad, jlen, Pp, P0, P1, static_cast<const bf16x8 *>(Xv),
+                                   static_cast<const bf16x8 *>(Xv) + npad * Pp * 2 / 8, Yout, itile,
+                                   0, split, smem, smem2);
+}
+
+template <int PREC, int NCB, int NQ>
+void grid_contract_launch(vv10_plan *p, const Workspace &ws) {
+    const int32_t ngrid = p->ntiles * ws.bgroups;
+    const unsigned blocks = (unsigned)(ngrid + p->npad / 64 * ws.jsplit);
+    const void *P0 = PREC == VV10_FP64 ? (const void *)p->P0 : p->P0f;
+    const void *P1 = PREC == VV10_FP64 ? (const void *)p->P1 : p->P1f;
+    k_grid_contract<PREC, NCB, NQ><<<blocks, 256, 0, p->stream>>>(
+        ngrid, p->ntiles, ws.bgroups, p->n_atom, p->npad, ws.jlen, ws.Pp, p->d_seg, p->d_tile_i0,
+        p->d_tile_n, p->d_tile_atom, P0, P1, p->P1, ws.X, ws.Z, ws.Dpart, ws.Igrp,
+        static_cast<double *>(ws.Ypart));
+}
+
+template <int NCB>
+void grid_contract_mode(vv10_plan *p, const Workspace &ws) {
+    if (p->prec == VV10_MIXED_FP32) return grid_contract_launch<VV10_MIXED_FP32, NCB, 4>(p, ws);
+    if (p->prec == VV10_MIXED_BF16X3) return grid_contract_launch<VV10_MIXED_BF16X3, NCB, 4>(p, ws);
+    const int left = ws.P - (ws.Pp - 16), nq = left > 0 ? (left + 3) / 4 : 4;
+    if (nq == 1) grid_contract_launch<VV10_FP64, NCB, 1>(p, ws);
+    else if (nq == 2) grid_contract_launch<VV10_FP64, NCB, 2>(p, ws);
+    else if (nq == 3) grid_contract_launch<VV10_FP64, NCB, 3>(p, ws);
+    else grid_contract_launch<VV10_FP64, NCB, 4>(p, ws);
+}
+
 // ---------------------------------------------------------------------------
 // Fused split-BF16 contraction for weights that move with the nuclei (one
 // column group of at most four blocks): the pair geometry of each (i, j) is
@@ -1307,6 +1380,20 @@ int contract_blocks_per_cu(vv10_precision prec, int ncb) {
 hipError_t launch_contract(vv10_plan *p, const Workspace &ws, bool screen) {
     if (ws.ncb < 1 || ws.ncb > max_ncb(p->prec)) return hipErrorInvalidValue;
     return dispatch_ncb(ws.ncb, [&](auto c) { return run<decltype(c)::value>(p, ws, screen); });
+}
+
+bool grid_contract_together(const vv10_plan *p, const Workspace &ws) {
+    return ws.ngroups == 1 && ws.ncb <= kTogetherNcb &&
+           (int64_t)p->ntiles * ws.bgroups <= kTogetherUnitsPerCu * (int64_t)p->num_cu;
+}
+
+hipError_t launch_grid_contract(vv10_plan *p, const Workspace &ws) {
+    if (!grid_contract_together(p, ws)) return hipErrorInvalidValue;
+    if (ws.ncb == 1) grid_contract_mode<1>(p, ws);
+    else if (ws.ncb == 2) grid_contract_mode<2>(p, ws);
+    else if (ws.ncb == 3) grid_contract_mode<3>(p, ws);
+    else grid_contract_mode<4>(p, ws);
+    return hipGetLastError();
 }
 
 bool fused_weighted_contract(const vv10_plan *p, const Workspace &ws) {

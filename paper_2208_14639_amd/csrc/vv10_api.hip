@@ -581,9 +581,19 @@ vv10_status vv10_nuclear_terms(vv10_plan *p, int32_t n_pert, const double *rho_x
     // the grid-term pass also produces the pair integrals E, U, W, A, B, C
     // unless the plan holds them already
     const int ints_from = p->ints_level;    // 0: all six, 3: A, B, C only, 6: none
-    hipError_t e = stage(p, VV10_STAGE_GRID, [&] {
-        return vv10::launch_grid_terms(p, weighted ? p->ww.Ze : nullptr, ints_from);
-    });
+    // a small call: packing first, then both passes in one launch (not where
+    // stages are timed, which are then the two passes)
+    const bool together = !weighted && !screen && ints_from < vv10::NI && !p->timing &&
+                          vv10::grid_contract_together(p, p->ws);
+    hipError_t e = hipSuccess;
+    if (together) {
+        e = vv10::launch_pert_prep(p, p->ws, rho_x, grad_rho_x);
+        if (e == hipSuccess) e = vv10::launch_grid_contract(p, p->ws);
+    } else {
+        e = stage(p, VV10_STAGE_GRID, [&] {
+            return vv10::launch_grid_terms(p, weighted ? p->ww.Ze : nullptr, ints_from);
+        });
+    }
     if (e == hipSuccess) p->ints_level = 6;
     if (e == hipSuccess)
         e = stage(p, VV10_STAGE_POTENTIAL, [&] {
@@ -593,7 +603,7 @@ vv10_status vv10_nuclear_terms(vv10_plan *p, int32_t n_pert, const double *rho_x
     if (e == hipSuccess && out->w_coef)
         e = hipMemcpyAsync(out->w_coef, p->F + (size_t)vv10::F_F0 * p->npad,
                            (size_t)p->n * sizeof(double), hipMemcpyDeviceToDevice, p->stream);
-    if (e == hipSuccess)
+    if (e == hipSuccess && !together)
         e = stage(p, VV10_STAGE_PERT_PREP, [&] { return vv10::launch_pert_prep(p, p->ws, rho_x, grad_rho_x, screen); });
     // weighted split-BF16 with one column group of at most four blocks: one
     // fused contraction for the main and the weight rows (timed as the
@@ -601,7 +611,7 @@ vv10_status vv10_nuclear_terms(vv10_plan *p, int32_t n_pert, const double *rho_x
     const bool fused = weighted && !screen && vv10::fused_weighted_contract(p, p->ws);
     if (e == hipSuccess && fused)
         e = stage(p, VV10_STAGE_WEIGHTS, [&] { return vv10::launch_weight_prep(p, w_x); });
-    if (e == hipSuccess)
+    if (e == hipSuccess && !together)
         e = stage(p, VV10_STAGE_CONTRACT, [&] {
             return fused ? vv10::launch_contract_weighted(p, p->ws, p->ww)
                          : vv10::launch_contract(p, p->ws, screen);

@@ -253,6 +253,10 @@ hipError_t launch_pert_prep(vv10_plan *p, const Workspace &ws, const double *rho
                             const double *grad_rho_x, bool screen = false);
 // screen: skip the (16-point, 16-column) blocks that ws.mask marks inactive.
 hipError_t launch_contract(vv10_plan *p, const Workspace &ws, bool screen = false);
+// A small unweighted, unscreened call with its pair integrals runs its grid pass
+// and its contraction as one launch.
+bool grid_contract_together(const vv10_plan *p, const Workspace &ws);
+hipError_t launch_grid_contract(vv10_plan *p, const Workspace &ws);
 // ints_from < 6: the pair integrals are formed in the same pass, as one partial
 // per atom group (group_parts; 6: not formed, the plan holds them).
 hipError_t launch_grid_terms(vv10_plan *p, double *Ze, int ints_from = 0);
