@@ -29,6 +29,8 @@
 //              columns form one group of at most four blocks the main
 //              contraction forms these pairs anyway, and the fused kernel of
 //              contract.hip evaluates both from one pair geometry.
+#include <type_traits>
+
 #include "dev_common.h"
 #include "vv10_internal.h"
 
@@ -171,33 +173,42 @@ constexpr int smem_w() {
     return 2 * kJC * (int)sizeof(typename WTraits<T>::P4) + kJC * NCB * 16 * (int)sizeof(T);
 }
 
-template <typename T, int NCB>
-__global__ __launch_bounds__(256, 2) void k_wcontract(int64_t npad, int64_t jlen, int32_t Pp,
-                                                      const typename WTraits<T>::P4 *__restrict__ P0,
-                                                      const typename WTraits<T>::P4 *__restrict__ P1,
-                                                      const T *__restrict__ X, double *__restrict__ Yout) {
+// NQ (FP64): quads of columns in the last block, 4 (the 16-column form) or fewer,
+// which go by fours on v_mfma_f64_4x4x4 as in the main contraction (hexamer,
+// P 54, N 27000: 4.66 -> 4.18 ms).
+template <typename T, int NCB, int NQ>
+__device__ __forceinline__ void tile_w(int64_t npad, int64_t jlen, int32_t Pp, int col0,
+                                       const typename WTraits<T>::P4 *__restrict__ P0,
+                                       const typename WTraits<T>::P4 *__restrict__ P1,
+                                       const T *__restrict__ X, double *__restrict__ Yout, char *smem) {
     typedef typename WTraits<T>::P4 P4;
     typedef typename WTraits<T>::Acc Acc;
-    constexpr int NC = NCB * 16;
+    constexpr int NC = NCB * 16, LB = NCB - 1;
+    constexpr int NB = NQ == 4 ? NCB : LB, NT = NQ == 4 ? 0 : NQ;   // blocks, quads
     static_assert(kFp32Run % kJC == 0, "FP32 runs end on chunk boundaries");
-    __shared__ __attribute__((aligned(16))) char smem[smem_w<T, NCB>()];
+    static_assert(NT == 0 || sizeof(T) == 8, "quads are FP64");
     P4 *sA = reinterpret_cast<P4 *>(smem);
     P4 *sB = sA + kJC;
     T *sX = reinterpret_cast<T *>(sB + kJC);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int m = lane & 15, kq = lane >> 4;
+    const int m = lane & 15, kq = lane >> 4, mq = lane & 3;
     const int64_t ibase = (int64_t)blockIdx.x * 64 + wave * 16;
-    const int col0 = blockIdx.y * NC;
     const int64_t jbeg = (int64_t)blockIdx.z * jlen;
     const int64_t jend = min(npad, jbeg + jlen);
     const P4 a0 = P0[ibase + m], a1 = P1[ibase + m];
-    Acc accp[NCB], accq[NCB], accv[NCB];
+    Acc accp[NB > 0 ? NB : 1], accq[NB > 0 ? NB : 1], accv[NB > 0 ? NB : 1];
+    T tp[NT > 0 ? NT : 1], tq[NT > 0 ? NT : 1], tv[NT > 0 ? NT : 1];
+    auto clear = [&]() {
 #pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) {
-        accp[cb] = (Acc){0, 0, 0, 0};
-        accq[cb] = (Acc){0, 0, 0, 0};
-        accv[cb] = (Acc){0, 0, 0, 0};
-    }
+        for (int cb = 0; cb < NB; ++cb) {
+            accp[cb] = (Acc){0, 0, 0, 0};
+            accq[cb] = (Acc){0, 0, 0, 0};
+            accv[cb] = (Acc){0, 0, 0, 0};
+        }
+#pragma unroll
+        for (int t = 0; t < NT; ++t) tp[t] = tq[t] = tv[t] = 0;
+    };
+    clear();
     // FP64 sums are stored once at the end; FP32 sums go into the partials
     // after each run of kFp32Run points
     const PartialRows Yb(Yout, blockIdx.z, npad * 3 * Pp, sizeof(T) == 4 && partials_f32(npad, jlen));
@@ -210,7 +221,7 @@ __global__ __launch_bounds__(256, 2) void k_wcontract(int64_t npad, int64_t jlen
             if constexpr (sizeof(T) == 8) {
                 double *y = Yb.y + off;
 #pragma unroll
-                for (int cb = 0; cb < NCB; ++cb) {
+                for (int cb = 0; cb < NB; ++cb) {
                     y[0 * Pp + cb * 16] = accp[cb][r];
                     y[1 * Pp + cb * 16] = accq[cb][r];
                     y[2 * Pp + cb * 16] = accv[cb][r];
@@ -228,12 +239,17 @@ __global__ __launch_bounds__(256, 2) void k_wcontract(int64_t npad, int64_t jlen
                 add_row<NCB>(Yb, off + 2 * (int64_t)Pp, v[2], first);
             }
         }
+        // 4x4x4: lane l holds row 4 ((l/4)%4) + l/16, column l%4
+        if constexpr (NT > 0) {
+            double *y = Yb.y + (ibase + 4 * ((lane >> 2) & 3) + kq) * 3 * Pp + col0 + LB * 16 + mq;
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) {
-            accp[cb] = (Acc){0, 0, 0, 0};
-            accq[cb] = (Acc){0, 0, 0, 0};
-            accv[cb] = (Acc){0, 0, 0, 0};
+            for (int t = 0; t < NT; ++t) {
+                y[0 * Pp + 4 * t] = tp[t];
+                y[1 * Pp + 4 * t] = tq[t];
+                y[2 * Pp + 4 * t] = tv[t];
+            }
         }
+        clear();
         first = false;
     };
     for (int64_t j0 = jbeg; j0 < jend; j0 += kJC) {
@@ -255,19 +271,42 @@ __global__ __launch_bounds__(256, 2) void k_wcontract(int64_t npad, int64_t jlen
             pair_w(a0, a1, sA[jl], sB[jl], kpv, kqv, kvv);
             kpv = jj == dself ? T(0) : kpv;
             kvv = jj == dself ? T(0) : kvv;
-            const T *xr = sX + jl * NC + m;
+            const T *xr = sX + jl * NC;
 #pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) {
-                const T xv = xr[cb * 16];
+            for (int cb = 0; cb < NB; ++cb) {
+                const T xv = xr[cb * 16 + m];
                 accp[cb] = WTraits<T>::mfma(kpv, xv, accp[cb]);
                 accq[cb] = WTraits<T>::mfma(kqv, xv, accq[cb]);
                 accv[cb] = WTraits<T>::mfma(kvv, xv, accv[cb]);
+            }
+            if constexpr (NT > 0) {
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    const double xv = xr[LB * 16 + 4 * t + mq];
+                    tp[t] = __builtin_amdgcn_mfma_f64_4x4x4f64(kpv, xv, tp[t], 0, 0, 0);
+                    tq[t] = __builtin_amdgcn_mfma_f64_4x4x4f64(kqv, xv, tq[t], 0, 0, 0);
+                    tv[t] = __builtin_amdgcn_mfma_f64_4x4x4f64(kvv, xv, tv[t], 0, 0, 0);
+                }
             }
         }
         if constexpr (sizeof(T) == 4)
             if ((j0 + kJC - jbeg) % kFp32Run == 0 && j0 + kJC < jend) flush();
     }
     flush();
+}
+
+// The launch's last group's last block holds NQ quads of columns (4: all 16).
+template <typename T, int NCB, int NQ>
+__global__ __launch_bounds__(256, 2) void k_wcontract(int64_t npad, int64_t jlen, int32_t Pp, int32_t cbase,
+                                                      const typename WTraits<T>::P4 *__restrict__ P0,
+                                                      const typename WTraits<T>::P4 *__restrict__ P1,
+                                                      const T *__restrict__ X, double *__restrict__ Yout) {
+    __shared__ __attribute__((aligned(16))) char smem[smem_w<T, NCB>()];
+    const int col0 = cbase + blockIdx.y * NCB * 16;
+    if (NQ == 4 || blockIdx.y + 1 == gridDim.y)
+        tile_w<T, NCB, NQ>(npad, jlen, Pp, col0, P0, P1, X, Yout, smem);
+    else
+        tile_w<T, NCB, 4>(npad, jlen, Pp, col0, P0, P1, X, Yout, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -322,7 +361,7 @@ constexpr int smem_wbf16() { return 2 * 2 * NCB * 16 * 4 * (int)sizeof(bf16x8); 
 // double-buffered in LDS and the A operands of the next block are formed
 // while the current block's MFMAs run.
 template <int NCB>
-__global__ __launch_bounds__(256, 2) void k_wcontract_bf16x3(int64_t npad, int64_t jlen, int32_t Pp,
+__global__ __launch_bounds__(256, 2) void k_wcontract_bf16x3(int64_t npad, int64_t jlen, int32_t Pp, int32_t cbase,
                                                              const float4 *__restrict__ P0,
                                                              const float4 *__restrict__ P1,
                                                              const bf16x8 *__restrict__ Xhi,
@@ -339,7 +378,7 @@ __global__ __launch_bounds__(256, 2) void k_wcontract_bf16x3(int64_t npad, int64
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int m = lane & 15, g = lane >> 4;
     const int64_t ibase = (int64_t)blockIdx.x * 64 + wave * 16;
-    const int col0 = blockIdx.y * NC;
+    const int col0 = cbase + blockIdx.y * NC;
     const int64_t jbeg = (int64_t)blockIdx.z * jlen;
     const int64_t jend = min(npad, jbeg + jlen);
     const float4 a0 = P0[ibase + m], a1 = P1[ibase + m];
@@ -465,38 +504,64 @@ __global__ __launch_bounds__(256, 2) void k_wcontract_bf16x3(int64_t npad, int64
     flush();
 }
 
+// groups of NCB column blocks from column cbase on.
 template <int NCB>
-hipError_t run_w(vv10_plan *p, const WeightWork &ww) {
+hipError_t run_w(vv10_plan *p, const WeightWork &ww, int32_t cbase, int groups) {
     const Workspace &ws = p->ws;
-    dim3 grid((unsigned)(p->npad / 64), (unsigned)ww.groups, (unsigned)ws.jsplit);
+    dim3 grid((unsigned)(p->npad / 64), (unsigned)groups, (unsigned)ws.jsplit);
     if (p->prec == VV10_FP64) {
-        if constexpr (NCB <= 4)
-            k_wcontract<double, NCB><<<grid, 256, 0, p->stream>>>(
-                p->npad, ws.jlen, ws.Pp, p->P0, p->P1, static_cast<const double *>(ww.Xv),
-                static_cast<double *>(ww.Ypart));
-        else
+        if constexpr (NCB <= 4) {
+            // quads of columns in the last block of the last group
+            const int left = cbase + groups * NCB * 16 == ws.Pp ? ws.P - (ws.Pp - 16) : 0;
+            const int nq = left > 0 ? (left + 3) / 4 : 4;
+            auto go = [&](auto q) {
+                k_wcontract<double, NCB, decltype(q)::value><<<grid, 256, 0, p->stream>>>(
+                    p->npad, ws.jlen, ws.Pp, cbase, p->P0, p->P1, static_cast<const double *>(ww.Xv),
+                    static_cast<double *>(ww.Ypart));
+            };
+            if (nq == 1) go(std::integral_constant<int, 1>{});
+            else if (nq == 2) go(std::integral_constant<int, 2>{});
+            else if (nq == 3) go(std::integral_constant<int, 3>{});
+            else go(std::integral_constant<int, 4>{});
+        } else {
             return hipErrorInvalidValue;
+        }
     } else if (p->prec == VV10_MIXED_FP32) {
-        k_wcontract<float, NCB><<<grid, 256, 0, p->stream>>>(
-            p->npad, ws.jlen, ws.Pp, p->P0f, p->P1f, static_cast<const float *>(ww.Xv),
+        k_wcontract<float, NCB, 4><<<grid, 256, 0, p->stream>>>(
+            p->npad, ws.jlen, ws.Pp, cbase, p->P0f, p->P1f, static_cast<const float *>(ww.Xv),
             static_cast<double *>(ww.Ypart));
     } else {
         const bf16x8 *xh = static_cast<const bf16x8 *>(ww.Xv);
         const bf16x8 *xl = xh + (size_t)p->npad * ws.Pp / 8;
         k_wcontract_bf16x3<NCB><<<grid, 256, 0, p->stream>>>(
-            p->npad, ws.jlen, ws.Pp, p->P0f, p->P1f, xh, xl, static_cast<double *>(ww.Ypart));
+            p->npad, ws.jlen, ws.Pp, cbase, p->P0f, p->P1f, xh, xl, static_cast<double *>(ww.Ypart));
     }
     return hipGetLastError();
 }
 
+hipError_t run_w(vv10_plan *p, const WeightWork &ww, int ncb, int32_t cbase, int groups) {
+    switch (ncb) {
+        case 1: return run_w<1>(p, ww, cbase, groups);
+        case 2: return run_w<2>(p, ww, cbase, groups);
+        case 3: return run_w<3>(p, ww, cbase, groups);
+        case 4: return run_w<4>(p, ww, cbase, groups);
+        case 5: return run_w<5>(p, ww, cbase, groups);
+        case 6: return run_w<6>(p, ww, cbase, groups);
+        case 7: return run_w<7>(p, ww, cbase, groups);
+        case 8: return run_w<8>(p, ww, cbase, groups);
+        default: return hipErrorInvalidValue;
+    }
+}
+
 }  // namespace
 
+// As few groups as the kernels' widest allows, of equal width but for the last:
+// every group forms the pairs again.  (Groups of exactly equal width made five
+// blocks in FP64, eight waters, five groups of one: 6.79 against 5.29 ms at N 24000.)
 void weight_shape(int32_t Pp, vv10_precision prec, WeightWork &ww) {
-    const int total = Pp / 16;
-    const int cap = max_wncb(prec);
-    ww.groups = 1;
-    while (total % ww.groups || total / ww.groups > cap) ++ww.groups;
-    ww.ncb = total / ww.groups;
+    const int total = Pp / 16, cap = max_wncb(prec);
+    ww.groups = (total + cap - 1) / cap;
+    ww.ncb = (total + ww.groups - 1) / ww.groups;
 }
 
 hipError_t launch_weight_own(vv10_plan *p, const double *w_x, double *Wown) {
@@ -527,17 +592,10 @@ hipError_t launch_weight_prep(vv10_plan *p, const double *w_x) {
 
 hipError_t launch_weight_contract(vv10_plan *p) {
     const WeightWork &ww = p->ww;
-    switch (ww.ncb) {
-        case 1: return run_w<1>(p, ww);
-        case 2: return run_w<2>(p, ww);
-        case 3: return run_w<3>(p, ww);
-        case 4: return run_w<4>(p, ww);
-        case 5: return run_w<5>(p, ww);
-        case 6: return run_w<6>(p, ww);
-        case 7: return run_w<7>(p, ww);
-        case 8: return run_w<8>(p, ww);
-        default: return hipErrorInvalidValue;
-    }
+    const int total = p->ws.Pp / 16, full = total / ww.ncb, rest = total - full * ww.ncb;
+    const hipError_t e = run_w(p, ww, ww.ncb, 0, full);
+    if (e != hipSuccess || rest == 0) return e;
+    return run_w(p, ww, rest, full * ww.ncb * 16, 1);
 }
 
 }  // namespace vv10
