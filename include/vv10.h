@@ -416,8 +416,9 @@ vv10_status vv10_batch_create(const vv10_params *params, int32_t n_mol, const in
  * kernel over the other contraction items, and a kernel over the grid-pass
  * items (molecule, grid tile, atom group); then each molecule's
  * pair-integral sums, energy and assembly as independent branches.
- * The graph is captured on the first call and replayed while the four
- * pointers stay the same.  Asynchronous on the batch's stream.
+ * The graph is captured on the first call and replayed by every call; a call
+ * with other pointers than the one before first enqueues one small kernel that
+ * tells the graph's kernels.  Asynchronous on the batch's stream.
  * Each molecule's results equal those of vv10_hessian_terms on the same
  * grid with the same tiles (same kernels, same reduction order).
  * Errors: VV10_E_ARG, VV10_E_STATE, VV10_E_HIP.

@@ -491,7 +491,9 @@ __device__ __forceinline__ double egrgr(int32_t n_atom, const double *__restrict
 __global__ __launch_bounds__(256) void k_finish(int32_t n_atom, int32_t P, int32_t Pp,
                                                 const double *__restrict__ Hsum,
                                                 const double *__restrict__ DS,
-                                                double *__restrict__ hess, double *__restrict__ grad) {
+                                                double *hess, double *__restrict__ grad,
+                                                const BatchBuffers *__restrict__ io) {
+    if (io) hess = global_ptr(io->hess);
     const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int64_t PP = (int64_t)P * P;
     if (k < PP) {
@@ -635,7 +637,8 @@ hipError_t launch_trial_response(vv10_plan *p, double *f_rho_t, double *f_gamma_
     return hipGetLastError();
 }
 
-hipError_t launch_assemble(vv10_plan *p, const vv10_nuclear_outputs &out, bool weighted) {
+hipError_t launch_assemble(vv10_plan *p, const vv10_nuclear_outputs &out, bool weighted,
+                           const BatchBuffers *io) {
     const Workspace &ws = p->ws;
     const WeightWork &ww = p->ww;
     const int64_t n = p->n;
@@ -657,7 +660,7 @@ hipError_t launch_assemble(vv10_plan *p, const vv10_nuclear_outputs &out, bool w
         if (partial_elem(p->prec, p->npad, ws.jlen) == sizeof(float)) go(static_cast<const float *>(ws.Ypart));
         else go(static_cast<const double *>(ws.Ypart));
     }
-    if (!hess && !grad) return hipGetLastError();
+    if (!hess && !grad && !io) return hipGetLastError();
     gemm_launch<2>(p, ws, ws.L, ws.Y, ws.Hpart);
     if (weighted) gemm_launch<1>(p, ws, ww.Lw, ww.Rw, ww.Hpart);
     {
@@ -670,7 +673,7 @@ hipError_t launch_assemble(vv10_plan *p, const vv10_nuclear_outputs &out, bool w
     }
     const int64_t nt = (int64_t)ws.P * ws.P + ws.P;
     k_finish<<<(unsigned)((nt + 255) / 256), 256, 0, p->stream>>>(p->n_atom, ws.P, ws.Pp, ws.Hsum,
-                                                                  ws.DS, hess, grad);
+                                                                  ws.DS, hess, grad, io);
     return hipGetLastError();
 }
 

@@ -11,7 +11,9 @@
 //           tile each (grid-position intermediates with the pair integrals)
 //   fork -> per molecule: pair integrals summed over atom groups, potential
 //           and energy, Hessian assembly -> join
-// and replays it while the caller's pointers stay the same.
+// and replays it on every run.  The graph's kernels read the caller's pointers
+// (one molecule's part of each) from a device table, which a run with other
+// pointers rewrites first, on the batch's stream: the batch is captured once.
 #include <algorithm>
 #include <new>
 #include <vector>
@@ -25,7 +27,6 @@ struct vv10_batch {
     std::vector<hipStream_t> side;
     std::vector<hipEvent_t> ev;                // fork/join events
     std::vector<vv10_plan *> plans;
-    std::vector<int64_t> rx_off, gx_off, h_off;
     vv10::BatchMol *d_mols = nullptr;
     vv10::BatchItem *d_items = nullptr;        // contraction, wide, grid lists
     int32_t *d_counter = nullptr;              // [3]: one per list
@@ -38,7 +39,10 @@ struct vv10_batch {
     int32_t n_grid_blocks = 0;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    const void *cap_ptr[4] = {nullptr, nullptr, nullptr, nullptr};
+    int64_t *d_off = nullptr;                  // [n_mol][2]: first elements in rho_x, hess
+    vv10::BatchBuffers *d_buffers = nullptr;   // [n_mol]
+    vv10::BatchBuffers buffers = {};           // the caller's, as d_buffers has them after the work enqueued so far
+    bool recorded = false;                     // a run was recorded into a caller's graph
     bool failed = false;
 };
 
@@ -57,6 +61,8 @@ void destroy_batch(vv10_batch *b) {
     vv10::dev_free(b->d_mols);
     vv10::dev_free(b->d_items);
     vv10::dev_free(b->d_counter);
+    vv10::dev_free(b->d_off);
+    vv10::dev_free(b->d_buffers);
     delete b;
 }
 
@@ -67,8 +73,7 @@ vv10_status status_of(hipError_t e) {
 }
 
 // Enqueue the whole batch on b->cap (inside stream capture).
-hipError_t enqueue_batch(vv10_batch *b, const double *rho_x, const double *grad_rho_x,
-                         double *energy, double *hess) {
+hipError_t enqueue_batch(vv10_batch *b) {
     const int K = (int)b->side.size();
     const size_t nm = b->plans.size();
     hipError_t e = hipEventRecord(b->ev[0], b->cap);
@@ -77,7 +82,7 @@ hipError_t enqueue_batch(vv10_batch *b, const double *rho_x, const double *grad_
     for (size_t m = 0; m < nm && e == hipSuccess; ++m) {
         vv10_plan *p = b->plans[m];
         p->stream = b->side[m % K];
-        e = vv10::launch_pert_prep(p, p->ws, rho_x + b->rx_off[m], grad_rho_x + b->gx_off[m]);
+        e = vv10::launch_pert_prep(p, p->ws, nullptr, nullptr, false, b->d_buffers + m);
     }
     for (int k = 0; k < K && e == hipSuccess; ++k) {
         e = hipEventRecord(b->ev[1 + k], b->side[k]);
@@ -99,10 +104,8 @@ hipError_t enqueue_batch(vv10_batch *b, const double *rho_x, const double *grad_
     for (size_t m = 0; m < nm && e == hipSuccess; ++m) {
         vv10_plan *p = b->plans[m];
         p->stream = b->side[m % K];
-        const vv10_nuclear_outputs out = {hess + b->h_off[m], nullptr, nullptr, nullptr, nullptr,
-                                          nullptr, nullptr, nullptr, nullptr, nullptr};
-        e = vv10::launch_potential(p, vv10::group_parts(p), energy + m, nullptr, nullptr);
-        if (e == hipSuccess) e = vv10::launch_assemble(p, out, false);
+        e = vv10::launch_potential(p, vv10::group_parts(p), nullptr, nullptr, nullptr, nullptr, b->d_buffers + m);
+        if (e == hipSuccess) e = vv10::launch_assemble(p, {}, false, b->d_buffers + m);
     }
     for (int k = 0; k < K && e == hipSuccess; ++k) {
         e = hipEventRecord(b->ev[2 + K + k], b->side[k]);
@@ -136,6 +139,7 @@ vv10_status vv10_batch_create(const vv10_params *params, int32_t n_mol, const in
     b->user_stream = stream;
     vv10_status st = VV10_OK;
     int64_t rx = 0, hx = 0;
+    std::vector<int64_t> off;
     for (int32_t m = 0; m < n_mol && st == VV10_OK; ++m) {
         const int64_t g0 = grid_off[m], n = grid_off[m + 1] - g0;
         const int32_t na = atom_off[m + 1] - atom_off[m];
@@ -146,9 +150,8 @@ vv10_status vv10_batch_create(const vv10_params *params, int32_t n_mol, const in
         b->plans.push_back(p);
         if (tiles) st = vv10_set_tiles(p, tiles + m);
         if (st == VV10_OK) st = vv10::ensure_workspace(p);
-        b->rx_off.push_back(rx);
-        b->gx_off.push_back(3 * rx);
-        b->h_off.push_back(hx);
+        off.push_back(rx);
+        off.push_back(hx);
         rx += (int64_t)3 * na * n;
         hx += (int64_t)9 * na * na;
     }
@@ -239,6 +242,13 @@ vv10_status vv10_batch_create(const vv10_params *params, int32_t n_mol, const in
                                 std::max<size_t>(1, items.size()) * sizeof(vv10::BatchItem));
         if (e == hipSuccess) e = vv10::dev_alloc(reinterpret_cast<void **>(&b->d_counter), 3 * sizeof(int32_t));
         if (e == hipSuccess)
+            e = vv10::dev_alloc(reinterpret_cast<void **>(&b->d_buffers),
+                                mols.size() * sizeof(vv10::BatchBuffers));
+        if (e == hipSuccess)
+            e = vv10::dev_alloc(reinterpret_cast<void **>(&b->d_off), off.size() * sizeof(int64_t));
+        if (e == hipSuccess)
+            e = hipMemcpy(b->d_off, off.data(), off.size() * sizeof(int64_t), hipMemcpyHostToDevice);
+        if (e == hipSuccess)
             e = hipMemcpy(b->d_mols, mols.data(), mols.size() * sizeof(vv10::BatchMol), hipMemcpyHostToDevice);
         if (e == hipSuccess && !items.empty())
             e = hipMemcpy(b->d_items, items.data(), items.size() * sizeof(vv10::BatchItem), hipMemcpyHostToDevice);
@@ -284,28 +294,31 @@ vv10_status vv10_batch_run(vv10_batch *b, const double *rho_x, const double *gra
                            double *energy, double *hess) {
     if (!b || b->failed) return VV10_E_STATE;
     if (!rho_x || !grad_rho_x || !energy || !hess) return VV10_E_ARG;
-    const void *ptr[4] = {rho_x, grad_rho_x, energy, hess};
     hipError_t e = hipSuccess;
-    if (!b->exec || !std::equal(ptr, ptr + 4, b->cap_ptr)) {
-        if (b->exec) (void)hipGraphExecDestroy(b->exec);
-        if (b->graph) (void)hipGraphDestroy(b->graph);
-        b->exec = nullptr;
-        b->graph = nullptr;
+    if (!b->exec) {
         e = hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal);
         if (e == hipSuccess) {
-            hipError_t e2 = enqueue_batch(b, rho_x, grad_rho_x, energy, hess);
+            hipError_t e2 = enqueue_batch(b);
             e = hipStreamEndCapture(b->cap, &b->graph);
             if (e2 != hipSuccess) e = e2;
         }
         if (e == hipSuccess) e = hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0);
-        if (e != hipSuccess) {
-            b->failed = true;
-            (void)hipGetLastError();
-            return VV10_E_HIP;
-        }
-        std::copy(ptr, ptr + 4, b->cap_ptr);
     }
-    e = hipGraphLaunch(b->exec, b->user_stream);
+    // a run recorded into a caller's graph rewrites the table whenever that
+    // graph is replayed: from then on every run writes it
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(b->user_stream, &capturing) != hipSuccess) (void)hipGetLastError();
+    if (capturing != hipStreamCaptureStatusNone) b->recorded = true;
+    // in stream order: after the replays that read the table, before the next
+    const vv10::BatchBuffers now = {rho_x, grad_rho_x, energy, hess};
+    const vv10::BatchBuffers &was = b->buffers;
+    if (e == hipSuccess && (b->recorded || now.rho_x != was.rho_x || now.grad_rho_x != was.grad_rho_x ||
+                            now.energy != was.energy || now.hess != was.hess)) {
+        e = vv10::launch_batch_buffers((int32_t)b->plans.size(), b->d_off, now, b->d_buffers,
+                                       b->user_stream);
+        if (e == hipSuccess) b->buffers = now;
+    }
+    if (e == hipSuccess) e = hipGraphLaunch(b->exec, b->user_stream);
     if (e != hipSuccess) {
         b->failed = true;
         (void)hipGetLastError();

@@ -956,6 +956,14 @@ __global__ __launch_bounds__(512, 1) void k_contract_persistent_wide(
 
 __global__ void k_zero_counter(int32_t *c) { *c = 0; }
 
+__global__ __launch_bounds__(64) void k_batch_buffers(int32_t n_mol, const int64_t *__restrict__ off,
+                                                      BatchBuffers all, BatchBuffers *__restrict__ dst) {
+    const int32_t m = blockIdx.x * 64 + threadIdx.x;
+    if (m >= n_mol) return;
+    const int64_t rx = off[2 * m], h = off[2 * m + 1];
+    dst[m] = {all.rho_x + rx, all.grad_rho_x + 3 * rx, all.energy + m, all.hess + h};
+}
+
 // The grid pass (with the pair integrals) and the contraction of a small call
 // as one launch: workgroups b < ngrid are grid units, the others contraction
 // tiles, which need nothing from each other.  A grid of a few hundred units
@@ -1458,6 +1466,11 @@ int persistent_wide_blocks_per_cu() {
         return 0;
     }
     return nb;
+}
+hipError_t launch_batch_buffers(int32_t n_mol, const int64_t *off, const BatchBuffers &all,
+                                BatchBuffers *dst, hipStream_t stream) {
+    k_batch_buffers<<<(unsigned)((n_mol + 63) / 64), 64, 0, stream>>>(n_mol, off, all, dst);
+    return hipGetLastError();
 }
 hipError_t launch_contract_persistent_wide(const BatchMol *mols, const BatchItem *items,
                                            int32_t n_items, int32_t *counter, int n_blocks,

@@ -18,6 +18,13 @@ __device__ __forceinline__ double rcp64(double x) {
     return __builtin_fma(r, __builtin_fma(e, e, e), r);
 }
 
+// A pointer that a kernel read from memory, known to be to global memory (the
+// compiler sees that of kernel arguments alone and would use flat accesses).
+template <typename T>
+__device__ __forceinline__ T *global_ptr(T *p) {
+    return (T *)(__attribute__((address_space(1))) T *)p;
+}
+
 // Barrier for the compiler only: the memory accesses before it are issued
 // before those after it.
 __device__ __forceinline__ void mem_order() { asm volatile("" ::: "memory"); }

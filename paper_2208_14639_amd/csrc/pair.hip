@@ -168,7 +168,8 @@ __global__ __launch_bounds__(768) void k_potential(int64_t n, int64_t npad, doub
                                                    double *__restrict__ f_rho,
                                                    double *__restrict__ f_gamma, double *epart,
                                                    uint32_t *counter, double *energy,
-                                                   const int32_t *__restrict__ valid) {
+                                                   const int32_t *__restrict__ valid,
+                                                   const BatchBuffers *__restrict__ io) {
     __shared__ double sI[3][256];
     __shared__ double s[256];
     __shared__ bool last;
@@ -256,7 +257,7 @@ __global__ __launch_bounds__(768) void k_potential(int64_t n, int64_t npad, doub
         s[t] = a;
     }
     tree();
-    if (threadIdx.x == 0) energy[0] = s[0];
+    if (threadIdx.x == 0) (io ? global_ptr(io->energy) : energy)[0] = s[0];
 }
 
 }  // namespace
@@ -318,12 +319,13 @@ hipError_t launch_pair_integrals6(vv10_plan *p, double *I_out) {
 }
 
 hipError_t launch_potential(vv10_plan *p, const IntegralParts &parts, double *energy,
-                            double *f_rho, double *f_gamma, const int32_t *valid) {
+                            double *f_rho, double *f_gamma, const int32_t *valid,
+                            const BatchBuffers *io) {
     const int64_t nb = p->npad / 256;
     double *epart = p->red;               // [nb] partials, then the energy at red[nb]
     k_potential<<<(unsigned)nb, parts.nk > 0 ? 768 : 256, 0, p->stream>>>(
         p->n, p->npad, p->beta, parts, p->P1, p->F, p->I, f_rho, f_gamma, epart, energy_counter(p),
-        energy ? energy : p->red + nb, valid);
+        energy ? energy : p->red + nb, valid, io);
     return hipGetLastError();
 }
 

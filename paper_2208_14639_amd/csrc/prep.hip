@@ -164,9 +164,14 @@ __global__ __launch_bounds__(256) void k_prep(
 constexpr int TT = 32;
 template <int MODE>
 __global__ __launch_bounds__(256) void k_pert_prep(
-    int64_t n, int64_t npad, int32_t P, int32_t Pp, const double *__restrict__ rho_x,
-    const double *__restrict__ grad_rho_x, const double *__restrict__ F,
-    void *__restrict__ Xv, double *__restrict__ L, float *__restrict__ bmax) {
+    int64_t n, int64_t npad, int32_t P, int32_t Pp, const double *rho_x,
+    const double *grad_rho_x, const double *__restrict__ F,
+    void *__restrict__ Xv, double *__restrict__ L, float *__restrict__ bmax,
+    const BatchBuffers *__restrict__ io) {
+    if (io) {
+        rho_x = global_ptr(io->rho_x);
+        grad_rho_x = global_ptr(io->grad_rho_x);
+    }
     __shared__ double sr[TT][TT + 1];
     __shared__ double sg[TT][TT + 1];
     __shared__ float sm[2][8][TT];
@@ -320,18 +325,18 @@ hipError_t launch_prepare(vv10_plan *p, const double *coords, const double *w,
 }
 
 hipError_t launch_pert_prep(vv10_plan *p, const Workspace &ws, const double *rho_x,
-                            const double *grad_rho_x, bool screen) {
+                            const double *grad_rho_x, bool screen, const BatchBuffers *io) {
     dim3 grid((unsigned)((p->npad + TT - 1) / TT), (unsigned)((ws.Pp + TT - 1) / TT));
     float *bmax = screen ? ws.bmax : nullptr;
     if (p->prec == VV10_FP64)
         k_pert_prep<VV10_FP64><<<grid, 256, 0, p->stream>>>(p->n, p->npad, ws.P, ws.Pp, rho_x,
-                                                            grad_rho_x, p->F, ws.X, ws.L, bmax);
+                                                            grad_rho_x, p->F, ws.X, ws.L, bmax, io);
     else if (p->prec == VV10_MIXED_FP32)
         k_pert_prep<VV10_MIXED_FP32><<<grid, 256, 0, p->stream>>>(p->n, p->npad, ws.P, ws.Pp, rho_x,
-                                                                  grad_rho_x, p->F, ws.X, ws.L, bmax);
+                                                                  grad_rho_x, p->F, ws.X, ws.L, bmax, io);
     else
         k_pert_prep<VV10_MIXED_BF16X3><<<grid, 256, 0, p->stream>>>(p->n, p->npad, ws.P, ws.Pp, rho_x,
-                                                                    grad_rho_x, p->F, ws.X, ws.L, bmax);
+                                                                    grad_rho_x, p->F, ws.X, ws.L, bmax, io);
     if (!screen) return hipGetLastError();
     const int64_t nblk = p->npad / 16;
     k_colmax<<<(unsigned)ws.Pp, 256, 0, p->stream>>>(nblk, ws.Pp, ws.bmax, ws.colmax);

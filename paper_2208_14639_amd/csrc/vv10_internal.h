@@ -175,6 +175,19 @@ struct BatchMol {
     const double4 *Pd;     // FP64 point data (the self pair)
     double *Z, *Dpart, *Igrp;   // grid-pass outputs, as the plan's workspace holds them
 };
+// One molecule's part of the caller's buffers of a batch run.  The kernels of the
+// captured graph read it from device memory, so the graph is captured once and
+// holds for any buffers: other ones take one small kernel ahead of the replay, in
+// the order of the batch's stream.  Outside a batch a kernel gets none, and its
+// own pointers hold.
+struct BatchBuffers {
+    const double *rho_x, *grad_rho_x;
+    double *energy, *hess;
+};
+// dst[m]: the parts of molecule m, which start at off[2 m] in all.rho_x (a third
+// of all.grad_rho_x's), at off[2 m + 1] in all.hess and at m in all.energy.
+hipError_t launch_batch_buffers(int32_t n_mol, const int64_t *off, const BatchBuffers &all,
+                                BatchBuffers *dst, hipStream_t stream);
 // One unit of work of a persistent kernel: with split >= 0 a contraction
 // item (molecule, column group grp, j split, i tile itile of 16 W points,
 // where W = persistent_waves(prec), or 8 for the wide kernel); with
@@ -247,10 +260,12 @@ hipError_t launch_pair_integrals6(vv10_plan *p, double *I_out);
 // valid (device, or null): when *valid != 0 (a failed input validation)
 // nothing is written to energy, f_rho, f_gamma.
 hipError_t launch_potential(vv10_plan *p, const IntegralParts &parts, double *energy,
-                            double *f_rho, double *f_gamma, const int32_t *valid = nullptr);
+                            double *f_rho, double *f_gamma, const int32_t *valid = nullptr,
+                            const BatchBuffers *io = nullptr);
 // screen: also the block maxima and the contraction mask (ws.bmax etc. allocated).
 hipError_t launch_pert_prep(vv10_plan *p, const Workspace &ws, const double *rho_x,
-                            const double *grad_rho_x, bool screen = false);
+                            const double *grad_rho_x, bool screen = false,
+                            const BatchBuffers *io = nullptr);
 // screen: skip the (16-point, 16-column) blocks that ws.mask marks inactive.
 hipError_t launch_contract(vv10_plan *p, const Workspace &ws, bool screen = false);
 // A small unweighted, unscreened call with its pair integrals runs its grid pass
@@ -279,7 +294,9 @@ bool fused_weighted_contract(const vv10_plan *p, const Workspace &ws);
 hipError_t launch_contract_weighted(vv10_plan *p, const Workspace &ws, const WeightWork &ww);
 hipError_t launch_trial_response(vv10_plan *p, double *f_rho_t, double *f_gamma_t);
 // weighted: also the weight-derivative terms (p->ww filled by the weight stages)
-hipError_t launch_assemble(vv10_plan *p, const vv10_nuclear_outputs &out, bool weighted);
+// io: the Hessian goes to the batch's buffer.
+hipError_t launch_assemble(vv10_plan *p, const vv10_nuclear_outputs &out, bool weighted,
+                           const BatchBuffers *io = nullptr);
 
 // Layout decisions shared by the host code.
 // n_cols: contraction columns (0 = the 3 n_atom nuclear perturbations).
