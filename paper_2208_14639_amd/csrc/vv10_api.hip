@@ -468,7 +468,11 @@ vv10_status vv10_prepare(const vv10_params *params, int64_t n_grid, int32_t n_at
     std::fill_n(flag, (size_t)n_atom + 4, -1);
     flag[0] = flag[n_atom + 1] = flag[n_atom + 2] = flag[n_atom + 3] = 0;
     e = vv10::launch_prepare(p, coords, weights, atom_of, rho, grad_rho, flag);
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
+    // waited for also after an error: it may be an earlier one of this thread,
+    // reported by launches that were enqueued all the same, and the words and
+    // the plan's blocks go back to their pools below
+    const hipError_t es = hipStreamSynchronize(stream);
+    if (e == hipSuccess) e = es;
     const int32_t *fault = flag + n_atom + 1;   // density, order, atom index
     vv10_status st = e != hipSuccess ? VV10_E_HIP
                      : fault[2]      ? VV10_E_ARG
