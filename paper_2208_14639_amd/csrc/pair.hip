@@ -262,6 +262,13 @@ __global__ __launch_bounds__(768) void k_potential(int64_t n, int64_t npad, doub
 
 }  // namespace
 
+namespace {
+
+// j points of each of S splits (whole chunks).
+int64_t pair_jlen(int64_t npad, int S) { return ((npad / S + JC - 1) / JC) * JC; }
+
+}  // namespace
+
 int pair_splits(int64_t npad) {
     const int64_t blocks = npad / 64;
     int S = (int)std::min<int64_t>(16, std::max<int64_t>(1, (kPairBlocks + blocks - 1) / blocks));
@@ -272,14 +279,17 @@ int pair_splits(int64_t npad) {
     if (268 * npad <= scratch)
         while (S > 1 && (268 + 8 * NI * S) * npad > scratch - (1 << 20)) --S;
     while (S > 1 && npad / S < JC) --S;
-    return S;
+    // no empty split: whole chunks a split can cover the grid with fewer (the
+    // dimer, N 4200, 17 chunks: two a split, nine of sixteen splits)
+    const int64_t jlen = pair_jlen(npad, S);
+    return (int)((npad + jlen - 1) / jlen);
 }
 
 namespace {
 
 void pair_launch(vv10_plan *p, bool six, double *I_out, IntegralParts *parts) {
     const int S = pair_splits(p->npad);
-    const int64_t jlen = ((p->npad / S + JC - 1) / JC) * JC;
+    const int64_t jlen = pair_jlen(p->npad, S);
     dim3 grid((unsigned)(p->npad / 64), (unsigned)S);
     double *Ipart = S == 1 ? I_out : p->Ipart;
     if (p->prec == VV10_FP64) {
