@@ -61,7 +61,7 @@ Layout layout(int64_t npad, int32_t n_atom) {
     L.P1f = take((size_t)npad * sizeof(float4));
     L.F = take((size_t)vv10::NF * npad * sizeof(double));
     L.I = take((size_t)vv10::NI * npad * sizeof(double));
-    const int S = vv10::pair_splits(npad);
+    const int S = vv10::pair_splits(npad, n_atom);
     L.Ipart = S > 1 ? take((size_t)S * vv10::NI * npad * sizeof(double)) : 0;
     L.atom_of = take((size_t)npad * sizeof(int32_t));
     L.red = take(vv10::reduction_doubles(npad) * sizeof(double));

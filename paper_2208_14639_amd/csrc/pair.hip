@@ -269,15 +269,15 @@ int64_t pair_jlen(int64_t npad, int S) { return ((npad / S + JC - 1) / JC) * JC;
 
 }  // namespace
 
-int pair_splits(int64_t npad) {
+int pair_splits(int64_t npad, int32_t n_atom) {
     const int64_t blocks = npad / 64;
     int S = (int)std::min<int64_t>(16, std::max<int64_t>(1, (kPairBlocks + blocks - 1) / blocks));
     // a grid that fits vv10_energy_potential_noalloc's scratch without
-    // partials keeps fitting (about 268 bytes a point besides them), and both
-    // paths split alike
-    const int64_t scratch = VV10_NOALLOC_SCRATCH_BYTES;
-    if (268 * npad <= scratch)
-        while (S > 1 && (268 + 8 * NI * S) * npad > scratch - (1 << 20)) --S;
+    // partials keeps fitting (about 268 bytes a point and 4 an atom besides
+    // them), and both paths split alike
+    const int64_t scratch = VV10_NOALLOC_SCRATCH_BYTES, rest = 268 * npad + 4 * (int64_t)n_atom;
+    if (rest <= scratch)
+        while (S > 1 && rest + 8 * NI * S * npad > scratch - (1 << 20)) --S;
     while (S > 1 && npad / S < JC) --S;
     // no empty split: whole chunks a split can cover the grid with fewer (the
     // dimer, N 4200, 17 chunks: two a split, nine of sixteen splits)
@@ -288,7 +288,7 @@ int pair_splits(int64_t npad) {
 namespace {
 
 void pair_launch(vv10_plan *p, bool six, double *I_out, IntegralParts *parts) {
-    const int S = pair_splits(p->npad);
+    const int S = pair_splits(p->npad, p->n_atom);
     const int64_t jlen = pair_jlen(p->npad, S);
     dim3 grid((unsigned)(p->npad / 64), (unsigned)S);
     double *Ipart = S == 1 ? I_out : p->Ipart;

@@ -99,8 +99,8 @@ namespace {
 size_t base_bytes(int64_t npad, int32_t n_atom, int64_t ntiles_bound) {
     size_t b = 2 * (size_t)npad * sizeof(double4) + 2 * (size_t)npad * sizeof(float4);
     b += (size_t)vv10::NF * npad * sizeof(double) + (size_t)vv10::NI * npad * sizeof(double);
-    if (vv10::pair_splits(npad) > 1)
-        b += (size_t)vv10::pair_splits(npad) * vv10::NI * npad * sizeof(double);
+    if (vv10::pair_splits(npad, n_atom) > 1)
+        b += (size_t)vv10::pair_splits(npad, n_atom) * vv10::NI * npad * sizeof(double);
     b += (size_t)npad * sizeof(int32_t) + (size_t)(n_atom + 1) * sizeof(int64_t);
     b += (size_t)(3 * ntiles_bound + n_atom + 1) * sizeof(int32_t);
     b += vv10::reduction_doubles(npad) * sizeof(double) + (size_t)(n_atom + 2) * sizeof(int32_t);
@@ -443,8 +443,8 @@ vv10_status vv10_prepare(const vv10_params *params, int64_t n_grid, int32_t n_at
     if (e == hipSuccess) e = dalloc(&p->P1f, npad);
     if (e == hipSuccess) e = dalloc(&p->F, (size_t)vv10::NF * npad);
     if (e == hipSuccess) e = dalloc(&p->I, (size_t)vv10::NI * npad);
-    if (e == hipSuccess && vv10::pair_splits(npad) > 1)
-        e = dalloc(&p->Ipart, (size_t)vv10::pair_splits(npad) * vv10::NI * npad);
+    if (e == hipSuccess && vv10::pair_splits(npad, n_atom) > 1)
+        e = dalloc(&p->Ipart, (size_t)vv10::pair_splits(npad, n_atom) * vv10::NI * npad);
     if (e == hipSuccess) e = dalloc(&p->atom_of, npad);
     if (e == hipSuccess) e = dalloc(&p->red, vv10::reduction_doubles(npad));
     if (e != hipSuccess) {

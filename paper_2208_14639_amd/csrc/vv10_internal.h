@@ -229,8 +229,8 @@ constexpr size_t kPinnedKept = 16;
 hipError_t pinned_take(void **ptr, size_t *cap);
 void pinned_give(void *ptr, size_t cap);
 
-// j splits of the pair-integral kernel for a padded grid size.
-int pair_splits(int64_t npad);
+// j splits of the pair-integral kernel for a padded grid size and atom count.
+int pair_splits(int64_t npad, int32_t n_atom);
 // Doubles of a plan's reduction scratch (centroid partials, energy partials;
 // the last holds the energy reduction's counter, which no partial reaches).
 size_t reduction_doubles(int64_t npad);

@@ -34,3 +34,14 @@ def test_no_split_is_empty(n):
     # (within the scratch of the allocation-free call, which fits all of these)
     want = min(16, -(-TARGET // (npad // 64)), npad // CHUNK)
     assert s == -(-(npad // CHUNK) // -(-(npad // CHUNK) // max(1, want))) or 268 * npad + 48 * want * npad > (63 << 20)
+
+
+@pytest.mark.parametrize("n,n_atom", [(129537, 300000), (180993, 300000), (128001, 500000),
+                                      (124161, 1000000), (180993, 1000000), (72193, 5000000),
+                                      (175361, 5000000)])
+def test_splits_leave_room_for_the_atoms(n, n_atom):
+    """A grid that fits the allocation-free call's scratch without partials keeps
+    fitting, however many (empty) atoms its flags count."""
+    from paper_2208_14639_amd import vv10
+    assert 0 < vv10.vv10_noalloc_bytes(n, n_atom) <= vv10.VV10_NOALLOC_SCRATCH_BYTES
+    splits(n, n_atom)
