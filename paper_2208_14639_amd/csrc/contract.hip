@@ -828,24 +828,21 @@ __device__ __forceinline__ void run_item(const BatchMol &d, const BatchItem &it,
         const int nq = last ? (left + 3) / 4 : 4;
         auto go = [&](auto q) __attribute__((always_inline)) {
             tile_f64<NCB, false, decltype(q)::value>(
-                d.npad, d.jlen, d.Pp, static_cast<const double4 *>(d.P0),
-                static_cast<const double4 *>(d.P1), static_cast<const double *>(d.X),
-                static_cast<double *>(d.Ypart), it.itile, it.grp, it.split, smem);
+                d.npad, d.jlen, d.Pp, global_as<double4>(d.P0), global_as<double4>(d.P1),
+                global_as<double>(d.X), global_ptr(static_cast<double *>(d.Ypart)), it.itile, it.grp, it.split, smem);
         };
         if (nq == 1) go(std::integral_constant<int, 1>{});
         else if (nq == 2) go(std::integral_constant<int, 2>{});
         else if (nq == 3) go(std::integral_constant<int, 3>{});
         else go(std::integral_constant<int, 4>{});
     } else if constexpr (PREC == VV10_MIXED_FP32) {
-        tile_f32<NCB>(d.npad, d.jlen, d.Pp, static_cast<const float4 *>(d.P0),
-                      static_cast<const float4 *>(d.P1), static_cast<const float *>(d.X),
-                      static_cast<double *>(d.Ypart), it.itile, it.grp, it.split, smem);
+        tile_f32<NCB>(d.npad, d.jlen, d.Pp, global_as<float4>(d.P0), global_as<float4>(d.P1),
+                      global_as<float>(d.X), global_ptr(static_cast<double *>(d.Ypart)), it.itile, it.grp, it.split, smem);
     } else {
-        const bf16x8 *xh = static_cast<const bf16x8 *>(d.X);
+        const bf16x8 *xh = global_as<bf16x8>(d.X);
         tile_bf16x3<NCB, false, PersistentTraits<PREC>::kWaves>(
-            d.npad, d.jlen, d.Pp, static_cast<const float4 *>(d.P0),
-            static_cast<const float4 *>(d.P1), xh, xh + d.npad * d.Pp * 2 / 8,
-            static_cast<double *>(d.Ypart), it.itile, it.grp, it.split, smem, smem2);
+            d.npad, d.jlen, d.Pp, global_as<float4>(d.P0), global_as<float4>(d.P1), xh,
+            xh + d.npad * d.Pp * 2 / 8, global_ptr(static_cast<double *>(d.Ypart)), it.itile, it.grp, it.split, smem, smem2);
     }
 }
 
@@ -853,10 +850,13 @@ __device__ __forceinline__ void run_item(const BatchMol &d, const BatchItem &it,
 // atom group at a time (with the pair integrals, as the Hessian
 // call forms them).  A kernel of its own keeps the grid pass's register
 // allocation (and the standalone grid kernel's waves per SIMD), where the
-// contraction kernels' allocations would hold it to two waves per SIMD.  At
-// four waves per SIMD the mixed form spills 8 registers; three waves without
-// spills measured slower on the 64-cluster batch (2625-2628 ms per launch
-// against 2614-2619).
+// contraction kernels' allocations would hold it to two waves per SIMD.
+// The pointers of a molecule's record are marked as global ones here and in the
+// contraction's kernels: taken for flat ones, their accesses needed vector
+// address registers, and this kernel spilled 9 or 10 (now none).  Eight clusters
+// of 2 to 30 waters, 1500 points an atom, split-BF16: contractions 51.3 + 194.9 ->
+// 50.9 + 193.3 ms, grid items 58.4 and 58.6; six of 3 to 30 with 1000 points in
+// FP64, contraction 537 -> 528 ms.
 template <int PREC>
 __global__ __launch_bounds__(64 * kGridWaves) __attribute__((amdgpu_waves_per_eu(PREC == VV10_FP64 ? 3 : 4))) void k_grid_persistent(
     const BatchMol *__restrict__ mols, const BatchItem *__restrict__ items, int32_t n_items,
@@ -874,10 +874,12 @@ __global__ __launch_bounds__(64 * kGridWaves) __attribute__((amdgpu_waves_per_eu
         const BatchItem it = items[k];
         const BatchMol d = mols[it.mol];
         // grid_unit orders its LDS writes after the previous reads itself
-        grid_unit<T, T4, true, false>(d.n_atom, d.Pp, d.bgroups, d.npad, d.seg, d.tile_i0,
-                                      d.tile_n, d.tile_atom, static_cast<const T4 *>(d.P0),
-                                      static_cast<const T4 *>(d.P1), d.Pd, d.Z, nullptr, d.Dpart,
-                                      d.Igrp, it.itile, it.grp, lds);
+        grid_unit<T, T4, true, false>(d.n_atom, d.Pp, d.bgroups, d.npad, global_ptr(d.seg),
+                                      global_ptr(d.tile_i0), global_ptr(d.tile_n),
+                                      global_ptr(d.tile_atom), global_as<T4>(d.P0),
+                                      global_as<T4>(d.P1), global_ptr(d.Pd), global_ptr(d.Z),
+                                      nullptr, global_ptr(d.Dpart), global_ptr(d.Igrp), it.itile,
+                                      it.grp, lds);
     }
 }
 
@@ -935,11 +937,11 @@ __global__ __launch_bounds__(512, 1) void k_contract_persistent_wide(
         if (k >= n_items) break;          // every workgroup leaves once the list is drained
         const BatchItem it = items[k];
         const BatchMol d = mols[it.mol];
-        const bf16x8 *xh = static_cast<const bf16x8 *>(d.X);
+        const bf16x8 *xh = global_as<bf16x8>(d.X);
         const bf16x8 *xl = xh + d.npad * d.Pp * 2 / 8;
-        const float4 *p0 = static_cast<const float4 *>(d.P0);
-        const float4 *p1 = static_cast<const float4 *>(d.P1);
-        double *y = static_cast<double *>(d.Ypart);
+        const float4 *p0 = global_as<float4>(d.P0);
+        const float4 *p1 = global_as<float4>(d.P1);
+        double *y = global_ptr(static_cast<double *>(d.Ypart));
         switch (d.ncb) {
 #define VV10_CASE(c)                                                                         \
     case c:                                                                                  \

@@ -19,10 +19,16 @@ __device__ __forceinline__ double rcp64(double x) {
 }
 
 // A pointer that a kernel read from memory, known to be to global memory (the
-// compiler sees that of kernel arguments alone and would use flat accesses).
+// compiler sees that of kernel arguments alone and would use flat accesses, whose
+// 64-bit addresses take vector registers).
 template <typename T>
 __device__ __forceinline__ T *global_ptr(T *p) {
-    return (T *)(__attribute__((address_space(1))) T *)p;
+    return (T *)(__attribute__((address_space(1))) T *)reinterpret_cast<uintptr_t>(p);
+}
+// A molecule's operand in the type that its mode holds it in.
+template <typename T>
+__device__ __forceinline__ const T *global_as(const void *p) {
+    return global_ptr(static_cast<const T *>(p));
 }
 
 // Barrier for the compiler only: the memory accesses before it are issued
