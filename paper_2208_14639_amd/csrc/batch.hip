@@ -177,7 +177,7 @@ vv10_status vv10_batch_create(const vv10_params *params, int32_t n_mol, const in
             d.n_atom = p->n_atom;
             d.bgroups = ws.bgroups;
             d.ntiles = p->ntiles;
-            d.pad0 = 0;
+            d.whole = p->whole;
             d.seg = p->d_seg;
             d.tile_i0 = p->d_tile_i0;
             d.tile_n = p->d_tile_n;

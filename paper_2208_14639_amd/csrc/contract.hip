@@ -873,13 +873,14 @@ __global__ __launch_bounds__(64 * kGridWaves) __attribute__((amdgpu_waves_per_eu
         if (k >= n_items) break;          // every workgroup leaves once the list is drained
         const BatchItem it = items[k];
         const BatchMol d = mols[it.mol];
+
         // grid_unit orders its LDS writes after the previous reads itself
         grid_unit<T, T4, true, false>(d.n_atom, d.Pp, d.bgroups, d.npad, global_ptr(d.seg),
                                       global_ptr(d.tile_i0), global_ptr(d.tile_n),
                                       global_ptr(d.tile_atom), global_as<T4>(d.P0),
                                       global_as<T4>(d.P1), global_ptr(d.Pd), global_ptr(d.Z),
                                       nullptr, global_ptr(d.Dpart), global_ptr(d.Igrp), it.itile,
-                                      it.grp, lds);
+                                      it.grp, d.whole, lds);
     }
 }
 
@@ -977,8 +978,8 @@ __global__ __launch_bounds__(64) void k_batch_buffers(int32_t n_mol, const int64
 // ten units a CU.
 constexpr int kTogetherNcb = 4, kTogetherUnitsPerCu = 10;
 template <int PREC, int NCB, int NQ>
-__global__ __launch_bounds__(256, 3) void k_grid_contract(
-    int32_t ngrid, int32_t ntiles, int32_t bgroups, int32_t n_atom, int64_t npad, int64_t jlen,
+__global__ __launch_bounds__(256, PREC == VV10_FP64 || (PREC == VV10_MIXED_BF16X3 && NCB > 2) ? 3 : 4) void k_grid_contract(
+    int32_t ngrid, int32_t ntiles, int32_t bgroups, bool whole, int32_t n_atom, int64_t npad, int64_t jlen,
     int32_t Pp, const int64_t *__restrict__ seg, const int32_t *__restrict__ tile_i0,
     const int32_t *__restrict__ tile_n, const int32_t *__restrict__ tile_atom,
     const void *__restrict__ P0v, const void *__restrict__ P1v, const double4 *__restrict__ Pd,
@@ -997,7 +998,7 @@ __global__ __launch_bounds__(256, 3) void k_grid_contract(
     if (b < ngrid) {
         const int grp = b / ntiles;
         grid_unit<T, T4, true, false>(n_atom, Pp, bgroups, npad, seg, tile_i0, tile_n, tile_atom,
-                                      P0, P1, Pd, Z, nullptr, Dpart, Igrp, b - grp * ntiles, grp,
+                                      P0, P1, Pd, Z, nullptr, Dpart, Igrp, b - grp * ntiles, grp, whole,
                                       *reinterpret_cast<GridLds<T4> *>(smem));
         return;
     }
@@ -1021,7 +1022,7 @@ void grid_contract_launch(vv10_plan *p, const Workspace &ws) {
     const void *P0 = PREC == VV10_FP64 ? (const void *)p->P0 : p->P0f;
     const void *P1 = PREC == VV10_FP64 ? (const void *)p->P1 : p->P1f;
     k_grid_contract<PREC, NCB, NQ><<<blocks, 256, 0, p->stream>>>(
-        ngrid, p->ntiles, ws.bgroups, p->n_atom, p->npad, ws.jlen, ws.Pp, p->d_seg, p->d_tile_i0,
+        ngrid, p->ntiles, ws.bgroups, p->whole, p->n_atom, p->npad, ws.jlen, ws.Pp, p->d_seg, p->d_tile_i0,
         p->d_tile_n, p->d_tile_atom, P0, P1, p->P1, ws.X, ws.Z, ws.Dpart, ws.Igrp,
         static_cast<double *>(ws.Ypart));
 }

@@ -9,14 +9,14 @@ namespace {
 // The grid pass as one workgroup per (tile, atom group): blockIdx = (tile, group).
 template <typename T, typename T4, bool INTS, bool ZE>
 __global__ __launch_bounds__(64 * kGridWaves) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1))) void k_grid(
-    int32_t n_atom, int32_t Pp, int32_t bgroups, int64_t npad, const int64_t *__restrict__ seg,
+    int32_t n_atom, int32_t Pp, int32_t bgroups, bool whole, int64_t npad, const int64_t *__restrict__ seg,
     const int32_t *__restrict__ tile_i0, const int32_t *__restrict__ tile_n,
     const int32_t *__restrict__ tile_atom, const T4 *__restrict__ P0,
     const T4 *__restrict__ P1, const double4 *__restrict__ Pd, double *__restrict__ Z,
     double *__restrict__ Ze, double *__restrict__ Dpart, double *__restrict__ Ipart) {
     __shared__ GridLds<T4> lds;
     grid_unit<T, T4, INTS, ZE>(n_atom, Pp, bgroups, npad, seg, tile_i0, tile_n, tile_atom, P0, P1,
-                               Pd, Z, Ze, Dpart, Ipart, blockIdx.x, blockIdx.y, lds);
+                               Pd, Z, Ze, Dpart, Ipart, blockIdx.x, blockIdx.y, whole, lds);
 }
 
 // Gradient pass (Section II.A): the pair integrals E, U, W of every outer
@@ -30,7 +30,7 @@ __global__ __launch_bounds__(64 * kGridWaves) __attribute__((amdgpu_waves_per_eu
 // Without INTS (the plan already holds E, U, W) only the grid sums are formed.
 template <typename T, typename T4, bool INTS>
 __global__ __launch_bounds__(64 * kGridWaves) void k_grid_grad(
-    int32_t n_atom, int32_t bgroups, int64_t npad, const int64_t *__restrict__ seg,
+    int32_t n_atom, int32_t bgroups, bool whole, int64_t npad, const int64_t *__restrict__ seg,
     const int32_t *__restrict__ tile_i0, const int32_t *__restrict__ tile_n,
     const int32_t *__restrict__ tile_atom, const T4 *__restrict__ P0,
     const T4 *__restrict__ P1, const double4 *__restrict__ Pd, double *__restrict__ Gpart,
@@ -47,7 +47,8 @@ __global__ __launch_bounds__(64 * kGridWaves) void k_grid_grad(
     const double ai = live ? (double)a1.y : 0.0;
     const T oi = a0.w;
     double pint[3] = {};
-    for (int B = grp; B < n_atom; B += bgroups) {
+    const GridDeal deal(whole, wave, grp, bgroups);
+    for (int B = deal.B0; B < n_atom; B += deal.Bstep) {
         const int64_t jb = seg[B], je = seg[B + 1];
         double acc[3] = {};
         // the tile sums are antisymmetric in (A, B) (a_i e_ij symmetric,
@@ -55,9 +56,9 @@ __global__ __launch_bounds__(64 * kGridWaves) void k_grid_grad(
         // ones from the (B, A) sums; B <= A still adds to the pair integrals
         const bool gsum = B > A;
         double *gp = Gpart + ((int64_t)t * n_atom + B) * 3;
-        if (!gsum && wave == 0 && lane < 3) gp[lane] = 0.0;
+        if (!gsum && (whole || wave == 0) && lane < 3) gp[lane] = 0.0;
         if (!INTS && !gsum) continue;
-        for (int64_t j0 = jb + TG * wave; j0 < je; j0 += TG * kGridWaves) {
+        for (int64_t j0 = jb + deal.j0; j0 < je; j0 += deal.jstep) {
             wave_lds_sync();
             const int64_t j = j0 + lane;
             sA[lane] = P0[j < je ? j : jb];
@@ -101,13 +102,11 @@ __global__ __launch_bounds__(64 * kGridWaves) void k_grid_grad(
                 for (int k = 0; k < 3; ++k) pint[k] += (double)pc[k];
         }
         if (!gsum) continue;
-        __syncthreads();   // the previous sums have been read
-#pragma unroll
-        for (int k = 0; k < 3; ++k) lds.red[wave][k][lane] = acc[k];
-        __syncthreads();
-        if (wave < 3) {
-            const double tot = wave_sum(ai * 3.0 * waves_sum(lds.red, wave, lane));
-            if (lane == 0) gp[wave] = tot;
+        deal.put<3>(lds.red, lane, acc);
+#pragma unroll 1
+        for (int x = deal.x0; x < deal.x1; ++x) {
+            const double tot = wave_sum(ai * 3.0 * deal.sum(lds.red, x, lane));
+            if (lane == 0) gp[x] = tot;
         }
     }
     if (INTS) {
@@ -136,11 +135,11 @@ void grid_terms_launch(vv10_plan *p, double *Ze) {
     dim3 grid((unsigned)p->ntiles, (unsigned)ws.bgroups);
     if (p->prec == VV10_FP64)
         k_grid<double, double4, INTS, ZE><<<grid, 64 * kGridWaves, 0, p->stream>>>(
-            p->n_atom, ws.Pp, ws.bgroups, p->npad, p->d_seg, p->d_tile_i0, p->d_tile_n,
+            p->n_atom, ws.Pp, ws.bgroups, p->whole, p->npad, p->d_seg, p->d_tile_i0, p->d_tile_n,
             p->d_tile_atom, p->P0, p->P1, p->P1, ws.Z, Ze, ws.Dpart, ws.Igrp);
     else
         k_grid<float, float4, INTS, ZE><<<grid, 64 * kGridWaves, 0, p->stream>>>(
-            p->n_atom, ws.Pp, ws.bgroups, p->npad, p->d_seg, p->d_tile_i0, p->d_tile_n,
+            p->n_atom, ws.Pp, ws.bgroups, p->whole, p->npad, p->d_seg, p->d_tile_i0, p->d_tile_n,
             p->d_tile_atom, p->P0f, p->P1f, p->P1, ws.Z, Ze, ws.Dpart, ws.Igrp);
 }
 
@@ -156,11 +155,11 @@ void grid_grad_mode(vv10_plan *p) {
     dim3 grid((unsigned)p->ntiles, (unsigned)gw.bgroups);
     if (p->prec == VV10_FP64)
         k_grid_grad<double, double4, INTS><<<grid, 64 * kGridWaves, 0, p->stream>>>(
-            p->n_atom, gw.bgroups, p->npad, p->d_seg, p->d_tile_i0, p->d_tile_n, p->d_tile_atom,
+            p->n_atom, gw.bgroups, p->whole, p->npad, p->d_seg, p->d_tile_i0, p->d_tile_n, p->d_tile_atom,
             p->P0, p->P1, p->P1, gw.Gpart, gw.Igrp);
     else
         k_grid_grad<float, float4, INTS><<<grid, 64 * kGridWaves, 0, p->stream>>>(
-            p->n_atom, gw.bgroups, p->npad, p->d_seg, p->d_tile_i0, p->d_tile_n, p->d_tile_atom,
+            p->n_atom, gw.bgroups, p->whole, p->npad, p->d_seg, p->d_tile_i0, p->d_tile_n, p->d_tile_atom,
             p->P0f, p->P1f, p->P1, gw.Gpart, gw.Igrp);
 }
 

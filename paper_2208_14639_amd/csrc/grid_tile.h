@@ -33,7 +33,10 @@
 // One workgroup of kGridWaves waves per (tile of 64 outer points, group of
 // atoms B); every wave holds the tile's points, one per lane, and takes every
 // kGridWaves-th 64-point chunk of each atom B; the waves' FP64 sums are added
-// in wave order through LDS at the end of an atom.  (One wave per tile and
+// in wave order through LDS at the end of an atom.  On coarse grids
+// (grid_whole_atoms), where an atom has too few chunks for the waves and its end
+// costs more than its pairs, a wave takes whole atoms instead: 40 waters with 60
+// points an atom, grid pass 225 -> 142 us in FP64 and 148 -> 92 in FP32.  (One wave per tile and
 // group left the last round of waves half empty, 7776 waves of 24 chunks each
 // on the hexamer and 396 on the dimer for 1024 SIMDs: grid pass of the hexamer
 // 0.93 -> 0.77 ms in FP32 and 1.59 -> 1.44 in FP64, of the dimer in FP64 0.128
@@ -156,7 +159,6 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-constexpr int kGridWaves = 4;
 constexpr int kGridRed = 9;   // sums of a wave held in LDS at once
 
 // LDS of one workgroup of the grid pass.
@@ -173,6 +175,30 @@ __device__ __forceinline__ double waves_sum(const double (*red)[kGridRed][TG], i
     for (int w = 1; w < kGridWaves; ++w) v += red[w][k][lane];
     return v;
 }
+
+// What a wave of a unit takes: every kGridWaves-th 64-point chunk of each atom B of
+// the group, the waves' sums added up at the end of an atom, or (whole) every
+// kGridWaves-th atom of the group with all its chunks, whose sums are its own.
+// x0 <= x < x1: the axes that it finishes.
+struct GridDeal {
+    bool whole;
+    int wave, B0, Bstep, j0, jstep, x0, x1;
+    __device__ __forceinline__ GridDeal(bool whole_, int wave_, int grp, int bgroups)
+        : whole(whole_), wave(wave_), B0(whole ? grp + wave * bgroups : grp),
+          Bstep(whole ? kGridWaves * bgroups : bgroups), j0(whole ? 0 : TG * wave),
+          jstep(whole ? TG : TG * kGridWaves), x0(whole ? 0 : wave), x1(whole ? 3 : min(wave + 1, 3)) {}
+    // This wave's sums acc[0..N), for sum() below.
+    template <int N>
+    __device__ __forceinline__ void put(double (*red)[kGridRed][TG], int lane, const double *acc) const {
+        if (!whole) __syncthreads();   // the previous sums have been read
+#pragma unroll
+        for (int k = 0; k < N; ++k) red[wave][k][lane] = acc[k];
+        if (!whole) __syncthreads();
+    }
+    __device__ __forceinline__ double sum(const double (*red)[kGridRed][TG], int k, int lane) const {
+        return whole ? red[wave][k][lane] : waves_sum(red, k, lane);
+    }
+};
 
 // One (tile t, atom group grp) unit of the grid pass, run by a workgroup of
 // kGridWaves waves.
@@ -199,7 +225,7 @@ __device__ __forceinline__ void grid_unit(
     const int32_t *__restrict__ tile_atom, const T4 *__restrict__ P0,
     const T4 *__restrict__ P1, const double4 *__restrict__ Pd, double *__restrict__ Z,
     double *__restrict__ Ze, double *__restrict__ Dpart, double *__restrict__ Ipart, int t,
-    int grp, GridLds<T4> &lds) {
+    int grp, bool whole, GridLds<T4> &lds) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     T4 *sA = lds.a[wave], *sB = lds.b[wave];
@@ -210,12 +236,13 @@ __device__ __forceinline__ void grid_unit(
     const T4 a0 = P0[i], a1 = P1[i];
     const double ai = live ? (double)a1.y : 0.0, ci = (double)a1.z;
     double pint[6] = {};
-    for (int B = grp; B < n_atom; B += bgroups) {
+    const GridDeal deal(whole, wave, grp, bgroups);
+    for (int B = deal.B0; B < n_atom; B += deal.Bstep) {
         if (!INTS && B == A) continue;
         const int64_t jb = seg[B], je = seg[B + 1];
         const bool dsum = B > A;
         double acc[16] = {};
-        for (int64_t j0 = jb + TG * wave; j0 < je; j0 += TG * kGridWaves) {
+        for (int64_t j0 = jb + deal.j0; j0 < je; j0 += deal.jstep) {
             wave_lds_sync();
             const int64_t j = j0 + lane;
             sA[lane] = P0[j < je ? j : jb];
@@ -254,40 +281,36 @@ __device__ __forceinline__ void grid_unit(
         if (B == A) continue;
         // B > A: E^{Bgr} = 3 acc[0..2], U^{Bgr} = -3 acc[3..5]; B < A:
         // E^{Bgr} + c_i U^{Bgr} = 3 acc[0..2] (and E^{Bgr} = 3 acc[3..5] with
-        // Ze); W^{Bgr} = -3 acc[6..8].  Wave x < 3 takes axis x, and two of
-        // the six D sums.
-        __syncthreads();   // the previous sums have been read
-#pragma unroll
-        for (int k = 0; k < 9; ++k) lds.red[wave][k][lane] = acc[k];
-        __syncthreads();
+        // Ze); W^{Bgr} = -3 acc[6..8]
+        // Axis x and two of the six D sums a wave, or all.
         double *dp = Dpart + ((int64_t)t * n_atom + B) * 9;
-        if (wave < 3) {
-            const double s0 = waves_sum(lds.red, wave, lane);
-            const double s3 = waves_sum(lds.red, 3 + wave, lane);
-            const double s6 = waves_sum(lds.red, 6 + wave, lane);
+        deal.put<9>(lds.red, lane, acc);
+#pragma unroll 1
+        for (int x = deal.x0; x < deal.x1; ++x) {
+            const double s0 = deal.sum(lds.red, x, lane);
+            const double s3 = deal.sum(lds.red, 3 + x, lane);
+            const double s6 = deal.sum(lds.red, 6 + x, lane);
             if (live) {
-                Z[(i * 2 + 0) * Pp + 3 * B + wave] = 3.0 * (dsum ? s0 - ci * s3 : s0);
-                Z[(i * 2 + 1) * Pp + 3 * B + wave] = -3.0 * s6;
-                if (ZE) Ze[i * Pp + 3 * B + wave] = 3.0 * (dsum ? s0 : s3);
+                Z[(i * 2 + 0) * Pp + 3 * B + x] = 3.0 * (dsum ? s0 - ci * s3 : s0);
+                Z[(i * 2 + 1) * Pp + 3 * B + x] = -3.0 * s6;
+                if (ZE) Ze[i * Pp + 3 * B + x] = 3.0 * (dsum ? s0 : s3);
             }
             // B < A: the assembly reads both parts from the (B, A) sums
             const double tot = dsum ? wave_sum(ai * 3.0 * s0) : 0.0;
-            if (lane == 0) dp[6 + wave] = tot;
+            if (lane == 0) dp[6 + x] = tot;
         }
         if (!dsum) {
-            if (wave == 3 && lane < 6) dp[lane] = 0.0;
+            if ((whole || wave == 3) && lane < 6) dp[lane] = 0.0;
             continue;
         }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < 7; ++k) lds.red[wave][k][lane] = acc[9 + k];
-        __syncthreads();
-        if (wave < 3) {
-            const double di = -3.0 * waves_sum(lds.red, 6, lane);
+        deal.put<7>(lds.red, lane, acc + 9);
+#pragma unroll 1
+        for (int x = deal.x0; x < deal.x1; ++x) {
+            const double di = -3.0 * deal.sum(lds.red, 6, lane);
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
-                const int k = 2 * wave + q;   // xx, yy, zz, xy, xz, yz
-                const double v = 6.0 * waves_sum(lds.red, k, lane) + (k < 3 ? di : 0.0);
+                const int k = 2 * x + q;   // xx, yy, zz, xy, xz, yz
+                const double v = 6.0 * deal.sum(lds.red, k, lane) + (k < 3 ? di : 0.0);
                 const double tot = wave_sum(ai * v);
                 if (lane == 0) dp[k] = tot;
             }

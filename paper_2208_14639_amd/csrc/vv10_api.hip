@@ -15,9 +15,28 @@ using vv10::Workspace;
 
 namespace vv10 {
 
+namespace {
+
+// Atom groups of the grid pass: towards 8192 (tile, group) units.
+int32_t grid_groups(int32_t n_atom, int32_t ntiles) {
+    return std::max(1, std::min<int>(n_atom, (8192 + std::max(ntiles, 1) - 1) / std::max(ntiles, 1)));
+}
+
+}  // namespace
+
+// The line, by points per atom p and atoms (grid pass and the sum of its groups,
+// us in FP64, chunks dealt against whole atoms): p 100: 9 atoms 31 and 35, 18 39 and
+// 37, 27 61 and 53; p 160: 27 87 and 94, 36 126 and 115, 60 285 and 274; p 200: 36
+// 179 and 182, 48 293 and 295, 60 433 and 422, 120 1744 and 1599; p 240: 60 483 and
+// 500, 120 1876 and 1903.
+bool grid_whole_atoms(int64_t n, int32_t n_atom) {
+    const double p = (double)n / n_atom;
+    return p <= (n_atom >= 54 ? 208.0 : std::min(160.0, 4.5 * n_atom));
+}
+
 void plan_workspace_shape(int64_t npad, int32_t n_atom, int32_t ntiles, int num_cu,
                           vv10_precision prec, Workspace &ws, int32_t jsplit_override,
-                          int32_t bgroups_override, int32_t n_cols) {
+                          int32_t bgroups_override, int32_t n_cols, bool whole) {
     ws.P = n_cols > 0 ? n_cols : 3 * n_atom;
     const int ncb_total = (ws.P + 15) / 16;
     const int cap = max_ncb(prec);
@@ -58,7 +77,13 @@ void plan_workspace_shape(int64_t npad, int32_t n_atom, int32_t ntiles, int num_
     const int tiles = (ws.Pp + 63) / 64;
     ws.gsplit = (int)std::max<int64_t>(1, std::min<int64_t>(num_cu / (tiles * tiles), npad / 64));
     if (ws.gsplit >= 8) ws.gsplit -= ws.gsplit % 8;
-    ws.bgroups = std::max(1, std::min<int>(n_atom, (8192 + std::max(ntiles, 1) - 1) / std::max(ntiles, 1)));
+    ws.bgroups = grid_groups(n_atom, ntiles);
+    if (whole) {
+        // as many atoms at a time, one a wave, in rounds of equal length
+        const int at_once = (ws.bgroups + kGridWaves - 1) / kGridWaves * kGridWaves;
+        const int rounds = (n_atom + at_once - 1) / at_once;
+        ws.bgroups = (n_atom + rounds * kGridWaves - 1) / (rounds * kGridWaves);
+    }
     if (bgroups_override > 0) ws.bgroups = std::min<int>(n_atom, bgroups_override);
 }
 
@@ -216,7 +241,7 @@ vv10_status vv10::ensure_workspace(vv10_plan *p) {
     if (p->ws.X) return VV10_OK;
     Workspace ws;
     vv10::plan_workspace_shape(p->npad, p->n_atom, p->ntiles, p->num_cu, p->prec, ws,
-                               p->tiles_jsplit, p->tiles_bgroups);
+                               p->tiles_jsplit, p->tiles_bgroups, 0, p->whole);
     if (injected_alloc_failure()) return VV10_E_OOM;
     const size_t ch = (size_t)p->npad * 2 * ws.Pp;
     hipError_t e = hipSuccess;
@@ -287,7 +312,7 @@ static vv10_status ensure_gradient_work(vv10_plan *p) {
     if (p->gw.Gpart) return VV10_OK;
     Workspace ws;
     vv10::plan_workspace_shape(p->npad, p->n_atom, p->ntiles, p->num_cu, p->prec, ws,
-                               p->tiles_jsplit, p->tiles_bgroups);
+                               p->tiles_jsplit, p->tiles_bgroups, 0, p->whole);
     vv10::GradWork gw;
     gw.bgroups = ws.bgroups;
     hipError_t e = dalloc(&gw.Gpart, (size_t)p->ntiles * p->n_atom * 3);
@@ -503,6 +528,7 @@ vv10_status vv10_prepare(const vv10_params *params, int64_t n_grid, int32_t n_at
     }
     p->ntiles = (int32_t)p->tile_i0.size();
     p->tile_first[n_atom] = p->ntiles;
+    p->whole = vv10::grid_whole_atoms(n_grid, n_atom);
     // one host image and one copy for all grid metadata (the image lives in
     // the plan, so the copy needs no synchronisation here)
     auto align = [](size_t x) { return (x + 255) / 256 * 256; };

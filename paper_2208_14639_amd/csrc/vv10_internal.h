@@ -33,7 +33,8 @@ enum Field {
 enum Integral { I_E = 0, I_U, I_W, I_A, I_B, I_C, NI };
 
 constexpr int kPad = 256;        // npad is a multiple of this
-constexpr int kGridTile = 64;    // i points per grid-term tile (one wave)
+constexpr int kGridTile = 64;    // i points per grid-term tile (one per lane of a wave)
+constexpr int kGridWaves = 4;    // waves of a grid-pass unit
 // The mixed contractions sum at most kFp32Run consecutive j points of a tile
 // in FP32 (the MFMA accumulators) and then add those sums into the tile's
 // rows of the split's FP64 partials: FP32 within a tile, FP64 across tiles
@@ -111,6 +112,7 @@ struct vv10_plan {
     std::vector<int64_t> seg;       // host: atom segments, seg[A]..seg[A+1]
     std::vector<int32_t> tile_i0, tile_n, tile_atom, tile_first;  // grid-term tiles
     int32_t ntiles = 0;
+    bool whole = false;             // grid-pass waves take whole atoms (grid_whole_atoms)
 
     // device memory owned by the plan
     double4 *P0 = nullptr;   // [npad] (x, y, z, omega), coordinates shifted by the grid centroid
@@ -169,7 +171,7 @@ struct BatchMol {
     const void *P0, *P1;   // double4 (FP64) or float4 (mixed) point data
     const void *X;         // (p, q) channels in the plan's layout
     void *Ypart;           // [jsplit][npad][2][Pp] partial outputs
-    int32_t n_atom, bgroups, ntiles, pad0;
+    int32_t n_atom, bgroups, ntiles, whole;
     const int64_t *seg;    // [n_atom + 1] atom segments
     const int32_t *tile_i0, *tile_n, *tile_atom;   // grid-pass tiles
     const double4 *Pd;     // FP64 point data (the self pair)
@@ -298,11 +300,14 @@ hipError_t launch_trial_response(vv10_plan *p, double *f_rho_t, double *f_gamma_
 hipError_t launch_assemble(vv10_plan *p, const vv10_nuclear_outputs &out, bool weighted,
                            const BatchBuffers *io = nullptr);
 
+// Whether a wave of a grid-pass unit takes whole atoms of its group (grid_tile.h).
+bool grid_whole_atoms(int64_t n, int32_t n_atom);
+
 // Layout decisions shared by the host code.
 // n_cols: contraction columns (0 = the 3 n_atom nuclear perturbations).
 void plan_workspace_shape(int64_t npad, int32_t n_atom, int32_t ntiles, int num_cu,
                           vv10_precision prec, Workspace &ws, int32_t jsplit_override = 0,
-                          int32_t bgroups_override = 0, int32_t n_cols = 0);
+                          int32_t bgroups_override = 0, int32_t n_cols = 0, bool whole = false);
 // Bytes of the trial-response workspace (X, L and partials for n_t columns)
 // plus its pair-integral table.
 size_t response_bytes(int64_t npad, vv10_precision prec, const Workspace &ws);
