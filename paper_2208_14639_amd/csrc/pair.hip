@@ -151,6 +151,40 @@ __global__ __launch_bounds__(256) void k_sum_integrals(int64_t npad, int nout, i
     I[k * npad + i] = a;
 }
 
+// a += q[s step], and with R = 2 b += q[s step + row], over s < S in order, the
+// loads of T partials issued together.  The last T are loaded without branches
+// (past the end the last one again, added as zero): in a loop of their own they
+// cost a wait each (18 groups of the hexamer, kernel 19.3 -> 13.8 us; 36 of 12
+// waters, N 7200, 26.5 -> 16.6; 90 of 30, N 5400, 72 -> 25).  T follows S, as a
+// load of nothing still takes its turn (three groups of one water by fours 7.9 us,
+// by eights 8.8).
+template <int T, int R>
+__device__ __forceinline__ void add_parts_by(const double *__restrict__ q, int64_t step, int64_t row,
+                                             int S, double &a, double &b) {
+    for (int s0 = 0; s0 < S; s0 += T) {
+        double u[T], v[T];
+#pragma unroll
+        for (int k = 0; k < T; ++k) {
+            const double *p = q + min(s0 + k, S - 1) * step;
+            u[k] = p[0];
+            if (R == 2) v[k] = p[row];
+        }
+#pragma unroll
+        for (int k = 0; k < T; ++k) {
+            a += s0 + k < S ? u[k] : 0.0;
+            if (R == 2) b += s0 + k < S ? v[k] : 0.0;
+        }
+    }
+}
+
+template <int R>
+__device__ __forceinline__ void add_parts(const double *__restrict__ q, int64_t step, int64_t row,
+                                          int S, double &a, double &b) {
+    if (S > 8) add_parts_by<16, R>(q, step, row, S, a, b);
+    else if (S > 4) add_parts_by<8, R>(q, step, row, S, a, b);
+    else add_parts_by<4, R>(q, step, row, S, a, b);
+}
+
 // Potential and energy terms (Section II.A):
 //   f^rho_i = beta + E_i + rho_i (kappa_r U_i + omega_r W_i)
 //   f^gamma_i = rho_i omega_g W_i
@@ -191,15 +225,10 @@ __global__ __launch_bounds__(768) void k_potential(int64_t n, int64_t npad, doub
             const double *q = ip.part + (int64_t)(ip.k0 + r) * npad + i;
             double a = 0.0, b = 0.0;
             if (ip.nk == 6) {
-#pragma unroll 8
-                for (int s = 0; s < ip.S; ++s, q += step) {
-                    a += q[0];
-                    b += q[3 * npad];
-                }
+                add_parts<2>(q, step, 3 * npad, ip.S, a, b);
                 I[(r + 3) * npad + i] = b;
             } else {
-#pragma unroll 16
-                for (int s = 0; s < ip.S; ++s, q += step) a += q[0];
+                add_parts<1>(q, step, 0, ip.S, a, b);
             }
             I[(ip.k0 + r) * npad + i] = a;
             sI[r][t] = ip.k0 == 0 ? a : I[r * npad + i];
