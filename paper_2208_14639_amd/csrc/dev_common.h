@@ -93,12 +93,15 @@ __device__ __forceinline__ void load16_lds(const void *base, uint32_t off, uint3
 // arithmetic takes 13 of 46 VALU instructions per 64 pairs of the FP32
 // contraction, which share the lanes of its matrix instructions (nine waters,
 // six blocks: 2.98 -> 2.81 ms; the FP64 response of the hexamer 5.67 -> 5.53).
+// One block in FP32 stays with the registers: four loads a chunk, a wave each,
+// whose wait nothing hides (response to 16 densities at N 9600: 215 us, straight
+// into LDS 218).
 template <int ROWS, int NC, typename T>
 __device__ __forceinline__ void stage_rows(const T *__restrict__ X, int32_t Pp, int col0, T *sX) {
     constexpr int U = NC * (int)sizeof(T) / 16;       // 16-byte units of a row
     constexpr int LOADS = ROWS * U / 64;
     static_assert(ROWS * U % 64 == 0, "whole loads");
-    if (Pp == NC) {
+    if (Pp == NC && (sizeof(T) == 8 || NC > 16)) {
         const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #pragma unroll
         for (int k = 0; k < (LOADS + 3) / 4; ++k) {
