@@ -1,6 +1,6 @@
 """Registers of the built kernels, from the metadata of the library's own code
-objects: the grid pass's kernels keep everything in registers (a spill in their
-pair loops is memory traffic per pair)."""
+objects: the kernels that run over pairs keep everything in registers (a spill in
+their loops is memory traffic per pair)."""
 import os
 import re
 import struct
@@ -40,9 +40,14 @@ def kernels(tmp):
     return out
 
 
-@pytest.mark.skipif(not os.path.exists(os.path.join(LLVM, "llvm-readelf")), reason="no llvm tools")
-def test_grid_kernels_do_not_spill(tmp_path):
-    found = {k: v for k, v in kernels(str(tmp_path)).items() if re.search(r"k_grid", k)}
-    assert len(found) >= 10
+needs_llvm = pytest.mark.skipif(not os.path.exists(os.path.join(LLVM, "llvm-readelf")),
+                                reason="no llvm tools")
+
+
+@needs_llvm
+@pytest.mark.parametrize("name,count", [("k_grid", 10), ("k_w?contract", 60), ("k_pair", 4)])
+def test_pair_kernels_do_not_spill(tmp_path, name, count):
+    found = {k: v for k, v in kernels(str(tmp_path)).items() if re.search(name, k)}
+    assert len(found) >= count
     spilled = {k: v["vgpr_spill_count"] for k, v in found.items() if int(v["vgpr_spill_count"])}
     assert not spilled, spilled
