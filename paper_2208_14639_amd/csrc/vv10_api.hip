@@ -65,6 +65,14 @@ void plan_workspace_shape(int64_t npad, int32_t n_atom, int32_t ntiles, int num_
             ws.jsplit = S;
         }
     }
+    // FP64 grids that do not fill one round however they are split: as many
+    // splits as leave 256 points each, their time being that of one split.
+    // (The score counts a split of a hundredth of the slots or less as not worth
+    // it: when the kernel of three blocks came to five workgroups a CU, the 720
+    // points of four waters went from three splits to one, 50 -> 92 us.  The mixed
+    // modes keep their splits, which end their FP32 runs.)
+    const int most = (int)std::min<int64_t>(16, std::max<int64_t>(1, npad / 256));
+    if (prec == VV10_FP64 && units * most <= slots) ws.jsplit = most;
     if (jsplit_override > 0) {
         const int max_split = (int)std::max<int64_t>(1, npad / 256);
         ws.jsplit = std::max(min_split, std::min(jsplit_override, max_split));
