@@ -21,13 +21,16 @@ __global__ __launch_bounds__(64 * kGridWaves) __attribute__((amdgpu_waves_per_eu
 
 // Gradient pass (Section II.A): the pair integrals E, U, W of every outer
 // point (over all j) and, per tile t of outer points (atom A) and atom
-// B > A, Gpart[t][B][a] = sum_{i in t} a_i E^{Bgr}_{i,a} (zero for B <= A),
+// B > A, Gpart[t][B][a] = sum_{i in t} a_i E^{Bgr}_{i,a} (B <= A: not written),
 // from which the grid part of the gradient follows,
 // E_gr = -sum_{B != A} sum_{i in A} a_i E^{Bgr}_i (translational invariance),
 // the B < A terms being minus the (B, A) ones.
 // The layout (four waves a unit; grid sums of the hexamer 0.27 -> 0.21 ms in
 // FP32) and the scaled sums are those of k_grid: E^{Bgr}_i = 3 sum_j p T d.
 // Without INTS (the plan already holds E, U, W) only the grid sums are formed.
+// LDS for three sums a wave, not the nine of k_grid, leaves room for more of its
+// workgroups (sums alone, hexamer in FP32 0.20 -> 0.19 ms; 40 waters with 60 points
+// an atom in FP64 66 -> 47 us, with whole atoms a wave).
 template <typename T, typename T4, bool INTS>
 __global__ __launch_bounds__(64 * kGridWaves) void k_grid_grad(
     int32_t n_atom, int32_t bgroups, bool whole, int64_t npad, const int64_t *__restrict__ seg,
@@ -35,7 +38,7 @@ __global__ __launch_bounds__(64 * kGridWaves) void k_grid_grad(
     const int32_t *__restrict__ tile_atom, const T4 *__restrict__ P0,
     const T4 *__restrict__ P1, const double4 *__restrict__ Pd, double *__restrict__ Gpart,
     double *__restrict__ Ipart) {
-    __shared__ GridLds<T4> lds;
+    __shared__ GridLds<T4, 3> lds;
     const int t = blockIdx.x, grp = blockIdx.y, lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     T4 *sA = lds.a[wave], *sB = lds.b[wave];
@@ -55,8 +58,6 @@ __global__ __launch_bounds__(64 * kGridWaves) void k_grid_grad(
         // d_ij = -d_ji): formed for B > A only, the assembly takes the B < A
         // ones from the (B, A) sums; B <= A still adds to the pair integrals
         const bool gsum = B > A;
-        double *gp = Gpart + ((int64_t)t * n_atom + B) * 3;
-        if (!gsum && (whole || wave == 0) && lane < 3) gp[lane] = 0.0;
         if (!INTS && !gsum) continue;
         for (int64_t j0 = jb + deal.j0; j0 < je; j0 += deal.jstep) {
             wave_lds_sync();
@@ -102,7 +103,8 @@ __global__ __launch_bounds__(64 * kGridWaves) void k_grid_grad(
                 for (int k = 0; k < 3; ++k) pint[k] += (double)pc[k];
         }
         if (!gsum) continue;
-        deal.put<3>(lds.red, lane, acc);
+        deal.template put<3>(lds.red, lane, acc);
+        double *gp = Gpart + ((int64_t)t * n_atom + B) * 3;
 #pragma unroll 1
         for (int x = deal.x0; x < deal.x1; ++x) {
             const double tot = wave_sum(ai * 3.0 * deal.sum(lds.red, x, lane));

@@ -159,17 +159,18 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-constexpr int kGridRed = 9;   // sums of a wave held in LDS at once
+constexpr int kGridRed = 9;   // sums of a wave held in LDS at once (gradient pass: 3)
 
 // LDS of one workgroup of the grid pass.
-template <typename T4>
+template <typename T4, int R = kGridRed>
 struct GridLds {
     T4 a[kGridWaves][TG], b[kGridWaves][TG];   // each wave's chunk
-    double red[kGridWaves][kGridRed][TG];      // the waves' sums
+    double red[kGridWaves][R][TG];             // the waves' sums
 };
 
 // Sum k of the waves, in wave order.
-__device__ __forceinline__ double waves_sum(const double (*red)[kGridRed][TG], int k, int lane) {
+template <int R>
+__device__ __forceinline__ double waves_sum(const double (*red)[R][TG], int k, int lane) {
     double v = red[0][k][lane];
 #pragma unroll
     for (int w = 1; w < kGridWaves; ++w) v += red[w][k][lane];
@@ -188,14 +189,15 @@ struct GridDeal {
           Bstep(whole ? kGridWaves * bgroups : bgroups), j0(whole ? 0 : TG * wave),
           jstep(whole ? TG : TG * kGridWaves), x0(whole ? 0 : wave), x1(whole ? 3 : min(wave + 1, 3)) {}
     // This wave's sums acc[0..N), for sum() below.
-    template <int N>
-    __device__ __forceinline__ void put(double (*red)[kGridRed][TG], int lane, const double *acc) const {
+    template <int N, int R>
+    __device__ __forceinline__ void put(double (*red)[R][TG], int lane, const double *acc) const {
         if (!whole) __syncthreads();   // the previous sums have been read
 #pragma unroll
         for (int k = 0; k < N; ++k) red[wave][k][lane] = acc[k];
         if (!whole) __syncthreads();
     }
-    __device__ __forceinline__ double sum(const double (*red)[kGridRed][TG], int k, int lane) const {
+    template <int R>
+    __device__ __forceinline__ double sum(const double (*red)[R][TG], int k, int lane) const {
         return whole ? red[wave][k][lane] : waves_sum(red, k, lane);
     }
 };
