@@ -534,8 +534,32 @@ namespace {
 // (atom, slice) for the atom's three directions, whose per-point fields it
 // reads once: bound by the 32 N P bytes of the derivatives.  The
 // hexamer (47 MB): 13.0 + 4.6 us, against 48 with one workgroup per x.
+// Grids of at most kGradOneSlice points take one slice, whose workgroups add the
+// tile sums as well: the second launch costs more than the slices save there (a
+// kept plan of one water, N 150: 8.7 -> 5.9 us; of four, N 720: 8.7 -> 7.7).
 // Fixed-order tree reductions throughout.
-constexpr int kGradSlices = 32;
+constexpr int kGradSlices = 32, kGradOneSlice = 1024;
+
+// This lane's share of the tile sums of x = 3 A + a: -sum_{B != A} sum_{t in A}
+// Gpart[t][B]; the pass forms B > A, and a B < A term is minus the (B, A) one,
+// i.e. +Gpart[t][A] over the tiles t of B.
+__device__ __forceinline__ double tile_terms(int32_t n_atom, int A, int a, int lane,
+                                             const int32_t *__restrict__ tile_first,
+                                             const double *__restrict__ Gpart) {
+    double v = 0.0;
+    const int t0 = tile_first[A], nt = tile_first[A + 1] - t0;
+#pragma unroll 8
+    for (int k = lane; k < (n_atom - A - 1) * nt; k += 64) {
+        const int B = A + 1 + k / nt, t = t0 + k % nt;
+        v -= Gpart[((int64_t)t * n_atom + B) * 3 + a];
+    }
+#pragma unroll 8
+    for (int t = lane; t < t0; t += 64) v += Gpart[((int64_t)t * n_atom + A) * 3 + a];
+    return v;
+}
+
+// ONE: one slice, grad is written; else the slice's sums go to part.
+template <bool ONE>
 __global__ __launch_bounds__(256) void k_gradient_points(int64_t n, int64_t npad, int64_t slice,
                                                          const int32_t *__restrict__ atom_of,
                                                          const double *__restrict__ F,
@@ -543,9 +567,14 @@ __global__ __launch_bounds__(256) void k_gradient_points(int64_t n, int64_t npad
                                                          const double *__restrict__ grad_rho_x,
                                                          const double *__restrict__ w_x,
                                                          const double *__restrict__ Wown,
-                                                         double *__restrict__ part) {
+                                                         const int32_t *__restrict__ tile_first,
+                                                         const double *__restrict__ Gpart,
+                                                         double *__restrict__ part,
+                                                         double *__restrict__ grad) {
     __shared__ double red[3][4];
     const int tid = threadIdx.x, A = blockIdx.x;
+    double tiles = 0.0;                 // waves 0, 1, 2: of their direction
+    if (ONE && tid < 192) tiles = tile_terms(gridDim.x, A, tid >> 6, tid & 63, tile_first, Gpart);
     const int64_t end = min(n, (int64_t)(blockIdx.y + 1) * slice);
     double s[3] = {0.0, 0.0, 0.0};
 #pragma unroll 2
@@ -570,9 +599,17 @@ __global__ __launch_bounds__(256) void k_gradient_points(int64_t n, int64_t npad
         if ((tid & 63) == 0) red[a][tid >> 6] = s[a];
     }
     __syncthreads();
-    if (tid < 3)
+    if constexpr (ONE) {
+        const int a = tid >> 6;
+        if (a < 3) {
+            tiles = wave_sum(tiles);
+            if ((tid & 63) == 0)
+                grad[3 * A + a] = red[a][0] + red[a][1] + red[a][2] + red[a][3] + tiles;
+        }
+    } else if (tid < 3) {
         part[(int64_t)blockIdx.y * 3 * gridDim.x + 3 * A + tid] =
             red[tid][0] + red[tid][1] + red[tid][2] + red[tid][3];
+    }
 }
 
 // The slices' point sums and the tile sums: one wave per x.
@@ -584,16 +621,7 @@ __global__ __launch_bounds__(64) void k_gradient(int32_t n_atom, int S,
     const int lane = threadIdx.x, x = blockIdx.x, A = x / 3, a = x % 3;
     double v = 0.0;
     for (int s = lane; s < S; s += 64) v += part[(int64_t)s * 3 * n_atom + x];
-    // -sum_{B != A} sum_{t in A} Gpart[t][B]: the pass forms B > A; a B < A
-    // term is minus the (B, A) one, i.e. +Gpart[t][A] over the tiles t of B
-    const int t0 = tile_first[A], nt = tile_first[A + 1] - t0;
-#pragma unroll 8
-    for (int k = lane; k < (n_atom - A - 1) * nt; k += 64) {
-        const int B = A + 1 + k / nt, t = t0 + k % nt;
-        v -= Gpart[((int64_t)t * n_atom + B) * 3 + a];
-    }
-#pragma unroll 8
-    for (int t = lane; t < t0; t += 64) v += Gpart[((int64_t)t * n_atom + A) * 3 + a];
+    v += tile_terms(n_atom, A, a, lane, tile_first, Gpart);
     v = wave_sum(v);
     if (lane == 0) grad[x] = v;
 }
@@ -603,6 +631,7 @@ __global__ __launch_bounds__(64) void k_gradient(int32_t n_atom, int S,
 // Slices of k_gradient_points: their sums go where the atom groups' partial
 // integrals were (gw.Igrp, [bgroups][3][npad], which the potential has added).
 static int gradient_slices(const vv10_plan *p) {
+    if (p->n <= kGradOneSlice) return 1;
     const int64_t room = (int64_t)p->gw.bgroups * p->npad / p->n_atom;
     return (int)std::max<int64_t>(1, std::min<int64_t>({kGradSlices, room, (p->n + 255) / 256}));
 }
@@ -616,8 +645,15 @@ hipError_t launch_gradient(vv10_plan *p, const double *rho_x, const double *grad
     const int S = gradient_slices(p);
     const int64_t slice = (p->n + S - 1) / S;
     double *part = p->gw.Igrp;
-    k_gradient_points<<<dim3((unsigned)p->n_atom, (unsigned)S), 256, 0, p->stream>>>(
-        p->n, p->npad, slice, p->atom_of, p->F, rho_x, grad_rho_x, w_x, p->wown, part);
+    if (p->n <= kGradOneSlice) {
+        k_gradient_points<true><<<(unsigned)p->n_atom, 256, 0, p->stream>>>(
+            p->n, p->npad, slice, p->atom_of, p->F, rho_x, grad_rho_x, w_x, p->wown, p->d_tile_first,
+            p->gw.Gpart, part, grad);
+        return hipGetLastError();
+    }
+    k_gradient_points<false><<<dim3((unsigned)p->n_atom, (unsigned)S), 256, 0, p->stream>>>(
+        p->n, p->npad, slice, p->atom_of, p->F, rho_x, grad_rho_x, w_x, p->wown, p->d_tile_first,
+        p->gw.Gpart, part, grad);
     k_gradient<<<(unsigned)(3 * p->n_atom), 64, 0, p->stream>>>(p->n_atom, S, p->d_tile_first, part,
                                                                 p->gw.Gpart, grad);
     return hipGetLastError();
