@@ -536,7 +536,7 @@ namespace {
 // hexamer (47 MB): 13.0 + 4.6 us, against 48 with one workgroup per x.
 // Grids of at most kGradOneSlice points take one slice, whose workgroups add the
 // tile sums as well: the second launch costs more than the slices save there (a
-// kept plan of one water, N 150: 8.7 -> 5.9 us; of four, N 720: 8.7 -> 7.7).
+// kept plan of one water, N 150: 8.7 -> 5.9 us; of four, N 720: 8.7 -> 6.2).
 // Fixed-order tree reductions throughout.
 constexpr int kGradSlices = 32, kGradOneSlice = 1024;
 
@@ -558,9 +558,11 @@ __device__ __forceinline__ double tile_terms(int32_t n_atom, int A, int a, int l
     return v;
 }
 
-// ONE: one slice, grad is written; else the slice's sums go to part.
+// ONE: one slice, a workgroup per direction x (three times as many), grad is
+// written; else the slice's sums go to part.
 template <bool ONE>
 __global__ __launch_bounds__(256) void k_gradient_points(int64_t n, int64_t npad, int64_t slice,
+                                                         int32_t n_atom,
                                                          const int32_t *__restrict__ atom_of,
                                                          const double *__restrict__ F,
                                                          const double *__restrict__ rho_x,
@@ -571,44 +573,42 @@ __global__ __launch_bounds__(256) void k_gradient_points(int64_t n, int64_t npad
                                                          const double *__restrict__ Gpart,
                                                          double *__restrict__ part,
                                                          double *__restrict__ grad) {
-    __shared__ double red[3][4];
-    const int tid = threadIdx.x, A = blockIdx.x;
-    double tiles = 0.0;                 // waves 0, 1, 2: of their direction
-    if (ONE && tid < 192) tiles = tile_terms(gridDim.x, A, tid >> 6, tid & 63, tile_first, Gpart);
+    constexpr int ND = ONE ? 1 : 3;     // directions of the workgroup
+    __shared__ double red[ND][4];
+    const int tid = threadIdx.x;
+    const int A = ONE ? blockIdx.x / 3 : blockIdx.x, a0 = ONE ? blockIdx.x % 3 : 0;
+    double tiles = 0.0;                 // of the first wave
+    if (ONE && tid < 64) tiles = tile_terms(n_atom, A, a0, tid, tile_first, Gpart);
     const int64_t end = min(n, (int64_t)(blockIdx.y + 1) * slice);
-    double s[3] = {0.0, 0.0, 0.0};
+    double s[ND] = {};
 #pragma unroll 2
     for (int64_t i = (int64_t)blockIdx.y * slice + tid; i < end; i += 256) {
         const double w = F[F_W * npad + i], fr = w * F[F_FR * npad + i];
         const double fg = 2.0 * (w * F[F_FG * npad + i]);
         const double gx = F[F_GX * npad + i], gy = F[F_GY * npad + i], gz = F[F_GZ * npad + i];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
+        for (int k = 0; k < ND; ++k) {
+            const int a = a0 + k;
             const int64_t o = (int64_t)(3 * A + a) * n + i;
             const double *d = grad_rho_x + 3 * o;
-            s[a] += fr * rho_x[o] + fg * (gx * d[0] + gy * d[1] + gz * d[2]);
+            s[k] += fr * rho_x[o] + fg * (gx * d[0] + gy * d[1] + gz * d[2]);
             if (w_x) {
                 const double wx = atom_of[i] == A ? Wown[i * 3 + a] : w_x[o];
-                s[a] += wx * F[F_F0 * npad + i];
+                s[k] += wx * F[F_F0 * npad + i];
             }
         }
     }
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        s[a] = wave_sum(s[a]);
-        if ((tid & 63) == 0) red[a][tid >> 6] = s[a];
+    for (int k = 0; k < ND; ++k) {
+        s[k] = wave_sum(s[k]);
+        if ((tid & 63) == 0) red[k][tid >> 6] = s[k];
     }
+    if (ONE && tid < 64) tiles = wave_sum(tiles);
     __syncthreads();
-    if constexpr (ONE) {
-        const int a = tid >> 6;
-        if (a < 3) {
-            tiles = wave_sum(tiles);
-            if ((tid & 63) == 0)
-                grad[3 * A + a] = red[a][0] + red[a][1] + red[a][2] + red[a][3] + tiles;
-        }
-    } else if (tid < 3) {
-        part[(int64_t)blockIdx.y * 3 * gridDim.x + 3 * A + tid] =
-            red[tid][0] + red[tid][1] + red[tid][2] + red[tid][3];
+    if (tid < ND) {
+        const double v = red[tid][0] + red[tid][1] + red[tid][2] + red[tid][3];
+        if (ONE) grad[3 * A + a0] = v + tiles;
+        else part[(int64_t)blockIdx.y * 3 * n_atom + 3 * A + tid] = v;
     }
 }
 
@@ -646,14 +646,14 @@ hipError_t launch_gradient(vv10_plan *p, const double *rho_x, const double *grad
     const int64_t slice = (p->n + S - 1) / S;
     double *part = p->gw.Igrp;
     if (p->n <= kGradOneSlice) {
-        k_gradient_points<true><<<(unsigned)p->n_atom, 256, 0, p->stream>>>(
-            p->n, p->npad, slice, p->atom_of, p->F, rho_x, grad_rho_x, w_x, p->wown, p->d_tile_first,
+        k_gradient_points<true><<<(unsigned)(3 * p->n_atom), 256, 0, p->stream>>>(
+            p->n, p->npad, slice, p->n_atom, p->atom_of, p->F, rho_x, grad_rho_x, w_x, p->wown, p->d_tile_first,
             p->gw.Gpart, part, grad);
         return hipGetLastError();
     }
     k_gradient_points<false><<<dim3((unsigned)p->n_atom, (unsigned)S), 256, 0, p->stream>>>(
-        p->n, p->npad, slice, p->atom_of, p->F, rho_x, grad_rho_x, w_x, p->wown, p->d_tile_first,
-        p->gw.Gpart, part, grad);
+        p->n, p->npad, slice, p->n_atom, p->atom_of, p->F, rho_x, grad_rho_x, w_x, p->wown,
+        p->d_tile_first, p->gw.Gpart, part, grad);
     k_gradient<<<(unsigned)(3 * p->n_atom), 64, 0, p->stream>>>(p->n_atom, S, p->d_tile_first, part,
                                                                 p->gw.Gpart, grad);
     return hipGetLastError();

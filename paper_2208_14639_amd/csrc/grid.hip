@@ -1,5 +1,7 @@
 // The grid pass (Section II.B grid-position intermediates) and the gradient
 // pass's grid sums; the per-wave unit of the grid pass is in grid_tile.h.
+#include <algorithm>
+
 #include "grid_tile.h"
 
 namespace vv10 {
@@ -31,16 +33,20 @@ __global__ __launch_bounds__(64 * kGridWaves) __attribute__((amdgpu_waves_per_eu
 // LDS for three sums a wave, not the nine of k_grid, leaves room for more of its
 // workgroups (sums alone, hexamer in FP32 0.20 -> 0.19 ms; 40 waters with 60 points
 // an atom in FP64 66 -> 47 us, with whole atoms a wave).
-template <typename T, typename T4, bool INTS>
-__global__ __launch_bounds__(64 * kGridWaves) void k_grid_grad(
+// W: waves of a workgroup; one where whole atoms a wave and no integrals leave
+// them nothing to share, so that a wave without an atom B > A holds no LDS, and an
+// atom each for as many as 16384 waves (30 waters with 60 points an atom in FP64 31
+// -> 24 us, 20 with 200 points 132 -> 115).
+template <typename T, typename T4, bool INTS, int W>
+__global__ __launch_bounds__(64 * W) void k_grid_grad(
     int32_t n_atom, int32_t bgroups, bool whole, int64_t npad, const int64_t *__restrict__ seg,
     const int32_t *__restrict__ tile_i0, const int32_t *__restrict__ tile_n,
     const int32_t *__restrict__ tile_atom, const T4 *__restrict__ P0,
     const T4 *__restrict__ P1, const double4 *__restrict__ Pd, double *__restrict__ Gpart,
     double *__restrict__ Ipart) {
-    __shared__ GridLds<T4, 3> lds;
+    __shared__ GridLds<T4, 3, W> lds;
     const int t = blockIdx.x, grp = blockIdx.y, lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     T4 *sA = lds.a[wave], *sB = lds.b[wave];
     const int A = tile_atom[t];
     const int nt = tile_n[t];
@@ -50,7 +56,7 @@ __global__ __launch_bounds__(64 * kGridWaves) void k_grid_grad(
     const double ai = live ? (double)a1.y : 0.0;
     const T oi = a0.w;
     double pint[3] = {};
-    const GridDeal deal(whole, wave, grp, bgroups);
+    const GridDeal deal(W == 1 || whole, wave, grp, bgroups, W);
     for (int B = deal.B0; B < n_atom; B += deal.Bstep) {
         const int64_t jb = seg[B], je = seg[B + 1];
         double acc[3] = {};
@@ -111,7 +117,7 @@ __global__ __launch_bounds__(64 * kGridWaves) void k_grid_grad(
             if (lane == 0) gp[x] = tot;
         }
     }
-    if (INTS) {
+    if constexpr (INTS) {
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < 3; ++k) lds.red[wave][k][lane] = pint[k];
@@ -151,17 +157,17 @@ void grid_terms_mode(vv10_plan *p, double *Ze) {
     else grid_terms_launch<INTS, false>(p, Ze);
 }
 
-template <bool INTS>
-void grid_grad_mode(vv10_plan *p) {
+template <bool INTS, int W>
+void grid_grad_launch(vv10_plan *p, int32_t groups) {
     const GradWork &gw = p->gw;
-    dim3 grid((unsigned)p->ntiles, (unsigned)gw.bgroups);
+    dim3 grid((unsigned)p->ntiles, (unsigned)groups);
     if (p->prec == VV10_FP64)
-        k_grid_grad<double, double4, INTS><<<grid, 64 * kGridWaves, 0, p->stream>>>(
-            p->n_atom, gw.bgroups, p->whole, p->npad, p->d_seg, p->d_tile_i0, p->d_tile_n, p->d_tile_atom,
+        k_grid_grad<double, double4, INTS, W><<<grid, 64 * W, 0, p->stream>>>(
+            p->n_atom, groups, p->whole, p->npad, p->d_seg, p->d_tile_i0, p->d_tile_n, p->d_tile_atom,
             p->P0, p->P1, p->P1, gw.Gpart, gw.Igrp);
     else
-        k_grid_grad<float, float4, INTS><<<grid, 64 * kGridWaves, 0, p->stream>>>(
-            p->n_atom, gw.bgroups, p->whole, p->npad, p->d_seg, p->d_tile_i0, p->d_tile_n, p->d_tile_atom,
+        k_grid_grad<float, float4, INTS, W><<<grid, 64 * W, 0, p->stream>>>(
+            p->n_atom, groups, p->whole, p->npad, p->d_seg, p->d_tile_i0, p->d_tile_n, p->d_tile_atom,
             p->P0f, p->P1f, p->P1, gw.Gpart, gw.Igrp);
 }
 
@@ -172,8 +178,9 @@ hipError_t launch_grid_terms(vv10_plan *p, double *Ze, int ints_from) {
 }
 
 hipError_t launch_grid_grad(vv10_plan *p, bool ints) {
-    if (ints) grid_grad_mode<true>(p);
-    else grid_grad_mode<false>(p);
+    if (ints) grid_grad_launch<true, kGridWaves>(p, p->gw.bgroups);
+    else if (p->whole) grid_grad_launch<false, 1>(p, std::min(p->n_atom, 1 + 16384 / p->ntiles));
+    else grid_grad_launch<false, kGridWaves>(p, p->gw.bgroups);
     return hipGetLastError();
 }
 

@@ -161,11 +161,11 @@ __device__ __forceinline__ void wave_lds_sync() {
 
 constexpr int kGridRed = 9;   // sums of a wave held in LDS at once (gradient pass: 3)
 
-// LDS of one workgroup of the grid pass.
-template <typename T4, int R = kGridRed>
+// LDS of one workgroup (W waves) of the grid pass.
+template <typename T4, int R = kGridRed, int W = kGridWaves>
 struct GridLds {
-    T4 a[kGridWaves][TG], b[kGridWaves][TG];   // each wave's chunk
-    double red[kGridWaves][R][TG];             // the waves' sums
+    T4 a[W][TG], b[W][TG];   // each wave's chunk
+    double red[W][R][TG];    // the waves' sums
 };
 
 // Sum k of the waves, in wave order.
@@ -184,9 +184,10 @@ __device__ __forceinline__ double waves_sum(const double (*red)[R][TG], int k, i
 struct GridDeal {
     bool whole;
     int wave, B0, Bstep, j0, jstep, x0, x1;
-    __device__ __forceinline__ GridDeal(bool whole_, int wave_, int grp, int bgroups)
+    __device__ __forceinline__ GridDeal(bool whole_, int wave_, int grp, int bgroups,
+                                        int waves = kGridWaves)
         : whole(whole_), wave(wave_), B0(whole ? grp + wave * bgroups : grp),
-          Bstep(whole ? kGridWaves * bgroups : bgroups), j0(whole ? 0 : TG * wave),
+          Bstep(whole ? waves * bgroups : bgroups), j0(whole ? 0 : TG * wave),
           jstep(whole ? TG : TG * kGridWaves), x0(whole ? 0 : wave), x1(whole ? 3 : min(wave + 1, 3)) {}
     // This wave's sums acc[0..N), for sum() below.
     template <int N, int R>
