@@ -297,9 +297,11 @@ __global__ __launch_bounds__(64 * kGemmWaves) void k_gemm(int64_t n, int64_t npa
 #pragma unroll
         for (int c = 0; c < NB; ++c) acc[a][c] = (v4d){0.0, 0.0, 0.0, 0.0};
     }
-    // several k steps per iteration (as many as the registers hold), their
-    // loads issued before their MFMAs; the MFMAs of each accumulator run in k
-    // order
+    // several k steps per iteration, their loads issued before their MFMAs; the
+    // MFMAs of each accumulator run in k order.  As many as the loop's registers
+    // hold: four blocks a side take two steps (twenty waters 434 us; one step 500,
+    // four, which spill in the loop, 484).  The 24 registers that they do spill
+    // are in the reduction below, once a workgroup.
     constexpr int ST = NB <= 2 ? 8 : NB == 3 ? 4 : 2;
     for (int64_t k00 = rb; k00 < re; k00 += 4 * ST) {
         // loads without branches, from clamped in-range addresses (finite

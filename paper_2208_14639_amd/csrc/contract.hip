@@ -392,8 +392,8 @@ struct PairSteps {
 // VALU instructions per wave and 16-point block.  The form with the waits
 // exposed took 107 M cycles per XCD at 2.05 GHz (matrix cores busy 60 %), this
 // one 87 M at 1.88 GHz (73 %): the clock falls as the cycles do, by the card's
-// power limit, so only less work (without the VALU share: 36.9 ms) would gain
-// more.  Contraction about 50.5 -> 46.3 ms; at four blocks (hexamer), bound by
+// power limit, so only less work would gain more.  Contraction about 50.5 -> 46.3
+// ms; at four blocks (hexamer), bound by
 // VALU issue, 1.45 -> 1.30 ms.
 template <int NCB>
 constexpr int smem_bf16x3() { return (4 * NCB + 2) * 64 * (int)sizeof(bf16x8); }
@@ -670,8 +670,8 @@ __global__ __launch_bounds__(256, 2) void k_contract_f32(int64_t npad, int64_t j
 // Waves (16 outer points each) of the split-BF16 kernels, by column blocks:
 // from eight blocks on, eight waves share each staged X (two per SIMD; their
 // accumulators leave room for no more), below four waves, whose workgroups
-// then fill the SIMDs with three or four waves each (eight waves at four
-// column blocks: 1.46 against 1.29-1.30 ms on the hexamer).
+// then fill the SIMDs with three waves each or more, two at seven blocks (eight
+// waves at four column blocks: 1.46 against 1.29-1.30 ms on the hexamer).
 template <int NCB>
 constexpr int bf16_waves() { return NCB >= kWideMinNcb ? 8 : 4; }
 
@@ -775,12 +775,14 @@ auto dispatch_ncb(int ncb, F &&f) -> decltype(f(std::integral_constant<int, 1>{}
 // ---------------------------------------------------------------------------
 // Two forms each: one for every column count that the list may hold, and one for
 // lists of at most kNarrowNcb column blocks (clusters of up to eight waters),
-// whose smaller register allocation (161, 112 and 162 VGPRs for 252, 208 and
-// 190) leaves room for one or two waves more per SIMD.  Two dozen clusters of
+// whose smaller register allocation (160, 104 and 162 VGPRs for 250, 198 and
+// 189) leaves room for one or two waves more per SIMD.  Two dozen clusters of
 // 1 to 6 waters with 600 points an atom, per run: FP32 7.70 -> 6.70 ms,
 // split-BF16 4.15 -> 4.08 (the clock falls with the waits); a dozen in FP64 6.66
 // -> 6.13 (5.75 with the column quads).  With a limit of four, 16 clusters of up to eight waters took FP32
-// 6.50 ms against 5.78 and split-BF16 3.27 against 3.22.
+// 6.50 ms against 5.78 and split-BF16 3.27 against 3.22; with seven, 14 clusters of
+// up to nine waters took FP32 5.00 ms against 5.39, but FP64 10.5 against 8.8 and
+// split-BF16 3.36 against 2.79 (accumulators moved to AGPRs, one wave per SIMD).
 constexpr int kNarrowNcb = 5;
 template <int PREC>
 struct PersistentTraits;
@@ -973,9 +975,10 @@ __global__ __launch_bounds__(64) void k_batch_buffers(int32_t n_mol, const int64
 // leaves part of the chip idle by itself; the tiles fill it.  A Hessian call of
 // one water (N 1500, FP64) 153 -> 133 us, of two (N 4200) 267 -> 248 in FP64,
 // 230 -> 214 in FP32, 205 -> 185 in split-BF16; of four (N 12000, 2256 units)
-// 1243 -> 1225 and 573 -> 555; the hexamer (N 27000, 7776 units), whose tiles run
-// with the grid pass's registers here, 7.09 -> 7.18 ms in FP64: the line is at
-// ten units a CU.
+// 1243 -> 1225 and 573 -> 555; of five (N 16500, 4050 units) 2680 -> 2671 and 977 ->
+// 941, past the line.  The six of N 18000 (5184 units) lose 0.6 % in FP64 and the
+// hexamer (N 27000, 7776 units), whose tiles run with the grid pass's registers
+// here, 7.09 -> 7.18 ms: at ten units a CU the line is on the safe side.
 constexpr int kTogetherNcb = 4, kTogetherUnitsPerCu = 10;
 template <int PREC, int NCB, int NQ>
 __global__ __launch_bounds__(256, PREC == VV10_FP64 || (PREC == VV10_MIXED_BF16X3 && NCB > 2) ? 3 : 4) void k_grid_contract(
@@ -1376,10 +1379,11 @@ hipError_t run_weighted(vv10_plan *p, const Workspace &ws, const WeightWork &ww)
 
 }  // namespace
 
-// The mixed modes' counts are fixed numbers (about what the kernels' registers
-// and LDS allow), not the runtime's: the split count that follows from them
-// decides where the FP32 runs end, so a result would otherwise change in its
-// last FP32 digits whenever a compiler allocates a register more.
+// The mixed modes' counts are fixed numbers, not what the built kernels reach
+// (split-BF16 now holds three workgroups at three and four blocks and two at
+// seven): the split count that follows from them decides where the FP32 runs end,
+// so a result would otherwise change in its last FP32 digits whenever a compiler
+// allocates a register more or a kernel is rewritten.
 int contract_blocks_per_cu(vv10_precision prec, int ncb) {
     static constexpr int f32_slots[13] = {0, 8, 8, 8, 6, 5, 5, 4, 4, 3, 3, 3, 3};
     if (ncb < 1 || ncb > max_ncb(prec)) return 0;

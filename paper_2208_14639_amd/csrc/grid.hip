@@ -1,5 +1,5 @@
 // The grid pass (Section II.B grid-position intermediates) and the gradient
-// pass's grid sums; the per-wave unit of the grid pass is in grid_tile.h.
+// pass's grid sums; the unit of the grid pass (four waves) is in grid_tile.h.
 #include <algorithm>
 
 #include "grid_tile.h"

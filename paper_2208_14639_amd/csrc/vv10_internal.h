@@ -171,7 +171,7 @@ struct BatchMol {
     const void *P0, *P1;   // double4 (FP64) or float4 (mixed) point data
     const void *X;         // (p, q) channels in the plan's layout
     void *Ypart;           // [jsplit][npad][2][Pp] partial outputs
-    int32_t n_atom, bgroups, ntiles, whole;
+    int32_t n_atom, bgroups, ntiles, whole;   // whole: as vv10_plan's
     const int64_t *seg;    // [n_atom + 1] atom segments
     const int32_t *tile_i0, *tile_n, *tile_atom;   // grid-pass tiles
     const double4 *Pd;     // FP64 point data (the self pair)
